@@ -939,7 +939,9 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
         for (int o = CH; o < 64; o <<= 1) csum[e] += __shfl_xor(csum[e], o, 64);
       }
       const int n = nw + (lane % CH) * 8;
-      if (lane < CH && n < ge.N) {
+      // colpart has ceil(M / 128) rows: the last tile's second 128-row slab
+      // lies past them when their number is odd
+      if (lane < CH && n < ge.N && mw < ge.M) {
         float* P = ge.colpart + (int64_t)(mw / C::WM) * ge.N + n;
         *(f32x4_t*)P = f32x4_t{csum[0], csum[1], csum[2], csum[3]};
         *(f32x4_t*)(P + 4) = f32x4_t{csum[4], csum[5], csum[6], csum[7]};
