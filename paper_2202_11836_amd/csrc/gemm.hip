@@ -1,7 +1,7 @@
-// Dense contractions of the encoder layer: bf16 MFMA GEMM (fp32 accumulate)
-// and an fp32 vector-ALU GEMM, both with fused epilogues.
+// Dense contractions of bf16 stages: MFMA GEMM (fp32 accumulate) with fused
+// epilogues.
 //
-// bf16 path: a persistent work-group per CU walks BM x BN output tiles; its
+// A persistent work-group per CU walks BM x BN output tiles; its
 // wavefronts (8 for 256 x 256 tiles, two per SIMD; 4 otherwise) form a
 // 2 x (waves / 2) grid, each owning a sub-tile computed with
 // v_mfma_f32_32x32x16_bf16.  k-tiles of 64 go straight from HBM into a ring
@@ -16,30 +16,6 @@
 #include "kernels.h"
 
 namespace {
-
-constexpr int NT = 256;
-
-struct TileCoord {
-  int tm, tn, zs, zb;
-};
-
-// Work-group index -> (m tile, n tile).  Consecutive dispatches go round robin
-// over the 8 XCDs; remap so that each XCD receives a contiguous range of
-// tiles, then walk that range in groups of GM tile-rows so that tiles that
-// share A rows / B columns run close together on one L2.
-__device__ __forceinline__ void tile_of_block(int nbm, int nbn, int& tm, int& tn) {
-  int total = nbm * nbn;
-  int bid = blockIdx.x;
-  if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
-  constexpr int GM = 8;
-  int per_group = GM * nbn;
-  int group = bid / per_group;
-  int first_m = group * GM;
-  int gsize = min(nbm - first_m, GM);
-  int r = bid - group * per_group;
-  tm = first_m + r % gsize;
-  tn = r / gsize;
-}
 
 // Tile order inside a z slice: groups of TILE_GM tile-rows, column by column
 // within a group (tiles that share A rows / B columns run close together).
@@ -529,6 +505,8 @@ __device__ __forceinline__ void group_args(kgroup_t* gg, int p, GemmArgs& g) {
   g.alpha = a->alpha;
   g.tile = a->tile;
   g.colpart = a->colpart;
+  g.cp_batch = a->cp_batch;
+  g.cp_ld = a->cp_ld;
   g.zdiv_total = a->zdiv_total;
 }
 
@@ -951,114 +929,6 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 vector-ALU GEMM: 64 x 64 tile, BK 16, 4 x 4 outputs per thread.
-// ---------------------------------------------------------------------------
-template <int EPI>
-__device__ __forceinline__ void epi_store_f32(const GemmArgs& g, int64_t offC, int zs, int m,
-                                              int n, float v) {
-  if (EPI == EPI_PARTIAL) {
-    ((float*)g.C + (int64_t)zs * g.M * g.ldc)[(int64_t)m * g.ldc + n] = v;
-  } else if (EPI == EPI_STORE) {
-    v *= g.alpha;
-    if (g.bias) v += g.bias[n];
-    ((float*)g.C + offC)[(int64_t)m * g.ldc + n] = v;
-  } else if (EPI == EPI_GELU) {
-    const float u = v + g.bias[n];
-    ((float*)g.C + offC)[(int64_t)m * g.ldc + n] = gelu_f(u);
-    ((float*)g.C2 + offC)[(int64_t)m * g.ldc + n] = gelu_grad_f(u);
-  } else if (EPI == EPI_MUL) {
-    const float d = ((const float*)g.aux + offC)[(int64_t)m * g.ldaux + n];
-    ((float*)g.C + offC)[(int64_t)m * g.ldc + n] = v * d;
-  } else if (EPI == EPI_RESID) {
-    float r = ((const float*)g.aux + offC)[(int64_t)m * g.ldaux + n];
-    ((float*)g.C + offC)[(int64_t)m * g.ldc + n] = v + r;
-  }
-}
-
-template <bool AK, bool BKM, int EPI>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmArgs g) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int nbm = (g.M + BM - 1) / BM, nbn = (g.N + BN - 1) / BN;
-  int tm, tn;
-  tile_of_block(nbm, nbn, tm, tn);
-  const int zs = blockIdx.z % g.ksplit;
-  const int zb = blockIdx.z / g.ksplit;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const float* __restrict__ A = (const float*)g.A + batch_off(zb, g.zdiv, g.sA1, g.sA2);
-  const float* __restrict__ B = (const float*)g.B + batch_off(zb, g.zdiv, g.sB1, g.sB2);
-  const int kbeg = zs * g.kchunk;
-  const int kend = min(g.K, kbeg + g.kchunk);
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  float acc[4][4] = {};
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    for (int e = tid; e < BM * BK; e += NT) {
-      int mm, kk;
-      if (AK) { mm = e / BK; kk = e % BK; } else { kk = e / BM; mm = e % BM; }
-      int gm = m0 + mm, gk = k0 + kk;
-      float v = 0.0f;
-      if (gm < g.M && gk < kend) v = AK ? A[(int64_t)gm * g.lda + gk] : A[(int64_t)gk * g.lda + gm];
-      As[kk][mm] = v;
-    }
-    for (int e = tid; e < BN * BK; e += NT) {
-      int nn, kk;
-      if (BKM) { nn = e / BK; kk = e % BK; } else { kk = e / BN; nn = e % BN; }
-      int gn = n0 + nn, gk = k0 + kk;
-      float v = 0.0f;
-      if (gn < g.N && gk < kend) v = BKM ? B[(int64_t)gn * g.ldb + gk] : B[(int64_t)gk * g.ldb + gn];
-      Bs[kk][nn] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  const int64_t offC = batch_off(zb, g.zdiv, g.sC1, g.sC2);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
-      if (m < g.M && n < g.N) epi_store_f32<EPI>(g, offC, zs, m, n, acc[i][j]);
-    }
-}
-
-// out = sum over splits of part[z] in split order; 4 consecutive values per
-// thread (mn % 4 == 0), all splits' loads issued before the sum.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part,
-                                                            int splits, int64_t mn,
-                                                            float* __restrict__ out) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i >= mn) return;
-  f32x4_t s = *(const f32x4_t*)(part + i);
-  int z = 1;
-  for (; z + 4 <= splits; z += 4) {
-    const f32x4_t a = *(const f32x4_t*)(part + (int64_t)z * mn + i);
-    const f32x4_t b = *(const f32x4_t*)(part + (int64_t)(z + 1) * mn + i);
-    const f32x4_t c = *(const f32x4_t*)(part + (int64_t)(z + 2) * mn + i);
-    const f32x4_t d = *(const f32x4_t*)(part + (int64_t)(z + 3) * mn + i);
-    s += a;
-    s += b;
-    s += c;
-    s += d;
-  }
-  for (; z < splits; ++z) s += *(const f32x4_t*)(part + (int64_t)z * mn + i);
-  *(f32x4_t*)(out + i) = s;
-}
-
 // wgrad_group_reduce: block b serves problem q with blk0[q] <= b <
 // blk0[q + 1]; each thread sums 4 consecutive elements of one tile over the
 // tile's pieces (slots) in k order.
@@ -1187,26 +1057,6 @@ hipError_t dispatch_layout(const GemmArgs& g, bool ak, bool bk, GemmEpi epi, boo
   return dispatch_epi<BM, BN, false, true>(g, epi, out_f32, batch, st);
 }
 
-template <bool AK, bool BKM>
-hipError_t dispatch_f32(const GemmArgs& g, GemmEpi epi, int batch, hipStream_t st) {
-  int nbm = (g.M + 63) / 64, nbn = (g.N + 63) / 64;
-  dim3 grid(nbm * nbn, 1, batch * g.ksplit);
-  switch (epi) {
-    case EPI_STORE:
-      hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM, EPI_STORE>), grid, dim3(NT), 0, st, g); break;
-    case EPI_GELU:
-      hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM, EPI_GELU>), grid, dim3(NT), 0, st, g); break;
-    case EPI_MUL:
-      hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM, EPI_MUL>), grid, dim3(NT), 0, st, g); break;
-    case EPI_RESID:
-      hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM, EPI_RESID>), grid, dim3(NT), 0, st, g); break;
-    case EPI_PARTIAL:
-      hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM, EPI_PARTIAL>), grid, dim3(NT), 0, st, g); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t gemm_bf16(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, bool out_f32,
@@ -1241,25 +1091,6 @@ hipError_t gemm_bf16(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi ep
   if (tile == 1) return dispatch_layout<256, 256>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
   if (tile == 2) return dispatch_layout<256, 128>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
   return dispatch_layout<128, 128>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
-}
-
-hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, int batch,
-                    hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  if (a_kmajor && b_kmajor) return dispatch_f32<true, true>(g, epi, batch, st);
-  if (a_kmajor && !b_kmajor) return dispatch_f32<true, false>(g, epi, batch, st);
-  if (!a_kmajor && !b_kmajor) return dispatch_f32<false, false>(g, epi, batch, st);
-  return dispatch_f32<false, true>(g, epi, batch, st);
-}
-
-hipError_t splitk_reduce(const float* part, int splits, int M, int N, float* out,
-                         hipStream_t st) {
-  int64_t mn = (int64_t)M * N;
-  if (mn == 0) return hipSuccess;
-  if (mn % 4 != 0 || splits < 1) return hipErrorInvalidValue;
-  int blocks = (int)((mn / 4 + 255) / 256);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, st, part, splits, mn, out);
-  return hipGetLastError();
 }
 
 namespace {

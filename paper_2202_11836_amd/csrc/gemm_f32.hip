@@ -1,0 +1,581 @@
+// Dense contractions of fp32 stages on v_mfma_f32_32x32x2_f32 (fp32 operands,
+// fp32 fused multiply-adds), with the epilogues of gemm.hip.
+//
+// What bounds it: the fp32 matrix rate (64 FLOP per cycle and SIMD, 157
+// TFLOP/s), so a wavefront's MFMAs take 64 cycles each and everything else
+// fits underneath if the loads are requested early enough.  k-tiles go from
+// HBM straight into a ring of LDS slots with direct-to-LDS buffer loads, up
+// to NS - 1 of them in flight, one barrier per k-tile; each wavefront owns
+// one 32 x 32 output block.  Two work-group shapes:
+//   64 x 64, 2 x 2 wavefronts, k-tiles of 32, four slots (64 KB, two
+//     work-groups per CU, so a second wavefront per SIMD covers waits);
+//   32 x 32, four wavefronts splitting every k-tile of 64 by k (their sums
+//     are added in wavefront order at the end), eight slots: for outputs with
+//     few 64 x 64 tiles, where the chain of MFMAs of one wavefront and the
+//     memory latency are the time.
+// Measured against the vector-ALU kernel this replaced (64 x 64 tiles, 4 x 4
+// outputs per thread, one global load -> LDS -> barrier per 16 k): a BERT-base
+// layer at 16 x 128 tokens, forward and backward, 3689 -> 1090 us, its FFN1
+// (2048 x 3072 x 768) 236 -> 105 us (92 TFLOP/s), its weight gradients 102
+// TFLOP/s; two layers of width 128 at 64 tokens 1086 -> 186 us.  Largest
+// relative error against 64 bits 1.2e-6 -> 7e-7 and 3.2e-7 -> 2.3e-7.
+#include <algorithm>
+
+#include "kernels.h"
+
+namespace {
+
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+// Largest number of 64 x 64 tiles for which 32 x 32 work-groups are used:
+// below one tile per CU the chip is part idle and a tile's latency is the
+// kernel's time.
+constexpr int64_t SMALL_TILES = 256;
+
+template <bool SMALL>
+struct Cfg {
+  static constexpr int R = SMALL ? 32 : 64;     // tile rows and columns
+  static constexpr int KG = SMALL ? 4 : 1;      // wavefront groups along k
+  static constexpr int BK = SMALL ? 64 : 32;    // k-tile depth
+  static constexpr int OP = R * BK * 4;         // bytes of one operand's k-tile
+  static constexpr int STAGE = 2 * OP;          // 16 KB
+};
+
+// Buffer resource from base on; lanes that must read 0 use offset OOB.
+constexpr int OOB = 0x7fffff00;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const float* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, OOB, 0x00020000);
+}
+
+// 16 or 4 bytes per lane to LDS (lane l's at dst + l * 16 or 4).
+template <bool VEC>
+__device__ __forceinline__ void load_lds(__amdgpu_buffer_rsrc_t rs, char* dst, int off) {
+  if constexpr (VEC)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, off, 0, 0, 0);
+  else
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 4, off, 0, 0, 0);
+}
+
+// "lgkmcnt = 0 and at most N vector memory operations outstanding" (gfx9
+// s_waitcnt encoding).
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N <= 63, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | 0x70 | (((N >> 4) & 3) << 14));
+}
+// Wait until at most `after` (0 .. MAX) of the latest k-tiles' loads, PER
+// each, are outstanding: loads complete in order.
+template <int PER, int MAX>
+__device__ __forceinline__ void wait_after(int after) {
+  if constexpr (MAX == 0) {
+    wait_vm<0>();
+  } else {
+    if (after >= MAX) wait_vm<PER * MAX>();
+    else wait_after<PER, MAX - 1>(after);
+  }
+}
+
+// Direct-to-LDS loads of one operand's k-tile (rows or columns 0 .. R - 1 of
+// `nr`, k values k0 .. k0 + BK - 1 below kend; everything outside reads 0:
+// the lane's offset is moved past the resource).  Each load has a resource of
+// its own, from its first element on, so that the 32-bit offsets span a few
+// rows only.  LDS layouts:
+//   k-major: BK / 32 sub-tiles [R][32], rows of 128 bytes with 16-byte chunk
+//     c at c ^ ((row >> 1) & 7), so that the 16 rows of a fragment read fall
+//     on distinct banks;
+//   m/n-major: [BK][R], as in memory.
+// VEC: 16 bytes per lane (operand 16-byte aligned, its contiguous extent a
+// multiple of 4); else 4 bytes per lane.
+template <int R, int BK, bool KMAJ, bool VEC>
+__device__ __forceinline__ void dma_op(const float* base, int64_t ld, int nr, int k0, int kend,
+                                       char* dst, int wave, int lane) {
+  constexpr int BYTES = VEC ? 16 : 4, PERI = 64 * BYTES;
+  constexpr int NI = R * BK * 4 / PERI / 4;  // instructions per wavefront
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int q = wave * NI + i;
+    const int e0 = q * (PERI / 4);  // the instruction's first element
+    const int el = lane * (BYTES / 4);
+    if constexpr (KMAJ) {
+      const int sub = e0 / (R * 32), row0 = (e0 % (R * 32)) / 32;  // whole rows of 32
+      const int dr = el >> 5, row = row0 + dr;
+      const int k = k0 + 32 * sub + 4 * (((el & 31) >> 2) ^ ((row >> 1) & 7)) + (el & 3);
+      const __amdgpu_buffer_rsrc_t rs = rsrc_of(base + (int64_t)row0 * ld);
+      const int vo = (row < nr && k < kend) ? (dr * (int)ld + k) * 4 : OOB;
+      load_lds<VEC>(rs, dst + q * PERI, vo);
+    } else {
+      const int kr0 = e0 / R, c0 = e0 % R;  // c0 != 0: a part of one k-row
+      const int dk = (c0 + el) / R, col = (c0 + el) % R;
+      const int k = k0 + kr0 + dk;
+      const __amdgpu_buffer_rsrc_t rs = rsrc_of(base + (int64_t)(k0 + kr0) * ld);
+      const int vo = (col < nr && k < kend) ? (dk * (int)ld + col) * 4 : OOB;
+      load_lds<VEC>(rs, dst + q * PERI, vo);
+    }
+  }
+}
+
+// Four consecutive k's of the lane's row (k-major) or column: k = 8 g + 4 hf
+// + j of the k range starting at kk (a multiple of 8) of the tile.  Both
+// operands use this k order, so MFMA step j multiplies k = 8 g + j (lanes
+// 0-31) and 8 g + 4 + j (lanes 32-63).
+// (LDS addresses are plain integers: read through the shared array's pointer,
+// the compiler made every k-tile's first read wait for all loads in flight.)
+typedef const __attribute__((address_space(3))) float lds_cfloat_t;
+typedef const __attribute__((address_space(3))) f32x4_t lds_cf32x4_t;
+template <int R, bool KMAJ>
+__device__ __forceinline__ f32x4_t frag4(uint32_t tile, int r, int kk, int hf) {
+  if constexpr (KMAJ) {
+    const int c = ((kk & 31) >> 2) + hf;
+    return *(lds_cf32x4_t*)(uintptr_t)(tile + (kk >> 5) * (R * 128) + r * 128 +
+                                       16 * (c ^ ((r >> 1) & 7)));
+  } else {
+    lds_cfloat_t* p = (lds_cfloat_t*)(uintptr_t)(tile + ((kk + 4 * hf) * R + r) * 4);
+    return f32x4_t{p[0], p[R], p[2 * R], p[3 * R]};
+  }
+}
+
+// Work-group barrier that leaves direct-to-LDS loads in flight (a plain
+// __syncthreads() waits for all of them); the caller has waited for those
+// that matter and for its own LDS operations.
+__device__ __forceinline__ void ring_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// N output elements of column n, rows m(0) .. m(N - 1) (v: the accumulators):
+// every operand is loaded before the first store (loads and stores share one
+// counter, so a load behind a store waits for it).  Returns their sum as
+// stored.
+template <int EPI, int N, typename F>
+__device__ __forceinline__ float epilogue(const GemmArgs& g, int64_t offC, int zs, F row, int n,
+                                          const float* v) {
+  if (n >= g.N) return 0.0f;
+  float x[N];
+  float bias = 0.0f;
+  if (EPI == EPI_GELU || (EPI == EPI_STORE && g.bias)) bias = g.bias[n];
+  if (EPI == EPI_MUL || EPI == EPI_RESID) {
+    const float* aux = (const float*)g.aux + offC + n;
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = row(i) < g.M ? aux[(int64_t)row(i) * g.ldaux] : 0.0f;
+  }
+  float* C = (float*)g.C + (EPI == EPI_PARTIAL ? (int64_t)zs * g.M * g.ldc : offC) + n;
+  float sum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (row(i) >= g.M) continue;
+    const int64_t at = (int64_t)row(i) * g.ldc;
+    float o = v[i];
+    if (EPI == EPI_STORE) o = o * g.alpha + bias;
+    if (EPI == EPI_MUL) o *= x[i];
+    if (EPI == EPI_RESID) o += x[i];
+    if (EPI == EPI_GELU) {
+      const float u = o + bias;
+      o = gelu_f(u);
+      ((float*)g.C2 + offC + n)[at] = gelu_grad_f(u);
+    }
+    C[at] = o;
+    sum += o;
+  }
+  return sum;
+}
+
+// One output tile (tm, tn) of batch entry zb over split zs of K.
+template <bool SMALL, int NS, bool AK, bool BKM, bool VEC, int EPI>
+__device__ __forceinline__ void tile_f32(const GemmArgs& g, int tm, int tn, int zb, int zs, char* smem) {
+  using C = Cfg<SMALL>;
+  constexpr int R = C::R, BK = C::BK, KG = C::KG;
+  constexpr int PER = C::STAGE / (VEC ? 1024 : 256) / 4;  // loads per k-tile and wavefront
+  static_assert(PER * (NS - 2) <= 63, "vmcnt range");
+  const int lane = threadIdx.x & 63, hf = lane >> 5, rr = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = tm * R, n0 = tn * R;
+  const int kbeg = zs * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+  const int64_t za = zb / g.zdiv, zr = zb % g.zdiv;
+  const int nt = (kend - kbeg + BK - 1) / BK;
+  const float* A = (const float*)g.A + za * g.sA1 + zr * g.sA2 + (AK ? (int64_t)kbeg : kbeg * g.lda);
+  const float* B = (const float*)g.B + za * g.sB1 + zr * g.sB2 + (BKM ? (int64_t)kbeg : kbeg * g.ldb);
+  if constexpr (AK) A += (int64_t)m0 * g.lda; else A += m0;
+  if constexpr (BKM) B += (int64_t)n0 * g.ldb; else B += n0;
+  const int nk = kend - kbeg, nm = g.M - m0, nn = g.N - n0;
+  auto issue = [&](int t) {
+    char* d = smem + (t % NS) * C::STAGE;
+    dma_op<R, BK, AK, VEC>(A, g.lda, nm, t * BK, nk, d, wave, lane);
+    dma_op<R, BK, BKM, VEC>(B, g.ldb, nn, t * BK, nk, d + C::OP, wave, lane);
+  };
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < nt) issue(t);
+  const int wm = SMALL ? 0 : (wave >> 1) * 32, wn = SMALL ? 0 : (wave & 1) * 32;
+  const int kw = SMALL ? wave * (BK / KG) : 0;  // the wavefront's k's of a k-tile
+  // One accumulator per group of 8 k's in a k-tile, added at the end: a chain
+  // of K / 8 additions per value instead of K / 2 (and, with one wavefront per
+  // SIMD, MFMAs that do not wait for one another).
+  constexpr int NF = BK / KG / 8;
+  f32x16_t accs[NF];
+#pragma unroll
+  for (int s = 0; s < NF; ++s)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accs[s][r] = 0.0f;
+  for (int t = 0; t < nt; ++t) {
+    // k-tile t has landed for everyone, and nobody reads k-tile t - 1 any more.
+    wait_after<PER, NS - 2>(min(nt - 1, t + NS - 2) - t);
+    ring_barrier();
+    if (t + NS - 1 < nt) issue(t + NS - 1);
+    const uint32_t At = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem +
+                        (t % NS) * C::STAGE;
+    const uint32_t Bt = At + C::OP;
+    // All of the k-tile's fragments first, so that one wavefront per SIMD
+    // waits for LDS once per k-tile and not once per four MFMAs.
+    f32x4_t a[NF], b[NF];
+#pragma unroll
+    for (int s = 0; s < NF; ++s) {
+      a[s] = frag4<R, AK>(At, wm + rr, kw + 8 * s, hf);
+      b[s] = frag4<R, BKM>(Bt, wn + rr, kw + 8 * s, hf);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int s = 0; s < NF; ++s)
+        accs[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][j], b[s][j], accs[s], 0, 0, 0);
+  }
+  f32x16_t acc = accs[0];
+#pragma unroll
+  for (int s = 1; s < NF; ++s) acc += accs[s];
+  // The four wavefronts' k sums, added in wavefront order; wavefront w then
+  // owns accumulator registers 4 w .. 4 w + 3 (rows 8 w + 4 hf + 0..3).
+  if constexpr (SMALL) {
+    __syncthreads();  // the ring becomes the exchange area: [wave][16][64]
+    float* ex = (float*)smem;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float* p = ex + (4 * wave + j) * 64 + lane;
+      v[j] = ((p[0] + p[1024]) + p[2048]) + p[3072];
+    }
+    const int64_t offC = za * g.sC1 + zr * g.sC2;
+    const int n = n0 + rr, mb = m0 + 8 * wave + 4 * hf;
+    const float cs = epilogue<EPI, 4>(g, offC, zs, [&](int j) { return mb + j; }, n, v);
+    if (g.colpart) {  // column sums of the tile's 32 rows, in a fixed order
+      __syncthreads();
+      ex[(wave * 2 + hf) * 32 + rr] = cs;
+      __syncthreads();
+      if (threadIdx.x < 32 && n < g.N) {
+        float s = ex[rr];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) s += ex[i * 32 + rr];
+        g.colpart[(zb / g.zdiv) * g.cp_batch + (int64_t)tm * g.cp_ld + (zb % g.zdiv) * g.sC2 + n] = s;
+      }
+    }
+  } else {
+    const int64_t offC = za * g.sC1 + zr * g.sC2;
+    const int n = n0 + wn + rr, mb = m0 + wm + 4 * hf;
+    float v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = acc[r];
+    float cs = epilogue<EPI, 16>(
+        g, offC, zs, [&](int r) { return mb + 8 * (r >> 2) + (r & 3); }, n, v);
+    if (g.colpart) {  // column sums per 32-row block: both lane halves' rows
+      cs += __shfl_xor(cs, 32, 64);
+      const int blk = (m0 + wm) / 32;
+      if (hf == 0 && n < g.N && m0 + wm < g.M)
+        g.colpart[(zb / g.zdiv) * g.cp_batch + (int64_t)blk * g.cp_ld + (zb % g.zdiv) * g.sC2 + n] = cs;
+    }
+  }
+}
+
+template <bool SMALL, bool VEC>
+struct Ring {
+  // 4-byte loads: four slots keep the outstanding count within vmcnt's range
+  static constexpr int NS = SMALL && VEC ? 8 : 4;
+  static constexpr int LDS = NS * Cfg<SMALL>::STAGE;
+};
+
+// Consecutive work-groups go round robin over the 8 XCDs: each XCD takes a
+// contiguous range of tiles, walked in groups of 8 tile-rows that share B.
+__device__ __forceinline__ void tile_of(int bid, int nbm, int nbn, int& tm, int& tn) {
+  const int total = nbm * nbn;
+  if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
+  constexpr int GM = 8;
+  const int group = bid / (GM * nbn), first = group * GM, size = min(nbm - first, GM);
+  const int r = bid - group * GM * nbn;
+  tm = first + r % size;
+  tn = r / size;
+}
+
+template <bool SMALL, bool AK, bool BKM, bool VEC, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
+  using Rg = Ring<SMALL, VEC>;
+  __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
+  constexpr int R = Cfg<SMALL>::R;
+  int tm, tn;
+  tile_of(blockIdx.x, (g.M + R - 1) / R, (g.N + R - 1) / R, tm, tn);
+  tile_f32<SMALL, Rg::NS, AK, BKM, VEC, EPI>(g, tm, tn, blockIdx.z / g.ksplit, blockIdx.z % g.ksplit,
+                                             smem);
+}
+
+// The three contractions of the attention backward in one launch (grid y):
+// p[0] dV = P^T dC, p[1] dQ = dS K, p[2] dK = dS^T Q, per (batch, head).
+struct Attn3 {
+  GemmArgs p[3];
+};
+template <bool SMALL, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_attn_bwd_kernel(Attn3 a) {
+  using Rg = Ring<SMALL, VEC>;
+  __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
+  constexpr int R = Cfg<SMALL>::R;
+  const int nbn = (a.p[0].N + R - 1) / R;
+  const int tm = blockIdx.x / nbn, tn = blockIdx.x % nbn;
+  if (blockIdx.y == 1)
+    tile_f32<SMALL, Rg::NS, true, false, VEC, EPI_STORE>(a.p[1], tm, tn, blockIdx.z, 0, smem);
+  else if (blockIdx.y == 0)
+    tile_f32<SMALL, Rg::NS, false, false, VEC, EPI_STORE>(a.p[0], tm, tn, blockIdx.z, 0, smem);
+  else
+    tile_f32<SMALL, Rg::NS, false, false, VEC, EPI_STORE>(a.p[2], tm, tn, blockIdx.z, 0, smem);
+}
+
+// A layer's weight gradients in one launch: work-group b serves problem q
+// with blk0[q] <= b < blk0[q + 1]; a problem's work-groups are its tiles times
+// its splits.
+struct WgradGroup {
+  GemmArgs p[GEMM_GROUP_MAX];
+  int blk0[GEMM_GROUP_MAX + 1];
+  int n;
+};
+template <bool SMALL>
+__global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
+  using Rg = Ring<SMALL, true>;
+  __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
+  constexpr int R = Cfg<SMALL>::R;
+  const int b = blockIdx.x;
+  int q = 0;
+#pragma unroll
+  for (int k = 1; k < GEMM_GROUP_MAX; ++k)
+    if (k < w.n && b >= w.blk0[k]) q = k;
+  // (a copy per problem: a run-time index into the argument would put it in
+  // scratch memory)
+  GemmArgs g;
+  switch (q) {
+    case 0: g = w.p[0]; break;
+    case 1: g = w.p[1]; break;
+    case 2: g = w.p[2]; break;
+    default: g = w.p[3]; break;
+  }
+  const int nbm = (g.M + R - 1) / R, nbn = (g.N + R - 1) / R;
+  const int lb = b - w.blk0[q], zs = lb / (nbm * nbn);
+  int tm, tn;
+  tile_of(lb - zs * nbm * nbn, nbm, nbn, tm, tn);
+  tile_f32<SMALL, Rg::NS, false, false, true, EPI_PARTIAL>(g, tm, tn, 0, zs, smem);
+}
+
+// out[q] = the fixed-order sum of problem q's splits; then the column
+// reductions, ceil(n / 16) work-groups per output vector.
+struct F32Reduce {
+  const float* part[GEMM_GROUP_MAX];
+  float* out[GEMM_GROUP_MAX];
+  int64_t mn[GEMM_GROUP_MAX];
+  int ks[GEMM_GROUP_MAX];
+  int blk0[GEMM_GROUP_MAX + 1];
+  int n;
+  ColJob col[COLJOB_MAX];
+  int cblk0[COLJOB_MAX + 1];
+  int ncol;
+};
+__global__ __launch_bounds__(256) void gemm_f32_group_reduce_kernel(F32Reduce rd) {
+  __shared__ f32x4_t sm[64][4];
+  const int b = blockIdx.x;
+  if (b >= rd.blk0[GEMM_GROUP_MAX]) {
+    int j = 0;
+#pragma unroll
+    for (int k = 1; k < COLJOB_MAX; ++k)
+      if (k < rd.ncol && b >= rd.cblk0[k]) j = k;
+    ColJob cj;
+    switch (j) {
+      case 0: cj = rd.col[0]; break;
+      case 1: cj = rd.col[1]; break;
+      case 2: cj = rd.col[2]; break;
+      default: cj = rd.col[3]; break;
+    }
+    const int nx = (cj.n + 15) / 16, lb = b - rd.cblk0[j], v = lb / nx;
+    float* o;
+    switch (v) {
+      case 0: o = cj.out[0]; break;
+      case 1: o = cj.out[1]; break;
+      case 2: o = cj.out[2]; break;
+      default: o = cj.out[3]; break;
+    }
+    colred_block(cj.part, cj.nblk, cj.nvec, cj.n, v, lb - v * nx, o, sm);
+    return;
+  }
+  int q = 0;
+#pragma unroll
+  for (int k = 1; k < GEMM_GROUP_MAX; ++k)
+    if (k < rd.n && b >= rd.blk0[k]) q = k;
+  const float* part;
+  float* out;
+  int64_t mn;
+  int ks, b0;
+  switch (q) {
+    case 0: part = rd.part[0]; out = rd.out[0]; mn = rd.mn[0]; ks = rd.ks[0]; b0 = rd.blk0[0]; break;
+    case 1: part = rd.part[1]; out = rd.out[1]; mn = rd.mn[1]; ks = rd.ks[1]; b0 = rd.blk0[1]; break;
+    case 2: part = rd.part[2]; out = rd.out[2]; mn = rd.mn[2]; ks = rd.ks[2]; b0 = rd.blk0[2]; break;
+    default: part = rd.part[3]; out = rd.out[3]; mn = rd.mn[3]; ks = rd.ks[3]; b0 = rd.blk0[3]; break;
+  }
+  const int64_t i = ((int64_t)(b - b0) * 256 + threadIdx.x) * 4;
+  if (i >= mn) return;
+  f32x4_t s = *(const f32x4_t*)(part + i);
+  for (int z = 1; z < ks; ++z) s += *(const f32x4_t*)(part + (int64_t)z * mn + i);
+  *(f32x4_t*)(out + i) = s;
+}
+
+// 16-byte loads: the operand's contiguous extent, row stride and every batch
+// offset are multiples of 4 (all allocations are 256-byte aligned).
+bool vec_ok(const GemmArgs& g, bool ak, bool bk) {
+  const int64_t any = g.lda | g.ldb | g.sA1 | g.sA2 | g.sB1 | g.sB2 | (ak ? g.K : g.M) |
+                      (bk ? g.K : g.N);
+  return (any & 3) == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
+}
+// A load's offsets span at most 8 rows and one k extent (32-bit bytes).
+bool fits(const GemmArgs& g) {
+  const int64_t k = g.K;
+  return std::max(g.lda, g.ldb) < ((int64_t)1 << 25) && k * 4 < ((int64_t)1 << 30);
+}
+int64_t tiles_of(const GemmArgs& g, int r) {
+  return (int64_t)((g.M + r - 1) / r) * ((g.N + r - 1) / r);
+}
+
+template <bool AK, bool BKM, int EPI>
+hipError_t launch(const GemmArgs& g, int batch, hipStream_t st) {
+  const bool vec = vec_ok(g, AK, BKM);
+  const bool small = tiles_of(g, 64) * batch * g.ksplit < SMALL_TILES;
+  const dim3 grid((unsigned)tiles_of(g, small ? 32 : 64), 1, (unsigned)(batch * g.ksplit));
+  if (vec) {
+    if (small)
+      hipLaunchKernelGGL((gemm_f32_kernel<true, AK, BKM, true, EPI>), grid, dim3(256), 0, st, g);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<false, AK, BKM, true, EPI>), grid, dim3(256), 0, st, g);
+    return hipGetLastError();
+  }
+  // Operands with rows that are not 16-byte aligned: the score matrix of a
+  // sequence length that is not a multiple of 4 (EPI_STORE, P V).
+  if constexpr (EPI == EPI_STORE && AK && !BKM) {
+    if (small)
+      hipLaunchKernelGGL((gemm_f32_kernel<true, AK, BKM, false, EPI>), grid, dim3(256), 0, st, g);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<false, AK, BKM, false, EPI>), grid, dim3(256), 0, st, g);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, int batch,
+                    hipStream_t st) {
+  if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
+  if (!a_kmajor || g.ksplit != 1 || !fits(g)) return hipErrorInvalidValue;
+  if (b_kmajor) {
+    if (epi == EPI_STORE) return launch<true, true, EPI_STORE>(g, batch, st);
+    if (epi == EPI_GELU) return launch<true, true, EPI_GELU>(g, batch, st);
+  } else {
+    if (epi == EPI_STORE) return launch<true, false, EPI_STORE>(g, batch, st);
+    if (epi == EPI_MUL) return launch<true, false, EPI_MUL>(g, batch, st);
+    if (epi == EPI_RESID) return launch<true, false, EPI_RESID>(g, batch, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmArgs& dk, int batch,
+                             hipStream_t st) {
+  if (dv.M <= 0 || batch <= 0) return hipSuccess;
+  Attn3 a = {{dv, dq, dk}};
+  for (const GemmArgs& g : a.p)
+    if (g.M != dv.M || g.N != dv.N || g.ksplit != 1) return hipErrorInvalidValue;
+  if (!fits(dv) || !fits(dq) || !fits(dk))
+    return hipErrorInvalidValue;
+  const bool vec = vec_ok(dv, false, false) && vec_ok(dq, true, false) && vec_ok(dk, false, false);
+  const bool small = tiles_of(dv, 64) * batch * 3 < SMALL_TILES;
+  const dim3 grid((unsigned)tiles_of(dv, small ? 32 : 64), 3, (unsigned)batch);
+  if (small && vec)
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<true, true>), grid, dim3(256), 0, st, a);
+  else if (small)
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<true, false>), grid, dim3(256), 0, st, a);
+  else if (vec)
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<false, true>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<false, false>), grid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+int gemm_f32_wgrad_splits(int M, int N, int K) {
+  // Two work-groups of 64 x 64 per CU; k ranges of at least 256.
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+  const int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / std::max<int64_t>(tiles, 1), K / 256));
+  const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
+  return (K + chunk - 1) / chunk;
+}
+
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
+                                int ncols, hipStream_t st) {
+  if (n < 0 || n > GEMM_GROUP_MAX || ncols < 0 || ncols > COLJOB_MAX) return hipErrorInvalidValue;
+  WgradGroup w{};
+  F32Reduce rd{};
+  int64_t t64 = 0;
+  for (int q = 0; q < n; ++q) {
+    GemmArgs g = p[q];
+    if (g.M < 1 || g.N < 1 || g.K < 1 || g.ldc != g.N || !vec_ok(g, false, false))
+      return hipErrorInvalidValue;
+    g.ksplit = gemm_f32_wgrad_splits(g.M, g.N, g.K);
+    g.kchunk = ((g.K + g.ksplit - 1) / g.ksplit + 63) / 64 * 64;
+    if (!fits(g)) return hipErrorInvalidValue;
+    // one split writes the gradient itself
+    if (g.ksplit == 1) g.C = out[q];
+    w.p[q] = g;
+    t64 += tiles_of(g, 64) * g.ksplit;
+  }
+  const bool small = t64 < SMALL_TILES;
+  int64_t blocks = 0, rblocks = 0;
+  for (int q = 0; q < n; ++q) {
+    const GemmArgs& g = w.p[q];
+    w.blk0[q] = (int)blocks;
+    blocks += tiles_of(g, small ? 32 : 64) * g.ksplit;
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    if (g.ksplit > 1) {
+      const int j = rd.n++;
+      rd.part[j] = (const float*)g.C;
+      rd.out[j] = out[q];
+      rd.mn[j] = (int64_t)g.M * g.N;
+      rd.ks[j] = g.ksplit;
+      rd.blk0[j] = (int)rblocks;
+      rblocks += (rd.mn[j] / 4 + 255) / 256;
+    }
+  }
+  for (int q = n; q <= GEMM_GROUP_MAX; ++q) w.blk0[q] = (int)blocks;
+  w.n = n;
+  for (int j = rd.n; j <= GEMM_GROUP_MAX; ++j) rd.blk0[j] = (int)rblocks;
+  if (n > 0) {
+    if (small)
+      hipLaunchKernelGGL((gemm_f32_wgrad_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+    else
+      hipLaunchKernelGGL((gemm_f32_wgrad_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  rd.ncol = ncols;
+  for (int j = 0; j < ncols; ++j) {
+    const ColJob& c = cols[j];
+    if (c.nvec < 1 || c.nvec > 4 || c.n < 0 || c.n % 4 != 0 || c.nblk < 0 || !c.part)
+      return hipErrorInvalidValue;
+    rd.col[j] = c;
+    rd.cblk0[j] = (int)rblocks;
+    rblocks += (int64_t)((c.n + 15) / 16) * c.nvec;
+  }
+  for (int j = ncols; j <= COLJOB_MAX; ++j) rd.cblk0[j] = (int)rblocks;
+  if (rblocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(gemm_f32_group_reduce_kernel, dim3((unsigned)rblocks), dim3(256), 0, st, rd);
+  return hipGetLastError();
+}

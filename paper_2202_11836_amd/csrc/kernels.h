@@ -41,7 +41,11 @@ struct GemmArgs {
   int tile;  // bf16 tile shape: 0 = automatic, 1 = 256x256, 2 = 256x128, 3 = 128x128
   // EPI_MUL on bf16, optional: column sums of the stored output per block
   // of 128 rows, colpart[m / 128][n] (needs tile 1).
+  // fp32: column sums of the stored output per block of 32 rows of each batch
+  // entry, colpart[(zb / zdiv) * cp_batch + (m / 32) * cp_ld + (zb % zdiv) *
+  // sC2 + n].
   float* colpart;
+  int64_t cp_batch, cp_ld;
   int zdiv_total;  // internal: batch * ksplit
 };
 
@@ -57,11 +61,15 @@ inline GemmArgs gemm_args(const void* A, int64_t lda, const void* B, int64_t ldb
 // for EPI_STORE; all other epilogues write bf16 (EPI_PARTIAL writes fp32).
 hipError_t gemm_bf16(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi,
                      bool out_f32, int batch, hipStream_t st);
-// fp32 operands on the vector ALU (fp32 accumulation), same conventions.
-hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi,
-                    int batch, hipStream_t st);
-// out[m][n] = sum_s part[s][m][n] (fixed order), fp32.
-hipError_t splitk_reduce(const float* part, int splits, int M, int N, float* out, hipStream_t st);
+// fp32 operands on fp32 MFMA, same conventions: A k-major, ksplit 1; B
+// k-major with EPI_STORE or EPI_GELU, n-major with EPI_STORE, EPI_MUL or
+// EPI_RESID.
+hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, int batch,
+                    hipStream_t st);
+// The attention backward's dV = P^T dC, dQ = dS K and dK = dS^T Q of every
+// (batch, head) in one launch (equal M and N, EPI_STORE).
+hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmArgs& dk, int batch,
+                             hipStream_t st);
 
 // Up to GEMM_GROUP_MAX weight-gradient GEMMs in one launch, stream-K: each
 // problem p[q] is a GEMM with both operands m/n-major (A(m, k) = A[k * lda +
@@ -91,8 +99,8 @@ struct GemmGroup {
 int wgrad_group_slots(const int* M, const int* N, int n, int K);
 hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st);
 // A column reduction run with a group's reduction: out[v][c] = the sum over
-// the nblk partial rows b of part[(b * nvec + v) * n + c], v < nvec <= 4, in
-// col_reduce's order (null outputs are skipped).
+// the nblk partial rows b of part[(b * nvec + v) * n + c], v < nvec <= 4, in a
+// fixed order (null outputs are skipped).
 struct ColJob {
   const float* part;
   int nblk, nvec, n;
@@ -104,6 +112,14 @@ constexpr int COLJOB_MAX = 4;
 // COLJOB_MAX column reductions cols, in one launch.
 hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
                               int ncols, hipStream_t st);
+
+// The weight gradients of one fp32 layer (both operands m/n-major) in one
+// launch, and in a second one the fixed-order sums of the problems split over
+// K (p[q].C holds gemm_f32_wgrad_splits slots of M x N partials where that is
+// more than 1) and the column reductions.
+int gemm_f32_wgrad_splits(int M, int N, int K);
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
+                                int ncols, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Row kernels (one wavefront per row), T = float or bf16_t.
@@ -123,15 +139,14 @@ hipError_t add_ln_fwd(const TA* a, const float* bias, const T* resid, const T* r
 // part[blk][2][:] = sum dz.
 constexpr int LN_BWD_RPB = 32;
 int ln_bwd_blocks(int rows);
-template <typename T>
-hipError_t ln_bwd(const T* dy, const T* xhat, const float* rstd, const float* gamma, T* dz,
-                  float* part, int rows, int h, hipStream_t st);
+hipError_t ln_bwd_f32(const float* dy, const float* xhat, const float* rstd, const float* gamma,
+                      float* dz, float* part, int rows, int h, hipStream_t st);
 
 // bf16 stages: the same with dy either one bf16 tensor (ahi = alo = b =
 // null) or the fp32 sum (ahi + alo) + b of three bf16 tensors (dy = null):
 // a residual branch carried as its bf16 rounding and rounding residual,
 // plus a bf16 GEMM product.  dz in bf16 and, when dzlo is not null, dz's
-// bf16 rounding residual.  Partials as ln_bwd.
+// bf16 rounding residual.  Partials as ln_bwd_f32.
 hipError_t ln_bwd_bf16(const bf16_t* dy, const bf16_t* ahi, const bf16_t* alo, const bf16_t* b,
                        const bf16_t* xhat, const float* rstd, const float* gamma, bf16_t* dz,
                        bf16_t* dzlo, float* part, int rows, int h, hipStream_t st);
@@ -142,10 +157,6 @@ hipError_t add3_bf16(const bf16_t* ahi, const bf16_t* alo, const bf16_t* b, bf16
 // part[blk][n] = sum over the block's rows of x[row][n].
 template <typename T>
 hipError_t col_partial(const T* x, int rows, int n, float* part, int nblk, hipStream_t st);
-
-// out[c][n] = sum_blk part[blk][c][n] for c < nvec (fixed order).
-hipError_t col_reduce(const float* part, int nblk, int nvec, int n, float* const* outs,
-                      hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Attention row kernels on a materialised score matrix.

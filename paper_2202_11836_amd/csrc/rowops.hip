@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T* __restrict__ dy,
   for (int i = 0; i < NC; ++i) {
     const int c = lane + 64 * i;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) pg[i][k] = pb[i][k] = pz[i][k] = 0.0f;
+    for (int k = 0; k < 8; ++k) pg[i][k] = pb[i][k] = pz[i][k] = gm[i][k] = 0.0f;
     if (c < nchunk) load8(gamma + 8 * c, gm[i]);
   }
   const int r0 = blockIdx.x * rpb;
@@ -419,17 +419,6 @@ __global__ __launch_bounds__(256) void col_partial_kernel(const T* __restrict__ 
   part[(int64_t)blk * n + c] = s;
 }
 
-struct OutPtrs {
-  float* p[4];
-};
-
-// 16 columns per block (colred_block), grid (ceil(n / 16), nvec).
-__global__ __launch_bounds__(256) void col_reduce_kernel(const float* __restrict__ part, int nblk,
-                                                         int nvec, int n, OutPtrs outs) {
-  __shared__ f32x4_t sm[64][4];
-  colred_block(part, nblk, nvec, n, blockIdx.y, blockIdx.x, outs.p[blockIdx.y], sm);
-}
-
 // P = softmax over keys of scale * scores, masked keys -> 0, empty rows -> 0.
 template <typename T>
 __global__ __launch_bounds__(256) void softmax_fwd_kernel(const float* __restrict__ scores,
@@ -551,25 +540,24 @@ hipError_t add3_bf16(const bf16_t* ahi, const bf16_t* alo, const bf16_t* b, bf16
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t ln_bwd(const T* dy, const T* xhat, const float* rstd, const float* gamma, T* dz,
-                  float* part, int rows, int h, hipStream_t st) {
+hipError_t ln_bwd_f32(const float* dy, const float* xhat, const float* rstd, const float* gamma,
+                      float* dz, float* part, int rows, int h, hipStream_t st) {
   if (h % 64 != 0 || h > 2048) return hipErrorInvalidValue;
   if (rows <= 0) return hipSuccess;
   const int nc = (h / 8 + 63) / 64;
   dim3 grid(ln_bwd_blocks(rows)), blk(256);
   size_t sh = (size_t)4 * 3 * h * sizeof(float);
   const int rpb = LN_BWD_RPB;
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    return ln_bwd_bf16(dy, nullptr, nullptr, nullptr, xhat, rstd, gamma, dz, nullptr, part, rows,
-                       h, st);
-  }
+#define LAUNCH_LNB(NCV)                                                                        \
+  hipLaunchKernelGGL((ln_bwd_kernel<float, NCV>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, \
+                     part, rows, h, rpb)
   switch (nc) {
-    case 1: hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, part, rows, h, rpb); break;
-    case 2: hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, part, rows, h, rpb); break;
-    case 3: hipLaunchKernelGGL((ln_bwd_kernel<T, 3>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, part, rows, h, rpb); break;
-    default: hipLaunchKernelGGL((ln_bwd_kernel<T, 4>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, part, rows, h, rpb); break;
+    case 1: LAUNCH_LNB(1); break;
+    case 2: LAUNCH_LNB(2); break;
+    case 3: LAUNCH_LNB(3); break;
+    default: LAUNCH_LNB(4); break;
   }
+#undef LAUNCH_LNB
   return hipGetLastError();
 }
 
@@ -579,17 +567,6 @@ hipError_t col_partial(const T* x, int rows, int n, float* part, int nblk, hipSt
   if (rpb < 1) rpb = 1;
   hipLaunchKernelGGL(col_partial_kernel<T>, dim3((n + 255) / 256, nblk), dim3(256), 0, st, x, rows,
                      n, rpb, part);
-  return hipGetLastError();
-}
-
-hipError_t col_reduce(const float* part, int nblk, int nvec, int n, float* const* outs,
-                      hipStream_t st) {
-  if (nvec > 4 || n % 4 != 0) return hipErrorInvalidValue;
-  if (n <= 0 || nvec <= 0) return hipSuccess;
-  OutPtrs o{};
-  for (int i = 0; i < nvec; ++i) o.p[i] = outs[i];
-  hipLaunchKernelGGL(col_reduce_kernel, dim3((n + 15) / 16, nvec), dim3(256), 0, st, part, nblk,
-                     nvec, n, o);
   return hipGetLastError();
 }
 
@@ -613,16 +590,14 @@ hipError_t softmax_bwd(const float* dP, const T* P, T* dS, int BH, int S, int ld
   return hipGetLastError();
 }
 
-#define INST(T)                                                                                 \
-  template hipError_t add_ln_fwd<T, float>(const float*, const float*, const T*, const T*,     \
-                                           const float*, const float*, T*, T*, T*, float*,    \
-                                           int, int, hipStream_t);                            \
-  template hipError_t ln_bwd<T>(const T*, const T*, const float*, const float*, T*, float*,    \
-                                int, int, hipStream_t);                                        \
-  template hipError_t col_partial<T>(const T*, int, int, float*, int, hipStream_t);            \
-  template hipError_t softmax_fwd<T>(const float*, const uint8_t*, T*, int, int, int, int,     \
-                                     float, hipStream_t);                                      \
-  template hipError_t softmax_bwd<T>(const float*, const T*, T*, int, int, int, float,         \
-                                     hipStream_t);
-INST(float)
-INST(bf16_t)
+template hipError_t add_ln_fwd<float, float>(const float*, const float*, const float*, const float*,
+                                             const float*, const float*, float*, float*, float*,
+                                             float*, int, int, hipStream_t);
+template hipError_t add_ln_fwd<bf16_t, float>(const float*, const float*, const bf16_t*,
+                                              const bf16_t*, const float*, const float*, bf16_t*,
+                                              bf16_t*, bf16_t*, float*, int, int, hipStream_t);
+template hipError_t col_partial<float>(const float*, int, int, float*, int, hipStream_t);
+template hipError_t softmax_fwd<float>(const float*, const uint8_t*, float*, int, int, int, int,
+                                       float, hipStream_t);
+template hipError_t softmax_bwd<float>(const float*, const float*, float*, int, int, int, float,
+                                       hipStream_t);

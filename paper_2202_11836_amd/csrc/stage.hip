@@ -21,7 +21,7 @@
 namespace {
 
 constexpr int HEAD_DIM = 64;
-constexpr int COL_PARTS = 128; // row blocks of the bias-gradient column sums
+constexpr int COL_PARTS = 128; // row blocks of a column-sum pass (fp32 stages, db_1)
 
 // Kernel launch sites of one layer, for event tracing (stage_trace_site).
 #define STAGE_SITES(X)                                                              \
@@ -175,12 +175,10 @@ struct stage {
   void* dz1lo = nullptr;    // [T, h]
   void* dz2lo = nullptr;    // [T, h]
   void* prod = nullptr;     // [T, h] bf16 data-gradient GEMM product joining them (bf16 stages)
-  float* part = nullptr;    // column-sum partials
-  float* part2 = nullptr;   // second LayerNorm's partials (bf16: reduced at the layer's end)
-  float* colpart_ffn = nullptr;  // [ceil(T/128), f] column sums of dU (bf16 stages)
-  float* colpart_qkv = nullptr;  // [B * ceil(S/32), 3h] column sums of dQKV (bf16 stages)
-  // Transposed weights of the layer being differentiated (bf16 stages), so
-  // that every data-gradient GEMM reads both operands k-contiguously.
+  float* part = nullptr;    // first LayerNorm's column partials
+  float* part2 = nullptr;   // second LayerNorm's
+  float* colpart_ffn = nullptr;  // [colpart_ffn_rows, f] column sums of dU
+  float* colpart_qkv = nullptr;  // [B * ceil(S/32), 3h] column sums of dQKV
   float* splitk = nullptr;  // split-K partials of the weight gradients
   size_t splitk_elems = 0;  // elements it holds
   size_t splitk_bytes = 0;  // bytes counted for it in bytes_act
@@ -336,31 +334,12 @@ stage_status dev_alloc(stage_t* s, std::vector<void*>& list, void** p, size_t by
   return STAGE_OK;
 }
 
-// Tiling of a weight-gradient GEMM dW[M, N] = sum over K = T tokens: the
-// output has few tiles, so the token range is split until about one
-// work-group per CU (256) is running.  256x256 tiles when the output has at
-// least 16 of them, else 128x128.  Returns the split count; *tile receives
-// the GemmArgs tile code.
-int wgrad_split(int64_t M, int64_t N, int K, int* tile) {
-  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  int64_t tiles;
-  if (t256 >= 16) {
-    *tile = 1;
-    tiles = t256;
-  } else {
-    *tile = 3;
-    tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  }
-  int ks = (int)std::max<int64_t>(1, 256 / tiles);
-  ks = std::min(ks, std::max(1, K / 512));  // chunks of at least 512 tokens
-  return ks;
-}
-
 // Elements of split-K partials the weight gradients of a backward over T
 // tokens need.  bf16 stages compute a layer's weight gradients in one group
 // launch (stream-K over all their tiles): room for all four gradients'
 // partials, or for the feed-forward or attention half of a partial layer.
-// fp32 stages compute them one at a time: the largest one's.  The figure is
+// fp32 stages: the partials of those of a layer's gradients that are split.
+// The figure is
 // not monotone in T (the stream-K piece count per tile depends on how the
 // k-tiles of all tiles divide among the work-groups), so it is evaluated for
 // every token count a forward prepares.
@@ -377,9 +356,8 @@ size_t splitk_need(const stage_t* s, int64_t T) {
   } else {
     const int64_t shapes[4][2] = {{3 * h, h}, {h, h}, {f, h}, {h, f}};
     for (auto& mn : shapes) {
-      int tile;
-      int ks = wgrad_split(mn[0], mn[1], (int)T, &tile);
-      if (ks > 1) need = std::max<size_t>(need, (size_t)ks * mn[0] * mn[1]);
+      const int ks = gemm_f32_wgrad_splits((int)mn[0], (int)mn[1], (int)std::max<int64_t>(T, 1));
+      if (ks > 1) need += (size_t)ks * mn[0] * mn[1];
     }
   }
   return need;
@@ -408,6 +386,18 @@ stage_status grow_splitk(stage_t* s, size_t need) {
   s->splitk_elems = need;
   s->splitk_bytes = bytes;
   return STAGE_OK;
+}
+
+// fp32 stages: the db_1 column sums are taken per 32 rows in the FFN2
+// data-gradient epilogue up to this token count (as many partial rows as the
+// separate pass leaves beyond it), which saves a launch and a read of dU where
+// launches are what a layer's time is made of.
+bool f32_fused_b1(int64_t T) { return (T + 31) / 32 <= COL_PARTS; }
+
+// Rows of the db_1 column partial sums for T tokens (bf16: one per 128 rows).
+int64_t colpart_ffn_rows(const stage_t* s, int64_t T) {
+  if (s->dtype == STAGE_BF16) return (T + 127) / 128;
+  return f32_fused_b1(T) ? (T + 31) / 32 : COL_PARTS;
 }
 
 stage_status ensure_activations(stage_t* s, int B, int S) {
@@ -458,15 +448,10 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
                                (st = A(&s->prod, T * h * e))))
     return st;
   const int64_t nqb = ((int64_t)S + 31) / 32;
-  if ((st = A((void**)&s->colpart_ffn, ((T + 127) / 128) * f * 4)) ||
-      (st = A((void**)&s->colpart_qkv, (int64_t)B * nqb * 3 * h * 4)))
-    return st;
-  const int64_t maxw = std::max<int64_t>(3 * h, f);
-  const int64_t part_elems =
-      std::max<int64_t>((int64_t)ln_bwd_blocks((int)T) * 3 * h, (int64_t)COL_PARTS * maxw);
-  if ((st = A((void**)&s->part, part_elems * 4))) return st;
-  if (s->dtype == STAGE_BF16 &&
-      (st = A((void**)&s->part2, (int64_t)ln_bwd_blocks((int)T) * 3 * h * 4)))
+  const int64_t ln_part = (int64_t)ln_bwd_blocks((int)T) * 3 * h;
+  if ((st = A((void**)&s->colpart_ffn, colpart_ffn_rows(s, T) * f * 4)) ||
+      (st = A((void**)&s->colpart_qkv, (int64_t)B * nqb * 3 * h * 4)) ||
+      (st = A((void**)&s->part, ln_part * 4)) || (st = A((void**)&s->part2, ln_part * 4)))
     return st;
   if (s->record_grads) {
     s->rec.assign(s->L, nullptr);
@@ -498,30 +483,8 @@ template <> struct Gemm<float> {
   }
 };
 
-// Weight gradient dW[M, N] = sum_t dY[t, m] * X[t, n] (fp32 out), split over
-// t when the output has few tiles; the split partials are summed in order.
-template <typename T>
-stage_status wgrad(stage_t* s, int site, int site_red, const T* dYm, int64_t ld_dy, const T* Xn,
-                   int64_t ld_x, int M, int N, int Tk, float* out) {
-  GemmArgs g = gemm_args(dYm, ld_dy, Xn, ld_x, out, N, M, N, Tk);
-  int ks = wgrad_split(M, N, Tk, &g.tile);
-  if (ks > 1 && (size_t)ks * M * N <= s->splitk_elems) {
-    int chunk = (Tk + ks - 1) / ks;
-    chunk = (chunk + 63) / 64 * 64;
-    ks = (Tk + chunk - 1) / chunk;
-    g.C = s->splitk;
-    g.ksplit = ks;
-    g.kchunk = chunk;
-    SITE_I(site, Gemm<T>::run(g, false, false, EPI_PARTIAL, true, 1, s->stream));
-    SITE_I(site_red, splitk_reduce(s->splitk, ks, M, N, out, s->stream));
-  } else {
-    SITE_I(site, Gemm<T>::run(g, false, false, EPI_STORE, true, 1, s->stream));
-  }
-  return STAGE_OK;
-}
-
 // A weight gradient dW[M, N] = dY^T X over the stage's tokens whose launch
-// is deferred to the layer's group launch (bf16 stages).
+// is deferred to the layer's group launch.
 struct WgradJob {
   const void* dy;
   int64_t ld_dy;
@@ -558,6 +521,25 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const ColJob* 
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
   SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
   SITE(WGRAD_GROUP_RED, wgrad_group_reduce(gs, outs, n, cols, ncols, s->stream));
+  return STAGE_OK;
+}
+
+// The same on fp32 stages.
+stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const ColJob* cols, int ncols) {
+  if (n == 0 && ncols == 0) return STAGE_OK;
+  const int Tn = s->B * s->S;
+  GemmArgs gs[GEMM_GROUP_MAX];
+  float* outs[GEMM_GROUP_MAX];
+  size_t off = 0;
+  for (int q = 0; q < n; ++q) {
+    const WgradJob& j = jobs[q];
+    gs[q] = gemm_args(j.dy, j.ld_dy, j.x, j.ld_x, s->splitk + off, j.N, j.M, j.N, Tn);
+    outs[q] = j.out;
+    const int ks = gemm_f32_wgrad_splits(j.M, j.N, Tn);
+    if (ks > 1) off += (size_t)ks * j.M * j.N;
+  }
+  if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
+  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, cols, ncols, s->stream));
   return STAGE_OK;
 }
 
@@ -675,33 +657,6 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
   return STAGE_OK;
 }
 
-// LayerNorm backward into partials `part`; their column reduction into
-// dgamma, dbeta, dbias runs here, or is queued in *defer (bf16 stages: run
-// with the layer's weight-gradient reduction).
-template <typename T>
-stage_status ln_backward(stage_t* s, int site, int site_red, const T* dy, const T* xhat, const float* rstd,
-                         const float* gamma, T* dz, float* dgamma, float* dbeta, float* dbias,
-                         float* part, ColJob* defer) {
-  const int Tn = s->B * s->S, h = s->h;
-  SITE_I(site, ln_bwd<T>(dy, xhat, rstd, gamma, dz, part, Tn, h, s->stream));
-  if (defer) {
-    *defer = ColJob{part, ln_bwd_blocks(Tn), 3, h, {dgamma, dbeta, dbias, nullptr}};
-    return STAGE_OK;
-  }
-  float* outs[3] = {dgamma, dbeta, dbias};
-  SITE_I(site_red, col_reduce(part, ln_bwd_blocks(Tn), 3, h, outs, s->stream));
-  return STAGE_OK;
-}
-
-template <typename T>
-stage_status col_sum(stage_t* s, int site, int site_red, const T* x, int n, float* out) {
-  const int Tn = s->B * s->S;
-  SITE_I(site, col_partial<T>(x, Tn, n, s->part, COL_PARTS, s->stream));
-  float* outs[1] = {out};
-  SITE_I(site_red, col_reduce(s->part, COL_PARTS, 1, n, outs, s->stream));
-  return STAGE_OK;
-}
-
 // Records the gradient reaching layer l's output when recording is on.
 stage_status record_grad(stage_t* s, int l, const float* x, const bf16_t* bf, const bf16_t* hi,
                          const bf16_t* lo, const bf16_t* b) {
@@ -713,8 +668,10 @@ stage_status record_grad(stage_t* s, int l, const float* x, const bf16_t* bf, co
   return STAGE_OK;
 }
 
-// Backward of an fp32 stage: every tensor in fp32, the weight gradients one
-// GEMM at a time (split over tokens), the materialised attention path.
+// Backward of an fp32 stage: every tensor in fp32, the materialised attention
+// path; the four weight gradients of a layer run in one launch at its end,
+// and the sums of their splits with the bias / LayerNorm column reductions
+// in a second one.
 stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
   using T = float;
   const int B = s->B, S = s->S, h = s->h, H = s->H, f = s->f;
@@ -735,123 +692,118 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
     T* dC = (T*)s->dC;
     T* dQKV = (T*)s->dQKV;
     const T* QKV = (const T*)v.QKV;
-    const void* Wq = p[STAGE_W_QKV];
-    const void* Wo = p[STAGE_W_O];
-    const void* W1 = p[STAGE_W_1];
-    const void* W2 = p[STAGE_W_2];
     const bool attn = has_attn(s, l), ffn = has_ffn(s, l);
     if ((r = record_grad(s, l, dYcur, nullptr, nullptr, nullptr, nullptr))) return r;
-    auto dW = [&](int site, int site_red, const T* dYm, int64_t ld_dy, const T* Xn,
-                  int64_t ld_x, int M, int N, float* out) -> stage_status {
-      return wgrad<T>(s, site, site_red, dYm, ld_dy, Xn, ld_x, M, N, Tn, out);
-    };
+    WgradJob wjobs[GEMM_GROUP_MAX];
+    int nw = 0;
+    ColJob cjobs[COLJOB_MAX];
+    int nc = 0;
     // Gradient reaching H1: computed by the feed-forward half, or the
     // incoming dy when the stage ends at this layer's attention half.
     const T* dH1in = dYcur;
     if (ffn) {
       // Y = LN(Z2): dZ2, dgamma2, dbeta2, and db_2 = sum_t dZ2
-      if ((r = ln_backward<T>(s, SITE_LN2_BWD, SITE_LN2_RED, dYcur, (const T*)v.xhat2, v.rstd2,
-                              (const float*)p[STAGE_G2], dZ2, gr[STAGE_G2], gr[STAGE_BE2],
-                              gr[STAGE_B_2], s->part, nullptr)))
-        return r;
+      SITE(LN2_BWD, ln_bwd_f32(dYcur, (const T*)v.xhat2, v.rstd2, (const float*)p[STAGE_G2], dZ2,
+                               s->part2, Tn, h, st));
+      cjobs[nc++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
+                           {gr[STAGE_G2], gr[STAGE_BE2], gr[STAGE_B_2], nullptr}};
       // dW_2 = dZ2^T G
-      if ((r = dW(SITE_W2_WGRAD, SITE_W2_RED, dZ2, h, (const T*)v.G, f, h, f, gr[STAGE_W_2]))) return r;
-      // dU = (dZ2 W_2) * GELU'(U)
+      wjobs[nw++] = {dZ2, h, v.G, f, h, f, gr[STAGE_W_2]};
+      // dU = (dZ2 W_2) * GELU'(U); db_1 = column sums of dU, per 32 rows in
+      // the epilogue or, over many rows, in a pass of their own
+      const bool fused = f32_fused_b1(Tn);
       {
-        GemmArgs g = gemm_args(dZ2, h, W2, f, dU, f, Tn, f, h);
+        GemmArgs g = gemm_args(dZ2, h, p[STAGE_W_2], f, dU, f, Tn, f, h);
         g.aux = v.Gd;
         g.ldaux = f;
-        SITE(FFN2_DGRAD, Gemm<T>::run(g, true, false, EPI_MUL, false, 1, st));
+        if (fused) {
+          g.colpart = s->colpart_ffn;
+          g.cp_ld = f;
+        }
+        SITE(FFN2_DGRAD, gemm_f32(g, true, false, EPI_MUL, 1, st));
       }
-      if ((r = col_sum<T>(s, SITE_B1_SUM, SITE_B1_RED, dU, f, gr[STAGE_B_1]))) return r;
+      if (!fused)
+        SITE(B1_SUM, col_partial<T>(dU, Tn, f, s->colpart_ffn, COL_PARTS, st));
+      cjobs[nc++] = ColJob{s->colpart_ffn, fused ? (Tn + 31) / 32 : COL_PARTS, 1, f,
+                           {gr[STAGE_B_1], nullptr, nullptr, nullptr}};
       // dW_1 = dU^T H1
-      if ((r = dW(SITE_W1_WGRAD, SITE_W1_RED, dU, f, (const T*)v.H1, h, f, h, gr[STAGE_W_1]))) return r;
+      wjobs[nw++] = {dU, f, v.H1, h, f, h, gr[STAGE_W_1]};
       // dH1 = dZ2 + dU W_1 (the stage's dx when it starts at this layer's
       // feed-forward half)
       T* dH1out = attn ? dH1 : dx;
       {
-        GemmArgs g = gemm_args(dU, f, W1, h, dH1out, h, Tn, h, f);
+        GemmArgs g = gemm_args(dU, f, p[STAGE_W_1], h, dH1out, h, Tn, h, f);
         g.aux = dZ2;
         g.ldaux = h;
-        SITE(FFN1_DGRAD, Gemm<T>::run(g, true, false, EPI_RESID, false, 1, st));
+        SITE(FFN1_DGRAD, gemm_f32(g, true, false, EPI_RESID, 1, st));
       }
       dH1in = dH1out;
     }  // feed-forward half
-    if (!attn) break;
-    // H1 = LN(Z1): dZ1, dgamma1, dbeta1, db_o
-    if ((r = ln_backward<T>(s, SITE_LN1_BWD, SITE_LN1_RED, dH1in, (const T*)v.xhat1, v.rstd1,
-                            (const float*)p[STAGE_G1], dZ1, gr[STAGE_G1], gr[STAGE_BE1],
-                            gr[STAGE_B_O], s->part, nullptr)))
-      return r;
-    // dW_o = dZ1^T C
-    if ((r = dW(SITE_WO_WGRAD, SITE_WO_RED, dZ1, h, (const T*)v.C, h, h, h, gr[STAGE_W_O]))) return r;
-    // dC = dZ1 W_o
-    {
-      GemmArgs g = gemm_args(dZ1, h, Wo, h, dC, h, Tn, h, h);
-      SITE(OUT_DGRAD, Gemm<T>::run(g, true, false, EPI_STORE, false, 1, st));
+    if (attn) {
+      // H1 = LN(Z1): dZ1, dgamma1, dbeta1, db_o
+      SITE(LN1_BWD, ln_bwd_f32(dH1in, (const T*)v.xhat1, v.rstd1, (const float*)p[STAGE_G1], dZ1,
+                               s->part, Tn, h, st));
+      cjobs[nc++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
+                           {gr[STAGE_G1], gr[STAGE_BE1], gr[STAGE_B_O], nullptr}};
+      // dW_o = dZ1^T C
+      wjobs[nw++] = {dZ1, h, v.C, h, h, h, gr[STAGE_W_O]};
+      // dC = dZ1 W_o
+      {
+        GemmArgs g = gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h);
+        SITE(OUT_DGRAD, gemm_f32(g, true, false, EPI_STORE, 1, st));
+      }
+      // dP[b, j] = dC_bj V_bj^T (fp32, into the score buffer)
+      {
+        GemmArgs g = gemm_args(dC, h, QKV + 2 * h, 3 * h, s->scores, S, S, S, HEAD_DIM);
+        g.zdiv = H;
+        g.sA1 = (int64_t)S * h;
+        g.sA2 = HEAD_DIM;
+        g.sB1 = (int64_t)S * 3 * h;
+        g.sB2 = HEAD_DIM;
+        g.sC1 = (int64_t)H * S * S;
+        g.sC2 = (int64_t)S * S;
+        SITE(DP_BWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
+      }
+      // dS = scale * P * (dP - rowsum(dP * P))
+      SITE(SOFTMAX_BWD, softmax_bwd<T>(s->scores, (const T*)v.P, (T*)s->dS, BH, S, S, scale, st));
+      // dV_bj = P_bj^T dC_bj, dQ_bj = dS_bj K_bj, dK_bj = dS_bj^T Q_bj, and
+      // their column sums per 32 rows of each sequence (db_qkv)
+      const int nqb = (S + 31) / 32;
+      {
+        auto prob = [&](const void* a, const T* b, int64_t ldb, int64_t sb1, int block) {
+          GemmArgs g = gemm_args(a, S, b, ldb, dQKV + (int64_t)block * h, 3 * h, S, HEAD_DIM, S);
+          g.zdiv = H;
+          g.sA1 = (int64_t)H * S * S;
+          g.sA2 = (int64_t)S * S;
+          g.sB1 = sb1;
+          g.sB2 = HEAD_DIM;
+          g.sC1 = (int64_t)S * 3 * h;
+          g.sC2 = HEAD_DIM;
+          g.colpart = s->colpart_qkv + (int64_t)block * h;
+          g.cp_ld = 3 * h;
+          g.cp_batch = (int64_t)nqb * 3 * h;
+          return g;
+        };
+        const int64_t sq = (int64_t)S * 3 * h;
+        SITE(DV_BWD, gemm_f32_attn_bwd(prob(v.P, dC, h, (int64_t)S * h, 2),
+                                       prob(s->dS, QKV + h, 3 * h, sq, 0),
+                                       prob(s->dS, QKV, 3 * h, sq, 1), BH, st));
+      }
+      cjobs[nc++] = ColJob{s->colpart_qkv, B * nqb, 1, 3 * h,
+                           {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
+      // dW_qkv = dQKV^T X
+      wjobs[nw++] = {dQKV, 3 * h, v.X, h, 3 * h, h, gr[STAGE_W_QKV]};
+      // dX = dZ1 + dQKV W_qkv  (the previous layer's dY, or the stage's dx)
+      T* dXout = (l > 0) ? (T*)s->dY : dx;
+      {
+        GemmArgs g = gemm_args(dQKV, 3 * h, p[STAGE_W_QKV], h, dXout, h, Tn, h, 3 * h);
+        g.aux = dZ1;
+        g.ldaux = h;
+        SITE(QKV_DGRAD, gemm_f32(g, true, false, EPI_RESID, 1, st));
+      }
+      dYcur = dXout;
     }
-    // dP[b, j] = dC_bj V_bj^T (fp32, into the score buffer)
-    {
-      GemmArgs g = gemm_args(dC, h, QKV + 2 * h, 3 * h, s->scores, S, S, S, HEAD_DIM);
-      g.zdiv = H;
-      g.sA1 = (int64_t)S * h;
-      g.sA2 = HEAD_DIM;
-      g.sB1 = (int64_t)S * 3 * h;
-      g.sB2 = HEAD_DIM;
-      g.sC1 = (int64_t)H * S * S;
-      g.sC2 = (int64_t)S * S;
-      SITE(DP_BWD, Gemm<T>::run(g, true, true, EPI_STORE, true, BH, st));
-    }
-    // dS = scale * P * (dP - rowsum(dP * P))
-    SITE(SOFTMAX_BWD, softmax_bwd<T>(s->scores, (const T*)v.P, (T*)s->dS, BH, S, S, scale, st));
-    // dV_bj = P_bj^T dC_bj
-    {
-      GemmArgs g = gemm_args(v.P, S, dC, h, dQKV + 2 * h, 3 * h, S, HEAD_DIM, S);
-      g.zdiv = H;
-      g.sA1 = (int64_t)H * S * S;
-      g.sA2 = (int64_t)S * S;
-      g.sB1 = (int64_t)S * h;
-      g.sB2 = HEAD_DIM;
-      g.sC1 = (int64_t)S * 3 * h;
-      g.sC2 = HEAD_DIM;
-      SITE(DV_BWD, Gemm<T>::run(g, false, false, EPI_STORE, false, BH, st));
-    }
-    // dQ_bj = dS_bj K_bj
-    {
-      GemmArgs g = gemm_args(s->dS, S, QKV + h, 3 * h, dQKV, 3 * h, S, HEAD_DIM, S);
-      g.zdiv = H;
-      g.sA1 = (int64_t)H * S * S;
-      g.sA2 = (int64_t)S * S;
-      g.sB1 = (int64_t)S * 3 * h;
-      g.sB2 = HEAD_DIM;
-      g.sC1 = (int64_t)S * 3 * h;
-      g.sC2 = HEAD_DIM;
-      SITE(DQ_BWD, Gemm<T>::run(g, true, false, EPI_STORE, false, BH, st));
-    }
-    // dK_bj = dS_bj^T Q_bj
-    {
-      GemmArgs g = gemm_args(s->dS, S, QKV, 3 * h, dQKV + h, 3 * h, S, HEAD_DIM, S);
-      g.zdiv = H;
-      g.sA1 = (int64_t)H * S * S;
-      g.sA2 = (int64_t)S * S;
-      g.sB1 = (int64_t)S * 3 * h;
-      g.sB2 = HEAD_DIM;
-      g.sC1 = (int64_t)S * 3 * h;
-      g.sC2 = HEAD_DIM;
-      SITE(DK_BWD, Gemm<T>::run(g, false, false, EPI_STORE, false, BH, st));
-    }
-    if ((r = col_sum<T>(s, SITE_BQKV_SUM, SITE_BQKV_RED, dQKV, 3 * h, gr[STAGE_B_QKV]))) return r;
-    // dW_qkv = dQKV^T X
-    if ((r = dW(SITE_WQKV_WGRAD, SITE_WQKV_RED, dQKV, 3 * h, (const T*)v.X, h, 3 * h, h, gr[STAGE_W_QKV]))) return r;
-    // dX = dZ1 + dQKV W_qkv  (the previous layer's dY, or the stage's dx)
-    T* dXout = (l > 0) ? (T*)s->dY : dx;
-    {
-      GemmArgs g = gemm_args(dQKV, 3 * h, Wq, h, dXout, h, Tn, h, 3 * h);
-      g.aux = dZ1;
-      g.ldaux = h;
-      SITE(QKV_DGRAD, Gemm<T>::run(g, true, false, EPI_RESID, false, 1, st));
-    }
-    dYcur = dXout;
+    if ((r = wgrad_group_f32(s, wjobs, nw, cjobs, nc))) return r;
   }
   return STAGE_OK;
 }
@@ -1222,9 +1174,8 @@ stage_status stage_backward_noalloc(stage_t* s, const void* dy, void* dx) {
   const int64_t h = s->h, f = s->f;
   const int64_t nlnb = ln_bwd_blocks((int)T);
   const size_t need_splitk = splitk_need(s, T);
-  const size_t n_part = (size_t)std::max<int64_t>(nlnb * 3 * h, (int64_t)COL_PARTS * std::max<int64_t>(3 * h, f));
-  const size_t n_part2 = (size_t)(nlnb * 3 * h);
-  const size_t n_cffn = (size_t)(((T + 127) / 128) * f);
+  const size_t n_part = (size_t)(nlnb * 3 * h);
+  const size_t n_cffn = (size_t)(colpart_ffn_rows(s, T) * f);
   const size_t n_cqkv = (size_t)((int64_t)s->B * ((s->S + 31) / 32) * 3 * h);
   size_t off = 0;
   auto take = [&](size_t elems) {
@@ -1234,7 +1185,7 @@ stage_status stage_backward_noalloc(stage_t* s, const void* dy, void* dx) {
   };
   float* sk = take(need_splitk);
   float* pt = take(n_part);
-  float* pt2 = take(n_part2);
+  float* pt2 = take(n_part);
   float* cf = take(n_cffn);
   float* cq = take(n_cqkv);
   if (off * sizeof(float) > NOALLOC_SCRATCH_BYTES)
