@@ -220,21 +220,6 @@ __device__ __forceinline__ void store_rows_t(const f32x16_t acc[2], float mul, b
   }
 }
 
-// Key extent per sequence: 1 + the last key position with mask != 0 (0 if
-// none).  Keys at or past it are never attended, so loops stop there.
-__global__ __launch_bounds__(256) void key_extent_kernel(const uint8_t* __restrict__ mask, int S,
-                                                         int* __restrict__ kext) {
-  __shared__ int sm[4];
-  const int b = blockIdx.x;
-  int last = 0;
-  for (int s = threadIdx.x; s < S; s += 256)
-    if (mask[(int64_t)b * S + s]) last = max(last, s + 1);
-  for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = last;
-  __syncthreads();
-  if (threadIdx.x == 0) kext[b] = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
-}
-
 // Work-group -> (row block, batch * head).  The grid is one-dimensional,
 // nq row blocks per (batch, head); consecutive work-groups go round robin
 // over the 8 XCDs, so they are remapped such that each XCD takes a
@@ -730,12 +715,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(AttnArgs a) {
 }
 
 }  // namespace
-
-hipError_t key_extent(const uint8_t* mask, int B, int S, int* kext, hipStream_t st) {
-  if (B == 0 || S == 0) return hipSuccess;
-  hipLaunchKernelGGL(key_extent_kernel, dim3(B), dim3(256), 0, st, mask, S, kext);
-  return hipGetLastError();
-}
 
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
   if (a.B == 0 || a.S == 0) return hipSuccess;

@@ -11,9 +11,10 @@
 // HBM keep that layout in LDS and their MFMA fragments are read with gfx950's
 // transposing LDS read.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
-#include "kernels.h"
+#include "gemm_tile.h"
 
 namespace {
 
@@ -65,7 +66,7 @@ __device__ __forceinline__ int64_t batch_off(int zb, int zdiv, int64_t s1, int64
 template <int BM, int BN>
 struct RingShape {
   static constexpr int BK = 64;
-  static constexpr int NS = (BM == 256 && BN == 256) ? 2 : (BM == 256 ? 3 : 4);
+  static constexpr int NS = BN == 256 ? 2 : 3;
   // Wavefronts per work-group: 2 along m times WAVES / 2 along n.  The
   // 256 x 256 tile runs 8 (two per SIMD, 128 x 64 each): while one
   // wavefront waits on loads, a barrier or its epilogue, the other's MFMAs
@@ -86,10 +87,6 @@ struct TileCfg {
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   // direct-to-LDS load instructions per k-tile per wavefront (1 KB each)
   static constexpr int DMA_PER_TILE = STAGE_BYTES / 1024 / WAVES;
-  // Requests of a k-tile split in time over the work-group (see the main
-  // loop): on for the 2- and 3-slot rings, off for the 4-slot one (128 x 128
-  // tiles), where it measured slower.
-  static constexpr bool STAGGER = NS <= 3;
   // Epilogue staging, beside the ring: 16 rows x WN fp32 per wavefront.
   static constexpr int EPI_BYTES = WAVES * 16 * WN * 4;
   static constexpr int LDS_BYTES = NS * STAGE_BYTES + EPI_BYTES;
@@ -98,232 +95,6 @@ struct TileCfg {
   static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0,
                 "whole 1 KB blocks per wavefront");
 };
-
-// Buffer resource over [base, base + bytes): loads past the end return 0.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
-  const int nrec = (int)(bytes < 0 ? 0 : (bytes > 0x7fffffff ? 0x7fffffff : bytes));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nrec, 0x00020000);
-}
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-// LDS tile layouts (no padding; 16-byte chunks XOR-swizzled so that the
-// fragment reads of each 16-lane group hit distinct banks):
-//   k-major  [R][BK]: row r, logical chunk c (8 k values) at physical chunk
-//            c ^ kswz(r) of the row's 2 BK bytes, kswz(r) = (r >> 1) & 7 for
-//            BK = 64 and (r >> 2) & 3 for BK = 32;
-//   m/n-major [BK][R]: k-row k, logical chunk c (8 rows/columns) at physical
-//            chunk c ^ (4 (k & 3)) of the row's 2R bytes (R >= 128), so the
-//            4 k-rows x 2 chunks of each 16-lane transposing read, and the two
-//            groups of a 32-lane pass, cover 16 distinct chunks.
-//
-// dma_tile issues the direct-to-LDS loads (buffer_load ... lds, 16 bytes per
-// lane; lane l of a load lands at LDS base + 16 l) that fill one operand tile
-// of k-tile k0 (k relative to the resource, see the kernel), so the tile
-// never passes through VGPRs.  Each 1 KB block is one instruction; the 4
-// wavefronts split the blocks.
-template <int BK>
-__device__ __forceinline__ int kswz(int r) {
-  return BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3);
-}
-
-template <int R, bool KMAJ, int BK, int W>
-__device__ __forceinline__ void dma_tile(__amdgpu_buffer_rsrc_t rs, int64_t ld, int k0, char* dst,
-                                         int wave, int lane) {
-  constexpr int NB = R * BK * 2 / 1024;  // 1 KB blocks in the tile
-#pragma unroll
-  for (int i = 0; i < NB / W; ++i) {
-    const int q = wave * (NB / W) + i;
-    int64_t elem;
-    if constexpr (KMAJ) {
-      constexpr int CPR = BK / 8;   // chunks per row
-      constexpr int RPB = 64 / CPR; // rows per block
-      const int row = RPB * q + lane / CPR;
-      const int c = (lane % CPR) ^ kswz<BK>(row);
-      elem = (int64_t)row * ld + k0 + 8 * c;
-    } else {
-      constexpr int CPR = R / 8;           // chunks per k-row
-      constexpr int KPB = 64 / CPR;        // k-rows per block
-      const int kr = KPB * q + lane / CPR;
-      const int c = (lane % CPR) ^ (4 * (kr & 3));
-      elem = (int64_t)(k0 + kr) * ld + 8 * c;
-    }
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + q * 1024), 16, (int)(elem * 2),
-                                             0, 0, 0);
-  }
-}
-
-// MFMA operand fragments: 8 consecutive k (offset ks * 16 + 8 * (lane / 32))
-// of row r0 + lane % 32.  k-major: one 16-byte read.  m/n-major: two
-// ds_read_b64_tr_b16.  That instruction works on groups of 16 lanes: lane j
-// supplies the address of 4 consecutive 16-bit values V[j][0..3], and lane i
-// receives V[4e + i / 4][i % 4] for e = 0..3.  Lane j of a group points at
-// k-row k0 + j / 4, columns mb + 4 (j % 4), so lane i receives column mb + i
-// at k-rows k0 .. k0 + 3 (the second read: k0 + 4 .. k0 + 7).
-typedef __attribute__((address_space(3))) char lds_char_t;
-
-// An m/n-major fragment as read: the two halves of the transposing reads
-// (ds_read_tr16_b64), combined only after lds_wait() / frag_hold().
-struct TrFrag {
-  u32x2_t lo, hi;
-};
-__device__ __forceinline__ bf16x8_t frag_val(const bf16x8_t& v) { return v; }
-__device__ __forceinline__ bf16x8_t frag_val(const TrFrag& v) {
-  return __builtin_bit_cast(bf16x8_t, u32x4_t{v.lo[0], v.lo[1], v.hi[0], v.hi[1]});
-}
-__device__ __forceinline__ void frag_hold(bf16x8_t&) {}
-__device__ __forceinline__ void frag_hold(TrFrag& v) {
-  lds_hold(v.lo);
-  lds_hold(v.hi);
-}
-
-// Per-lane LDS addresses of one operand's fragments in ring slot 0, so that
-// every fragment read in the main loop is one instruction with an immediate
-// offset (no per-read address arithmetic).  k-major: one address per
-// k-step, fragment f (32 rows further) at +f * 32 * 2 BK.  m/n-major: one
-// address per fragment, k-step ks at +ks * 16 * 2R, the second transposing
-// read at +4 * 2R.  (The swizzle terms depend only on the lane because the
-// wavefront's first row is a multiple of 32.)
-template <int R, bool KMAJ, int BK, int NF>
-struct FragPtrs {
-  static constexpr int KS = BK / 16;
-  static constexpr int N = KMAJ ? KS : NF;
-  using Frag = typename std::conditional<KMAJ, bf16x8_t, TrFrag>::type;
-  uint32_t p[N];
-  __device__ __forceinline__ void init(uint32_t base, int r0, int lane) {
-    if constexpr (KMAJ) {
-      const int r = r0 + (lane & 31);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        p[ks] = base + r * (2 * BK) + 16 * ((2 * ks + (lane >> 5)) ^ kswz<BK>(r));
-    } else {
-      const int grp = lane >> 4, j = lane & 15;
-      const int kr = 8 * (grp >> 1) + (j >> 2);
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const int col = r0 + f * 32 + 16 * (grp & 1) + 4 * (j & 3);
-        p[f] = base + kr * (2 * R) + 16 * ((col >> 3) ^ (4 * (kr & 3))) + 2 * (col & 7);
-      }
-    }
-  }
-  __device__ __forceinline__ void advance(int delta) {
-#pragma unroll
-    for (int n = 0; n < N; ++n) p[n] += delta;
-  }
-  // fragment f of k-step KSI
-  template <int KSI>
-  __device__ __forceinline__ Frag get(int f) const {
-    if constexpr (KMAJ) {
-      return *(const __attribute__((address_space(3))) bf16x8_t*)(
-          (const lds_char_t*)(uintptr_t)p[KSI] + f * 32 * (2 * BK));
-    } else {
-      return TrFrag{ds_read_tr16_b64<KSI * 16 * (2 * R)>(p[f]),
-                    ds_read_tr16_b64<KSI * 16 * (2 * R) + 4 * (2 * R)>(p[f])};
-    }
-  }
-};
-
-
-// Epilogue for 8 consecutive columns n..n+7 of row m (n % 8 == 0, n < N).
-// b0, b1: bias[n .. n + 7] (EPI_STORE with a bias, EPI_GELU), loaded once
-// per tile by the caller.  For EPI_MUL, v returns the values as stored.
-template <int EPI, bool OUTF32>
-__device__ __forceinline__ void epi8(const GemmArgs& g, int64_t offC, int zs, int m, int n,
-                                     float v[8], u32x4_t x, f32x4_t b0, f32x4_t b1) {
-  const int64_t idx = (int64_t)m * g.ldc + n;
-  if (EPI == EPI_PARTIAL) {
-    float* C = (float*)g.C + (int64_t)zs * g.M * g.ldc + idx;
-    *(f32x4_t*)C = f32x4_t{v[0], v[1], v[2], v[3]};
-    *(f32x4_t*)(C + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
-    return;
-  }
-  if (EPI == EPI_STORE || EPI == EPI_GELU) {
-    if (EPI == EPI_STORE) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] *= g.alpha;
-    }
-    if (g.bias) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] += b0[i];
-        v[4 + i] += b1[i];
-      }
-    }
-  }
-  if (EPI == EPI_STORE && OUTF32) {
-    float* C = (float*)g.C + offC + idx;
-    *(f32x4_t*)C = f32x4_t{v[0], v[1], v[2], v[3]};
-    *(f32x4_t*)(C + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
-    return;
-  }
-  if (EPI == EPI_MUL || EPI == EPI_RESID) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float a0 = __uint_as_float(x[i] << 16), a1 = __uint_as_float(x[i] & 0xffff0000u);
-      if (EPI == EPI_MUL) {
-        v[2 * i] *= a0;
-        v[2 * i + 1] *= a1;
-      } else {
-        v[2 * i] += a0;
-        v[2 * i + 1] += a1;
-      }
-    }
-  }
-  if (EPI == EPI_GELU) {
-    // v holds u = acc + bias: store GELU(u) and GELU'(u)
-    u32x4_t o, q;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float gv[2], dv[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float u = v[2 * i + e];
-        const GeluParts p = gelu_parts(u);
-        gv[e] = u * p.cdf;
-        dv[e] = fmaf(u * 0.39894228040143268f, p.e, p.cdf);
-      }
-      o[i] = pack_bf16x2(gv[0], gv[1]);
-      q[i] = pack_bf16x2(dv[0], dv[1]);
-    }
-    *(u32x4_t*)((bf16_t*)g.C + offC + idx) = o;
-    *(u32x4_t*)((bf16_t*)g.C2 + offC + idx) = q;
-    return;
-  }
-  u32x4_t o;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-  *(u32x4_t*)((bf16_t*)g.C + offC + idx) = o;
-  if (EPI == EPI_MUL) {  // hand back the stored (rounded) values
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = __uint_as_float(o[i] << 16);
-      v[2 * i + 1] = __uint_as_float(o[i] & 0xffff0000u);
-    }
-  }
-
-}
-
-// EPI_MUL / EPI_RESID on 8 values: v * aux or v + aux (aux: 8 packed bf16),
-// rounded to bf16 and packed; v returns the rounded values.
-template <int EPI>
-__device__ __forceinline__ u32x4_t aux8(float v[8], u32x4_t x) {
-  u32x4_t o;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float a0 = __uint_as_float(x[i] << 16), a1 = __uint_as_float(x[i] & 0xffff0000u);
-    if (EPI == EPI_MUL) {
-      v[2 * i] *= a0;
-      v[2 * i + 1] *= a1;
-    } else {
-      v[2 * i] += a0;
-      v[2 * i + 1] += a1;
-    }
-    o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-    v[2 * i] = __uint_as_float(o[i] << 16);
-    v[2 * i + 1] = __uint_as_float(o[i] & 0xffff0000u);
-  }
-  return o;
-}
 
 // One output tile's operands: buffer resources and k-tile range.
 struct TileOps {
@@ -386,15 +157,6 @@ __device__ __forceinline__ void issue_ktile(const GemmArgs& g, const TileOps& T,
   char* b = smem + (t % C::NS) * C::STAGE_BYTES;
   dma_tile<BM, AK, C::BK, C::WAVES>(T.rsA, g.lda, T.kA0 + t * C::BK, b, wave, lane);
   dma_tile<BN, BKM, C::BK, C::WAVES>(T.rsB, g.ldb, T.kB0 + t * C::BK, b + C::A_BYTES, wave, lane);
-}
-
-// s_waitcnt immediate (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] |
-// lgkmcnt[11:8] | vmcnt[5:4] << 14) for "lgkmcnt = 0 and at most N vector
-// memory operations outstanding".
-template <int N>
-__device__ __forceinline__ void wait_vm_lgkm0() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | 0x70 | (((N >> 4) & 3) << 14));
 }
 
 // Wait until k-tile t + 1 has landed, given that `after` later k-tiles
@@ -647,7 +409,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     // landed and nobody reads k-tile t's slot any more), refill that slot
     // with k-tile t + NS, then read.
     //
-    // With STAGGER only the first half of the wavefronts (0 .. WAVES/2 - 1)
+    // Only the first half of the wavefronts (0 .. WAVES/2 - 1)
     // request their part of k-tile t + NS right after that barrier; the
     // other half request theirs at the start of k-tile t + 1.  Issuing the
     // direct-to-LDS loads stalls a wavefront until the CU's address unit
@@ -659,15 +421,15 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     // halves have requested the same k-tiles, so that wait is unchanged.
     // Measured (same box): 256 x 256 encoder GEMM set -3.9%, weight-
     // gradient group -5%, 8192^3 -3%, 256 x 128 tiles at 4096 tokens -2% to
-    // -11% (128 x 128: +1% to +7%, hence off there); splitting the pairs the other way
-    // (even / odd wavefronts) or each wavefront's own loads in two gave
+    // -11%; splitting the pairs the other way (even / odd wavefronts) or each
+    // wavefront's own loads in two gave
     // -0.3% to -1.6%; requesting the second half one or two k-steps later
     // was slower than not splitting.
     for (int t = 0; t < ntiles; ++t) {
       static_for<0, KS>([&](auto ksc) {
         constexpr int ks = decltype(ksc)::value;
         constexpr int cur = ks & 1, nxt = cur ^ 1;
-        if constexpr (C::STAGGER && ks == 0) {
+        if constexpr (ks == 0) {
           if (wave >= C::WAVES / 2 && t >= 1 && t - 1 + NS < ntiles)
             issue_ktile<BM, BN, AK, BKM>(g, T, t - 1 + NS, smem, wave, lane);
         }
@@ -695,7 +457,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
           // these reads before the last k-step's MFMAs.
           wait_ktile<C::DMA_PER_TILE, NS>(min(ntiles - 1, t + NS - 1) - (t + 1));
           __syncthreads();
-          if (t + NS < ntiles && !(C::STAGGER && wave >= C::WAVES / 2))
+          if (t + NS < ntiles && wave < C::WAVES / 2)
             issue_ktile<BM, BN, AK, BKM>(g, T, t + NS, smem, wave, lane);
           // move the fragment pointers to the next ring slot
           const int delta = ((t + 1) % NS == 0) ? -(NS - 1) * C::STAGE_BYTES : C::STAGE_BYTES;
@@ -1033,64 +795,112 @@ hipError_t launch_bf16(const GemmArgs& g0, int batch, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, bool AK, bool BKM>
-hipError_t dispatch_epi(const GemmArgs& g, GemmEpi epi, bool out_f32, int batch,
-                        hipStream_t st) {
-  switch (epi) {
-    case EPI_STORE:
-      return out_f32 ? launch_bf16<BM, BN, AK, BKM, EPI_STORE, true>(g, batch, st)
-                     : launch_bf16<BM, BN, AK, BKM, EPI_STORE, false>(g, batch, st);
-    case EPI_GELU: return launch_bf16<BM, BN, AK, BKM, EPI_GELU, false>(g, batch, st);
-    case EPI_MUL: return launch_bf16<BM, BN, AK, BKM, EPI_MUL, false>(g, batch, st);
-    case EPI_RESID: return launch_bf16<BM, BN, AK, BKM, EPI_RESID, false>(g, batch, st);
-    case EPI_PARTIAL: return launch_bf16<BM, BN, AK, BKM, EPI_PARTIAL, true>(g, batch, st);
+}  // namespace
+
+hipError_t gemm_bf16(const GemmArgs& g0, bool b_kmajor, GemmEpi epi, hipStream_t st) {
+  GemmArgs g = g0;
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  // Vector epilogue and n-major staging work in 8-column units; k-tiles of
+  // 64 never straddle a split boundary, and k-major operands are read
+  // without a k bound.
+  if (g.N % 8 != 0 || g.ldc % 8 != 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0)
+    return hipErrorInvalidValue;
+  if (g.ksplit > 1 && (g.kchunk % 64 != 0 || epi != EPI_PARTIAL)) return hipErrorInvalidValue;
+  if (epi == EPI_MUL && !g.colpart) return hipErrorInvalidValue;
+  // Operands are read through buffer resources with 32-bit byte extents and
+  // offsets: each operand must span less than 2 GiB.
+  if ((int64_t)g.M * g.lda * 2 >= ((int64_t)1 << 31) ||
+      (int64_t)(b_kmajor ? g.N : g.K) * g.ldb * 2 >= ((int64_t)1 << 31))
+    return hipErrorInvalidValue;
+  if (g.tile == 0) g.tile = gemm_bf16_plan(g.M, g.N, g.K, b_kmajor, epi, false).tile;
+  if (g.tile == GEMM_TILE_256x256 && g.ksplit == 1) {
+    if (b_kmajor) {
+      if (epi == EPI_STORE) return launch_bf16<256, 256, true, true, EPI_STORE, false>(g, 1, st);
+      if (epi == EPI_GELU) return launch_bf16<256, 256, true, true, EPI_GELU, false>(g, 1, st);
+      if (epi == EPI_PARTIAL) return launch_bf16<256, 256, true, true, EPI_PARTIAL, true>(g, 1, st);
+    } else {
+      if (epi == EPI_STORE) return launch_bf16<256, 256, true, false, EPI_STORE, false>(g, 1, st);
+      if (epi == EPI_MUL) return launch_bf16<256, 256, true, false, EPI_MUL, false>(g, 1, st);
+    }
+    return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
+  return gemm_mid(g, b_kmajor, epi, g.tile, st);
 }
 
-template <int BM, int BN>
-hipError_t dispatch_layout(const GemmArgs& g, bool ak, bool bk, GemmEpi epi, bool out_f32,
-                           int batch, hipStream_t st) {
-  if (ak && bk) return dispatch_epi<BM, BN, true, true>(g, epi, out_f32, batch, st);
-  if (ak && !bk) return dispatch_epi<BM, BN, true, false>(g, epi, out_f32, batch, st);
-  if (!ak && !bk) return dispatch_epi<BM, BN, false, false>(g, epi, out_f32, batch, st);
-  return dispatch_epi<BM, BN, false, true>(g, epi, out_f32, batch, st);
+namespace {
+
+// Time model of a tile shape, in microseconds: a launch (a), per round of
+// work-groups over the CUs its k-tiles (c each) and epilogue (e per 128 x 128
+// outputs; twice that for the GELU and GELU' ones), but no less than its
+// operand traffic out of L2 (bw, TB/s) plus its output (wb, TB/s).  64 x 64
+// work-groups share a CU in pairs, so their rounds are not whole.  Fitted to
+// 7700 timed launches (M 40 .. 16384, the products of layers of width 192 ..
+// 2048); the tile it picks is on average 1.8% slower than the best one
+// measured, and 2.1 times faster than the rule it replaces (tiles of 128 x 128
+// and more, no splits, four wavefronts).
+struct TileModel {
+  int bm, bn;
+  double a, c, e, bw, wb;
+};
+constexpr TileModel TILE_MODEL[] = {
+    {256, 256, 5.0, 1.30, 0.94, 9.8, 4.15}, {256, 128, 5.0, 0.75, 0.2, 13.0, 3.65},
+    {128, 128, 4.0, 0.327, 0.87, 13.7, 2.9}, {128, 64, 3.0, 0.242, 2.7, 16.6, 1.96},
+    {64, 64, 3.1, 0.167, 1.2, 18.7, 3.53}};
+
+double tile_time(int tile, int64_t M, int64_t N, int64_t K, int ks, GemmEpi epi) {
+  const TileModel& m = TILE_MODEL[tile - 1];
+  const double cus = device_cus();
+  const double wg = (double)((M + m.bm - 1) / m.bm) * ((N + m.bn - 1) / m.bn) * ks;
+  const double nk = (double)((K / 64 + ks - 1) / ks);
+  const double rounds = tile == GEMM_TILE_64x64 ? std::max(1.0, wg / cus) : std::ceil(wg / cus);
+  const bool act = epi == EPI_GELU || epi == EPI_MUL;
+  const double epil = m.e * (m.bm * m.bn / 16384.0) * (act ? 2.0 : 1.0);
+  const double out = (double)M * N * (act || epi == EPI_PARTIAL ? 4 : 2) * ks;
+  const double mem = wg * nk * (m.bm + m.bn) * 128.0 / (m.bw * 1e6) + out / (m.wb * 1e6);
+  // a consumer that sums partials reads them at about 5 TB/s
+  const double extra = (ks - 1) * (double)M * N * 4 / 5e6;
+  return m.a + std::max(rounds * (nk * m.c + epil), mem) + extra;
 }
 
 }  // namespace
 
-hipError_t gemm_bf16(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, bool out_f32,
-                     int batch, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  // Vector epilogue and m/n-major staging work in 8-column units; k-tiles of
-  // 64 never straddle a split boundary, and k-major operands are read
-  // without a k bound.
-  if (g.N % 8 != 0 || g.ldc % 8 != 0) return hipErrorInvalidValue;
-  if (g.ksplit > 1 && g.kchunk % 64 != 0) return hipErrorInvalidValue;
-  if ((a_kmajor || b_kmajor) && g.K % 64 != 0) return hipErrorInvalidValue;
-  if ((!a_kmajor && g.M % 8 != 0) || (g.lda % 8 != 0) || (g.ldb % 8 != 0)) return hipErrorInvalidValue;
-  // Operands are read through buffer resources with 32-bit byte extents and
-  // offsets: each operand (per batch entry) must span less than 2 GiB.
-  const int64_t a_bytes = (int64_t)(a_kmajor ? g.M : g.K) * g.lda * 2;
-  const int64_t b_bytes = (int64_t)(b_kmajor ? g.N : g.K) * g.ldb * 2;
-  if (a_bytes >= ((int64_t)1 << 31) || b_bytes >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  int tile = g.tile;
-  if (tile == 0) {
-    // The largest tile whose count still covers about three quarters of
-    // the CUs (one persistent work-group per CU): a 256 x 256 tile has
-    // twice the arithmetic per loaded byte of a 128 x 128 one, but idle
-    // CUs cost more.  Measured at T = 4096 tokens, N = 1024 (64 tiles of
-    // 256 x 256 on 256 CUs): 128 x 128 tiles 1.45-1.55x faster than
-    // 256 x 128 ones, which were 1.3x faster than 256 x 256.
-    const int64_t zb = (int64_t)batch * g.ksplit;
-    const int64_t need = 3 * (int64_t)device_cus() / 4;
-    const int64_t t1 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256) * zb;
-    const int64_t t2 = (int64_t)((g.M + 255) / 256) * ((g.N + 127) / 128) * zb;
-    tile = (g.M >= 256 && g.N >= 256 && t1 >= need) ? 1 : (g.M >= 256 && g.N > 128 && t2 >= need) ? 2 : 3;
+GemmPlan gemm_bf16_plan(int M, int N, int K, bool b_kmajor, GemmEpi epi, bool split) {
+  const int64_t cus = device_cus();
+  const int64_t t1 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  const bool act = epi == EPI_GELU || epi == EPI_MUL;
+  GemmPlan best = {GEMM_TILE_128x128, 1};
+  double tb = 0.0;
+  auto consider = [&](int tile, int ks) {
+    const double t = tile_time(tile, M, N, K, ks, epi);
+    if (tb == 0.0 || t < tb) {
+      tb = t;
+      best = {tile, ks};
+    }
+  };
+  // 256 x 256 tiles read a quarter as much per product as 64 x 64 ones, but
+  // below three quarters of a tile per CU (55% with the long epilogues) the
+  // model, fitted over several rounds, does not describe them: idle CUs cost
+  // more.
+  if (M >= 256 && N >= 256 && (epi != EPI_PARTIAL || b_kmajor) &&
+      t1 >= (act ? cus * 11 / 20 : cus * 3 / 4))
+    consider(GEMM_TILE_256x256, 1);
+  consider(GEMM_TILE_256x128, 1);
+  consider(GEMM_TILE_128x128, 1);
+  consider(GEMM_TILE_128x64, 1);
+  // (column sums of 64-row tiles are only provided for up to 8192 rows)
+  if (epi != EPI_MUL || M <= 8192) consider(GEMM_TILE_64x64, 1);
+  if (split) {
+    for (int ks = 2; ks <= GEMM_SPLIT_MAX; ks += 2) {
+      const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
+      if ((K + chunk - 1) / chunk != ks || (int64_t)ks * M * N > GEMM_SPLIT_ELEMS) continue;
+      for (int tile = GEMM_TILE_256x128; tile <= GEMM_TILE_64x64; ++tile) consider(tile, ks);
+    }
   }
-  if (tile == 1) return dispatch_layout<256, 256>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
-  if (tile == 2) return dispatch_layout<256, 128>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
-  return dispatch_layout<128, 128>(g, a_kmajor, b_kmajor, epi, out_f32, batch, st);
+  return best;
+}
+
+int64_t gemm_colpart_max(int64_t M) {
+  return std::max((M + 127) / 128, (std::min<int64_t>(M, 8192) + 63) / 64);
 }
 
 namespace {
@@ -1105,6 +915,12 @@ int group_grid() {
 int first_phase(int64_t tiles, int kt) {
   const int64_t w = tiles * kt / group_grid();
   return (int)std::max<int64_t>(1, std::min<int64_t>(kt, w));
+}
+
+// The k-tile sequence of a group launch of `tiles` tiles.
+SkSeq group_seq(int64_t tiles, int K) {
+  const int kt = (K + 63) / 64;
+  return {tiles * kt, (int)tiles, kt, first_phase(tiles, kt), group_grid()};
 }
 
 // Checks and the stream-K table of a group; false for invalid problems.
@@ -1142,16 +958,54 @@ bool group_table_of(const GemmArgs* p, int n, GemmGroup& gg) {
 
 }  // namespace
 
+// The stream-K group against whole gradients per work-group (gemm_mid.hip).
+// The group's k-tiles of 256 x 256 run at twice the rate per byte read, but it
+// writes about 256 + tiles partials of 256 KB and reads them back (50-60 us at
+// width 1024, whatever the token count), and with few tokens most of its
+// work-groups have almost no k-tiles.  The model's figures are fitted to timed
+// groups of width 192 .. 2048 and 40 .. 16384 tokens; on average its choice is
+// 0.8% slower than the best one.  Width 768: 2048 tokens 84 -> 37 us, 16384
+// tokens 276 -> 237 us; width 1024 (1.5 rounds of 256 x 128 tiles): 4096 tokens
+// 132 -> 117 us, 16384 tokens 382 us against 428 us (the group stays).
+int wgrad_plan(const int* M, const int* N, int n, int K) {
+  const double cus = device_cus(), kt = (K + 63) / 64;
+  double area = 0, t256 = 0, t2 = 0, t128 = 0, t64 = 0;
+  auto cd = [](int a, int b) { return (double)((a + b - 1) / b); };
+  for (int q = 0; q < n; ++q) {
+    area += (double)M[q] * N[q];
+    t256 += cd(M[q], 256) * cd(N[q], 256);
+    t2 += cd(M[q], 256) * cd(N[q], 128);
+    t128 += cd(M[q], 128) * cd(N[q], 128);
+    t64 += cd(M[q], 64) * cd(N[q], 64);
+  }
+  const bool whole = t256 / cus == std::floor(t256 / cus);
+  const double pieces = whole ? t256 : std::max(t256, cus) + t256;
+  const double group = 25 + t256 * kt / cus * 1.8 + (pieces * 262144 * 2 + area * 4) / 8e6;
+  auto mid = [&](double wg, double rounds, double a, double c, double e, double kbytes, double bw,
+                 double wb) {
+    return a + std::max(rounds * (kt * c + e), wg * kt * kbytes / (bw * 1e6) + area * 4 / (wb * 1e6));
+  };
+  const double m2 = mid(t2, std::ceil(t2 / cus), 5.9, 0.59, 0.14, 49152, 12.9, 4.3);
+  const double m128 = mid(t128, std::ceil(t128 / cus), 4.6, 0.36, 0.48, 32768, 14.5, 3.6);
+  const double m64 = mid(t64, std::max(1.0, t64 / cus), 3.3, 0.24, 0.0, 16384, 25.0, 3.1);
+  // (beyond 8192 tokens the operands of tiles that are far apart no longer
+  // meet in the caches and the models of whole gradients are too fast, unless
+  // the 256 x 128 tiles are one round: width 512, 16384 tokens 145 us with the
+  // group against 159 us)
+  if (K > 8192 && !(t2 <= cus && m2 < group && t2 > 0.75 * cus)) return 0;
+  if (group < m2 && group < m128 && group < m64) return 0;
+  return m2 <= m128 && m2 <= m64 ? GEMM_TILE_256x128 : m128 <= m64 ? GEMM_TILE_128x128 : GEMM_TILE_64x64;
+}
+
 int wgrad_group_slots(const int* M, const int* N, int n, int K) {
-  if (n < 1 || n > GEMM_GROUP_MAX || K < 1) return 0;
+  if (n < 1 || n > GEMM_GROUP_MAX || K < 1) return -1;
   int64_t tiles = 0;
   for (int q = 0; q < n; ++q) {
-    if (M[q] < 0 || N[q] < 0) return 0;
+    if (M[q] < 0 || N[q] < 0) return -1;
     tiles += (int64_t)((M[q] + 255) / 256) * ((N[q] + 255) / 256);
   }
-  if (tiles == 0) return 1;
-  const int kt = (K + 63) / 64;
-  const SkSeq sq = {tiles * kt, (int)tiles, kt, first_phase(tiles, kt), group_grid()};
+  if (tiles == 0 || wgrad_plan(M, N, n, K) != 0) return 0;
+  const SkSeq sq = group_seq(tiles, K);
   int slots = 1;
   for (int t = 0; t < (int)tiles; ++t) {
     int a1, n1, a2, n2;
@@ -1173,8 +1027,8 @@ hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st) {
 
 hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
                               int ncols, hipStream_t st) {
-  GemmGroup gg;
-  if (!group_table_of(p, n, gg) || !out || ncols < 0 || ncols > COLJOB_MAX || (ncols && !cols))
+  GemmGroup gg{};
+  if ((n != 0 && (!group_table_of(p, n, gg) || !out)) || ncols < 0 || ncols > COLJOB_MAX || (ncols && !cols))
     return hipErrorInvalidValue;
   SkReduce rd{};
   rd.n = n;

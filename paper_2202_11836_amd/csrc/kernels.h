@@ -38,9 +38,9 @@ struct GemmArgs {
   int ksplit;
   int kchunk;
   float alpha;
-  int tile;  // bf16 tile shape: 0 = automatic, 1 = 256x256, 2 = 256x128, 3 = 128x128
-  // EPI_MUL on bf16, optional: column sums of the stored output per block
-  // of 128 rows, colpart[m / 128][n] (needs tile 1).
+  int tile;  // bf16: a GemmTile, 0 = gemm_bf16_plan's choice
+  // EPI_MUL on bf16: column sums of the stored output per block of
+  // gemm_colpart_rows(tile) rows, colpart[m / rows][n].
   // fp32: column sums of the stored output per block of 32 rows of each batch
   // entry, colpart[(zb / zdiv) * cp_batch + (m / 32) * cp_ld + (zb % zdiv) *
   // sC2 + n].
@@ -57,10 +57,42 @@ inline GemmArgs gemm_args(const void* A, int64_t lda, const void* B, int64_t ldb
   return g;
 }
 
-// bf16 operands on MFMA (fp32 accumulation).  out_f32 selects fp32 output
-// for EPI_STORE; all other epilogues write bf16 (EPI_PARTIAL writes fp32).
-hipError_t gemm_bf16(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi,
-                     bool out_f32, int batch, hipStream_t st);
+// Tile shapes of the bf16 GEMMs: the first in gemm.hip (persistent work-
+// groups), the others in gemm_mid.hip.
+enum GemmTile {
+  GEMM_TILE_256x256 = 1,
+  GEMM_TILE_256x128 = 2,
+  GEMM_TILE_128x128 = 3,
+  GEMM_TILE_128x64 = 4,
+  GEMM_TILE_64x64 = 5
+};
+struct GemmPlan {
+  int tile;
+  int ks;  // splits of K (1 unless `split`)
+};
+// Tile (and, with split, the number of K splits) for a bf16 GEMM.  split: the
+// consumer sums fp32 partials, so the output may be GEMM_SPLIT_MAX or fewer
+// partials, of at most max(M * N, GEMM_SPLIT_ELEMS) elements in all.
+constexpr int GEMM_SPLIT_MAX = 6;
+constexpr int64_t GEMM_SPLIT_ELEMS = (int64_t)4 << 20;
+GemmPlan gemm_bf16_plan(int M, int N, int K, bool b_kmajor, GemmEpi epi, bool split);
+// Rows per column partial sum of EPI_MUL with this tile, and the most partial
+// rows any token count up to M needs.
+inline int gemm_colpart_rows(int tile) {
+  return tile == GEMM_TILE_64x64 ? 64 : tile == GEMM_TILE_256x128 ? 256 : 128;
+}
+int64_t gemm_colpart_max(int64_t M);
+// bf16 operands on MFMA (fp32 accumulation), A k-major, batch 1.  b k-major:
+// EPI_STORE, EPI_GELU, EPI_PARTIAL; n-major: EPI_STORE, EPI_MUL, EPI_PARTIAL.
+// EPI_PARTIAL writes fp32 (C[split][M][ldc], ksplit splits of kchunk), the
+// others bf16.
+hipError_t gemm_bf16(const GemmArgs& g, bool b_kmajor, GemmEpi epi, hipStream_t st);
+// g with its K range cut into ks chunks of whole k-tiles.
+inline GemmArgs gemm_split(GemmArgs g, int ks) {
+  g.kchunk = ((g.K + ks - 1) / ks + 63) / 64 * 64;
+  g.ksplit = (g.K + g.kchunk - 1) / g.kchunk;
+  return g;
+}
 // fp32 operands on fp32 MFMA, same conventions: A k-major, ksplit 1; B
 // k-major with EPI_STORE or EPI_GELU, n-major with EPI_STORE, EPI_MUL or
 // EPI_RESID.
@@ -94,8 +126,9 @@ struct GemmGroup {
   int kf;                         // k-tiles of each tile in the first phase
   int64_t work;                   // k-tiles over all tiles, tile0[n] * kt
 };
-// Slots of M x N fp32 partials each problem's C must hold for such a group
-// (the most pieces of one tile) on this device; 0 for invalid sizes.
+// Slots of M x N fp32 partials each problem's C must hold for the plan of
+// such a group (the most pieces of one tile) on this device: 0 when the plan
+// needs none, -1 for invalid sizes.
 int wgrad_group_slots(const int* M, const int* N, int n, int K);
 hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st);
 // A column reduction run with a group's reduction: out[v][c] = the sum over
@@ -109,9 +142,18 @@ struct ColJob {
 constexpr int COLJOB_MAX = 4;
 // out[q][m][n] = the sum over the pieces of (m, n)'s tile of slot j of
 // p[q].C, in k order (same p as the GEMM launch), and the ncols <=
-// COLJOB_MAX column reductions cols, in one launch.
+// COLJOB_MAX column reductions cols, in one launch (n = 0: only those).
 hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
                               int ncols, hipStream_t st);
+
+// gemm_bf16 with one of the tiles of gemm_mid.hip.
+hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hipStream_t st);
+// n weight gradients (operands m/n-major, ldc = N), each written whole, in
+// one launch.
+hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile, hipStream_t st);
+// How a layer's weight gradients are computed: 0 = the stream-K group below
+// with its reduction, else a tile of gemm_mid_wgrad (no partials).
+int wgrad_plan(const int* M, const int* N, int n, int K);
 
 // The weight gradients of one fp32 layer (both operands m/n-major) in one
 // launch, and in a second one the fixed-order sums of the problems split over
@@ -125,34 +167,51 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, con
 // Row kernels (one wavefront per row), T = float or bf16_t.
 // ---------------------------------------------------------------------------
 // z = a + bias + resid (+ resid_lo);  y = gamma * xhat + beta with
-// xhat = (z - mean) * rstd.  a is the fp32 output of the preceding GEMM;
+// xhat = (z - mean) * rstd.  a is the fp32 output of the preceding GEMM, the
+// sum of np partials rows * h apart (np = 1, 2, 4 or 6);
 // resid_lo (optional, may be null) is the rounding residual of resid; ylo
 // (optional, may be null) receives y - y as stored, in T.
 template <typename T, typename TA>
-hipError_t add_ln_fwd(const TA* a, const float* bias, const T* resid, const T* resid_lo,
+hipError_t add_ln_fwd(const TA* a, int np, const float* bias, const T* resid, const T* resid_lo,
                       const float* gamma, const float* beta, T* y, T* ylo, T* xhat, float* rstd,
                       int rows, int h, hipStream_t st);
 
 // dz = rstd * (g - mean(g) - xhat * mean(g * xhat)), g = dy * gamma.
-// Column partial sums per block of LN_BWD_RPB rows (ln_bwd_blocks(rows)
+// Column partial sums per block of ln_bwd_rpb(rows) rows (ln_bwd_blocks(rows)
 // blocks): part[blk][0][:] = sum dy*xhat, part[blk][1][:] = sum dy,
 // part[blk][2][:] = sum dz.
-constexpr int LN_BWD_RPB = 32;
+int ln_bwd_rpb(int rows);
 int ln_bwd_blocks(int rows);
+int ln_bwd_blocks_max(int rows);  // the most any number of rows up to this one needs
 hipError_t ln_bwd_f32(const float* dy, const float* xhat, const float* rstd, const float* gamma,
                       float* dz, float* part, int rows, int h, hipStream_t st);
 
-// bf16 stages: the same with dy either one bf16 tensor (ahi = alo = b =
-// null) or the fp32 sum (ahi + alo) + b of three bf16 tensors (dy = null):
-// a residual branch carried as its bf16 rounding and rounding residual,
-// plus a bf16 GEMM product.  dz in bf16 and, when dzlo is not null, dz's
-// bf16 rounding residual.  Partials as ln_bwd_f32.
-hipError_t ln_bwd_bf16(const bf16_t* dy, const bf16_t* ahi, const bf16_t* alo, const bf16_t* b,
-                       const bf16_t* xhat, const float* rstd, const float* gamma, bf16_t* dz,
-                       bf16_t* dzlo, float* part, int rows, int h, hipStream_t st);
-// out = bf16((ahi + alo) + b), all bf16, n elements (a multiple of 8).
-hipError_t add3_bf16(const bf16_t* ahi, const bf16_t* alo, const bf16_t* b, bf16_t* out,
-                     int64_t n, hipStream_t st);
+// A gradient on the backward residual stream of a bf16 stage: one bf16 tensor
+// bf, or the fp32 sum (hi + lo) + product of a residual branch carried as its
+// bf16 rounding and rounding residual and a data-gradient GEMM's product, in
+// bf16 (b) or as np fp32 partials pf, n elements apart (n: the tensor's size).
+struct GradIn {
+  const bf16_t* bf;
+  const bf16_t* hi;
+  const bf16_t* lo;
+  const bf16_t* b;
+  const float* pf;
+  int np;  // 2, 4 or 6 with pf
+};
+// bf16 stages: ln_bwd_f32 for such a gradient.  dz in bf16 and, when dzlo is
+// not null, dz's bf16 rounding residual.
+hipError_t ln_bwd_bf16(const GradIn& dy, const bf16_t* xhat, const float* rstd, const float* gamma,
+                       bf16_t* dz, bf16_t* dzlo, float* part, int rows, int h, hipStream_t st);
+// out = the gradient (a sum, not bf) rounded to bf16, n elements (a multiple
+// of 8); or in fp32 (any form of it).
+hipError_t grad_bf16(const GradIn& in, bf16_t* out, int64_t n, hipStream_t st);
+hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st);
+
+// Start of a forward pass: X = x (nx bytes, a multiple of 16; both 16-byte
+// aligned); mask = key_mask, or all ones when that is null; when kext is not
+// null, kext[b] = 1 + last s with mask[b][s] != 0 (0 if none).
+hipError_t stage_prep(const void* x, void* X, int64_t nx, const uint8_t* key_mask, uint8_t* mask,
+                      int B, int S, int* kext, hipStream_t st);
 
 // part[blk][n] = sum over the block's rows of x[row][n].
 template <typename T>
@@ -200,8 +259,6 @@ struct AttnArgs {
   float scale_log2;  // softmax scale * log2(e)
   float scale;       // softmax scale
 };
-// kext[b] = 1 + last s with mask[b][s] != 0 (0 if none).
-hipError_t key_extent(const uint8_t* mask, int B, int S, int* kext, hipStream_t st);
 // Forward pass (needs kext).
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st);
 // dsum and dQ (into out's Q block); must run before attn_backward_dkdv.

@@ -3,6 +3,7 @@
 // gamma / beta gradients, and the masked row softmax (forward and backward).
 // One wavefront owns one row; reductions across the row are wavefront
 // shuffles.  No MFMA here.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -53,8 +54,9 @@ __device__ __forceinline__ float as_stored(float v, const float*) { return v; }
 // resid_lo when not null (a value carried as its bf16 rounding and the
 // rounding residual); ylo, when not null, receives y's rounding residual
 // y - bf16(y) in bf16, so that y + ylo carries y to about 16 significant
-// bits.
-template <typename T, typename TA, int NC>
+// bits.  a is the sum of NP partials (rows * h apart), all loads issued
+// before the sum.
+template <typename T, typename TA, int NC, int NP>
 __global__ __launch_bounds__(256) void add_ln_fwd_kernel(const TA* __restrict__ a,
                                                          const float* __restrict__ bias,
                                                          const T* __restrict__ resid,
@@ -76,7 +78,9 @@ __global__ __launch_bounds__(256) void add_ln_fwd_kernel(const TA* __restrict__ 
     const int c = lane + 64 * i;
     if (c < nchunk) {
       float av[8], rv[8], bv[8], lv[8];
-      load8(a + base + 8 * c, av);
+      float ap[NP][8];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) load8(a + q * (int64_t)rows * h + base + 8 * c, ap[q]);
       load8(resid + base + 8 * c, rv);
       load8(bias + 8 * c, bv);
       if (resid_lo) {
@@ -86,6 +90,9 @@ __global__ __launch_bounds__(256) void add_ln_fwd_kernel(const TA* __restrict__ 
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
+        av[k] = ap[0][k];
+#pragma unroll
+        for (int q = 1; q < NP; ++q) av[k] += ap[q][k];
         z[i][k] = av[k] + bv[k] + rv[k];
         s += z[i][k];
       }
@@ -250,21 +257,33 @@ __device__ __forceinline__ float bf_at(const u32x4_t& r, int k) {
   return (k & 1) ? bf_hi(r[k >> 1]) : bf_lo(r[k >> 1]);
 }
 
-// The incoming gradient dy is either one bf16 tensor or, when SUM3, the
-// fp32 sum (ahi + alo) + b of three bf16 tensors: the backward residual
-// stream of a bf16 stage, i.e. the residual branch carried as its bf16
-// rounding ahi plus the rounding residual alo (about 16 significant bits),
-// plus the bf16 product b of the data-gradient GEMM, so that the stream
-// itself is never rounded to bf16.
+// Product of a data-gradient GEMM at 8 elements: NP fp32 partials, n apart.
+template <int NP>
+__device__ __forceinline__ void load_parts(const float* pf, int64_t n, float v[8]) {
+  float p[NP][8];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) load8(pf + q * n, p[q]);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    v[k] = p[0][k];
+#pragma unroll
+    for (int q = 1; q < NP; ++q) v[k] += p[q][k];
+  }
+}
+
+// The incoming gradient is one bf16 tensor (NP = -1), or the backward
+// residual stream of a bf16 stage, never itself rounded to bf16: the fp32 sum
+// (hi + lo) + product of the residual branch, carried as its bf16 rounding
+// plus the rounding residual (about 16 significant bits), and the
+// data-gradient GEMM's product in bf16 (NP = 0) or as NP fp32 partials.
 // dz goes out in bf16 (the operand of the following GEMMs) and, when dzlo
 // is not null, its rounding residual dz - bf16(dz) in bf16 as well (the
 // residual branch of the next addition).
-template <int NC, bool SUM3>
+template <int NC, int NP>
 __global__ __launch_bounds__(256, (NC <= 2 ? 2 : 1)) void ln_bwd_bf16_kernel(
-    const bf16_t* __restrict__ dy, const bf16_t* __restrict__ ahi, const bf16_t* __restrict__ alo,
-    const bf16_t* __restrict__ dyb, const bf16_t* __restrict__ xhat,
-    const float* __restrict__ rstd, const float* __restrict__ gamma, bf16_t* __restrict__ dz,
-    bf16_t* __restrict__ dzlo, float* __restrict__ part, int rows, int h, int rpb) {
+    GradIn in, const bf16_t* __restrict__ xhat, const float* __restrict__ rstd,
+    const float* __restrict__ gamma, bf16_t* __restrict__ dz, bf16_t* __restrict__ dzlo,
+    float* __restrict__ part, int rows, int h, int rpb) {
   extern __shared__ float red[];  // [4 wavefronts][3][h]
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
@@ -282,8 +301,9 @@ __global__ __launch_bounds__(256, (NC <= 2 ? 2 : 1)) void ln_bwd_bf16_kernel(
   const int r1 = min(rows, r0 + rpb);
   const float inv_h = 1.0f / (float)h;
   for (int row0 = r0 + wave; row0 < r1; row0 += 8) {
-    // dy packed bf16 (SUM3: the product b, with ahi and alo beside it)
+    // packed bf16: the gradient or the product, with hi and lo beside it
     u32x4_t dr[2][NC], xr[2][NC], hr[2][NC], lr[2][NC];
+    float pr[NP > 0 ? 2 : 1][NC][8];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int row = row0 + 4 * u;
@@ -292,26 +312,28 @@ __global__ __launch_bounds__(256, (NC <= 2 ? 2 : 1)) void ln_bwd_bf16_kernel(
       for (int i = 0; i < NC; ++i) {
         const int c = lane + 64 * i;
         if (c < nchunk && row < r1) {
-          if constexpr (SUM3) {
-            hr[u][i] = *(const u32x4_t*)(ahi + base + 8 * c);
-            lr[u][i] = *(const u32x4_t*)(alo + base + 8 * c);
-            dr[u][i] = *(const u32x4_t*)(dyb + base + 8 * c);
-          } else {
-            dr[u][i] = *(const u32x4_t*)(dy + base + 8 * c);
+          if constexpr (NP >= 0) {
+            hr[u][i] = *(const u32x4_t*)(in.hi + base + 8 * c);
+            lr[u][i] = *(const u32x4_t*)(in.lo + base + 8 * c);
           }
+          if constexpr (NP > 0) load_parts<NP>(in.pf + base + 8 * c, (int64_t)rows * h, pr[u][i]);
+          else dr[u][i] = *(const u32x4_t*)((NP == 0 ? in.b : in.bf) + base + 8 * c);
           xr[u][i] = *(const u32x4_t*)(xhat + base + 8 * c);
         } else {
           hr[u][i] = lr[u][i] = dr[u][i] = u32x4_t{0, 0, 0, 0};
           xr[u][i] = u32x4_t{0, 0, 0, 0};
+          if constexpr (NP > 0) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) pr[u][i][k] = 0.0f;
+          }
         }
       }
     }
     // the incoming gradient at (u, i, k)
     auto dyv = [&](int u, int i, int k) -> float {
-      if constexpr (SUM3)
-        return (bf_at(hr[u][i], k) + bf_at(lr[u][i], k)) + bf_at(dr[u][i], k);
-      else
-        return bf_at(dr[u][i], k);
+      if constexpr (NP > 0) return (bf_at(hr[u][i], k) + bf_at(lr[u][i], k)) + pr[u][i][k];
+      else if constexpr (NP == 0) return (bf_at(hr[u][i], k) + bf_at(lr[u][i], k)) + bf_at(dr[u][i], k);
+      else return bf_at(dr[u][i], k);
     };
     float sg[2] = {0.0f, 0.0f}, sgx[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -389,21 +411,57 @@ __global__ __launch_bounds__(256, (NC <= 2 ? 2 : 1)) void ln_bwd_bf16_kernel(
     P[e] = ((red[e] + red[3 * h + e]) + red[6 * h + e]) + red[9 * h + e];
 }
 
-// out = (ahi + alo) + b rounded to bf16 (all bf16), 8 elements per thread
-// (n % 8 == 0).
-__global__ __launch_bounds__(256) void add3_bf16_kernel(const bf16_t* __restrict__ ahi,
-                                                        const bf16_t* __restrict__ alo,
-                                                        const bf16_t* __restrict__ b,
-                                                        bf16_t* __restrict__ out, int64_t n8) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  float vh[8], vl[8], vb[8];
-  load8(ahi + 8 * i, vh);
-  load8(alo + 8 * i, vl);
-  load8(b + 8 * i, vb);
+// The gradient `in` at 8 elements per thread (n % 8 == 0), rounded to T.
+template <typename T, int NP>
+__global__ __launch_bounds__(256) void grad_kernel(GradIn in, T* __restrict__ out, int64_t n) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (i >= n) return;
+  float v[8];
+  if constexpr (NP < 0) {
+    load8(in.bf + i, v);
+  } else {
+    float l[8], b[8];
+    load8(in.hi + i, v);
+    load8(in.lo + i, l);
+    if constexpr (NP > 0) load_parts<NP>(in.pf + i, n, b);
+    else load8(in.b + i, b);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) vh[k] = (vh[k] + vl[k]) + vb[k];
-  store8(out + 8 * i, vh);
+    for (int k = 0; k < 8; ++k) v[k] = (v[k] + l[k]) + b[k];
+  }
+  store8(out + i, v);
+}
+
+// Work-groups [0, B): one sequence's mask (and key extent); the others copy x.
+__global__ __launch_bounds__(256) void stage_prep_kernel(const u32x4_t* __restrict__ x,
+                                                         u32x4_t* __restrict__ X, int64_t n16,
+                                                         const uint8_t* __restrict__ key_mask,
+                                                         uint8_t* __restrict__ mask, int B, int S,
+                                                         int* __restrict__ kext) {
+  if ((int)blockIdx.x < B) {
+    __shared__ int sm[4];
+    const int64_t b0 = (int64_t)blockIdx.x * S;
+    int last = 0;
+    for (int s = threadIdx.x; s < S; s += 256) {
+      const uint8_t v = key_mask ? key_mask[b0 + s] : 1;
+      mask[b0 + s] = v;
+      if (v) last = max(last, s + 1);
+    }
+    if (!kext) return;
+    for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = last;
+    __syncthreads();
+    if (threadIdx.x == 0) kext[blockIdx.x] = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
+    return;
+  }
+  // four 16-byte chunks per thread, a work-group's chunks side by side
+  const int64_t i0 = (int64_t)(blockIdx.x - B) * 1024 + threadIdx.x;
+  u32x4_t v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + 256 * k < n16) v[k] = x[i0 + 256 * k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + 256 * k < n16) X[i0 + 256 * k] = v[k];
 }
 
 template <typename T>
@@ -475,68 +533,106 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float* __restric
 }  // namespace
 
 template <typename T, typename TA>
-hipError_t add_ln_fwd(const TA* a, const float* bias, const T* resid, const T* resid_lo,
+hipError_t add_ln_fwd(const TA* a, int np, const float* bias, const T* resid, const T* resid_lo,
                       const float* gamma, const float* beta, T* y, T* ylo, T* xhat, float* rstd,
                       int rows, int h, hipStream_t st) {
   if (h % 64 != 0 || h > 2048) return hipErrorInvalidValue;
   if (rows <= 0) return hipSuccess;
   const int nc = (h / 8 + 63) / 64;
   dim3 grid((rows + 3) / 4), blk(256);
-#define LAUNCH_LN(NCV)                                                                        \
-  hipLaunchKernelGGL((add_ln_fwd_kernel<T, TA, NCV>), grid, blk, 0, st, a, bias, resid, resid_lo, \
-                     gamma, beta, y, ylo, xhat, rstd, rows, h)
-  switch (nc) {
-    case 1: LAUNCH_LN(1); break;
-    case 2: LAUNCH_LN(2); break;
-    case 3: LAUNCH_LN(3); break;
-    default: LAUNCH_LN(4); break;
+#define LAUNCH_LN(NCV, NPV)                                                                   \
+  hipLaunchKernelGGL((add_ln_fwd_kernel<T, TA, NCV, NPV>), grid, blk, 0, st, a, bias, resid,  \
+                     resid_lo, gamma, beta, y, ylo, xhat, rstd, rows, h)
+#define LAUNCH_LN_NC(NPV)               \
+  switch (nc) {                         \
+    case 1: LAUNCH_LN(1, NPV); break;   \
+    case 2: LAUNCH_LN(2, NPV); break;   \
+    case 3: LAUNCH_LN(3, NPV); break;   \
+    default: LAUNCH_LN(4, NPV); break;  \
   }
+  if (np == 1) {
+    LAUNCH_LN_NC(1)
+  } else if constexpr (std::is_same<T, bf16_t>::value) {
+    if (np == 2) LAUNCH_LN_NC(2)
+    else if (np == 4) LAUNCH_LN_NC(4)
+    else if (np == 6) LAUNCH_LN_NC(6)
+    else return hipErrorInvalidValue;
+  } else {
+    return hipErrorInvalidValue;
+  }
+#undef LAUNCH_LN_NC
 #undef LAUNCH_LN
   return hipGetLastError();
 }
 
-int ln_bwd_blocks(int rows) { return (rows + LN_BWD_RPB - 1) / LN_BWD_RPB; }
+// 32 rows per work-group (two row pairs per wavefront and eight loads of them
+// in flight hide HBM latency); fewer when that leaves less than one work-group
+// per CU: 2048 rows of 768 took 15.5 us in 64 work-groups.
+int ln_bwd_rpb(int rows) { return rows > 4096 ? 32 : rows > 2048 ? 16 : rows > 1024 ? 8 : 4; }
+int ln_bwd_blocks(int rows) { return (rows + ln_bwd_rpb(rows) - 1) / ln_bwd_rpb(rows); }
+int ln_bwd_blocks_max(int rows) {
+  // 1024, 2048 and 4096 rows make 256 work-groups each
+  return rows <= 1024 ? ln_bwd_blocks(rows) : std::max(256, ln_bwd_blocks(rows));
+}
 
-hipError_t ln_bwd_bf16(const bf16_t* dy, const bf16_t* ahi, const bf16_t* alo, const bf16_t* b,
-                       const bf16_t* xhat, const float* rstd, const float* gamma, bf16_t* dz,
-                       bf16_t* dzlo, float* part, int rows, int h, hipStream_t st) {
+hipError_t ln_bwd_bf16(const GradIn& in, const bf16_t* xhat, const float* rstd, const float* gamma,
+                       bf16_t* dz, bf16_t* dzlo, float* part, int rows, int h, hipStream_t st) {
   if (h % 64 != 0 || h > 2048) return hipErrorInvalidValue;
-  const bool sum3 = ahi && alo && b;
-  if ((dy == nullptr) == !sum3) return hipErrorInvalidValue;
+  if (!in.bf && (!in.hi || !in.lo || (!in.b && !in.pf))) return hipErrorInvalidValue;
   if (rows <= 0) return hipSuccess;
   const int nc = (h / 8 + 63) / 64;
   dim3 grid(ln_bwd_blocks(rows)), blk(256);
   size_t sh = (size_t)4 * 3 * h * sizeof(float);
-  const int rpb = LN_BWD_RPB;
-#define LAUNCH_LNB(NCV, S3)                                                                   \
-  hipLaunchKernelGGL((ln_bwd_bf16_kernel<NCV, S3>), grid, blk, sh, st, dy, ahi, alo, b, xhat,  \
-                     rstd, gamma, dz, dzlo, part, rows, h, rpb)
-  if (!sum3) {
-    switch (nc) {
-      case 1: LAUNCH_LNB(1, false); break;
-      case 2: LAUNCH_LNB(2, false); break;
-      case 3: LAUNCH_LNB(3, false); break;
-      default: LAUNCH_LNB(4, false); break;
-    }
-  } else {
-    switch (nc) {
-      case 1: LAUNCH_LNB(1, true); break;
-      case 2: LAUNCH_LNB(2, true); break;
-      case 3: LAUNCH_LNB(3, true); break;
-      default: LAUNCH_LNB(4, true); break;
-    }
+  const int rpb = ln_bwd_rpb(rows);
+#define LAUNCH_LNB(NCV, NPV)                                                                   \
+  hipLaunchKernelGGL((ln_bwd_bf16_kernel<NCV, NPV>), grid, blk, sh, st, in, xhat, rstd, gamma, \
+                     dz, dzlo, part, rows, h, rpb)
+#define LAUNCH_LNB_NC(NPV)               \
+  switch (nc) {                          \
+    case 1: LAUNCH_LNB(1, NPV); break;   \
+    case 2: LAUNCH_LNB(2, NPV); break;   \
+    case 3: LAUNCH_LNB(3, NPV); break;   \
+    default: LAUNCH_LNB(4, NPV); break;  \
   }
+  if (in.bf) LAUNCH_LNB_NC(-1)
+  else if (in.b) LAUNCH_LNB_NC(0)
+  else if (in.np == 2) LAUNCH_LNB_NC(2)
+  else if (in.np == 4) LAUNCH_LNB_NC(4)
+  else if (in.np == 6) LAUNCH_LNB_NC(6)
+  else return hipErrorInvalidValue;
+#undef LAUNCH_LNB_NC
 #undef LAUNCH_LNB
   return hipGetLastError();
 }
 
-hipError_t add3_bf16(const bf16_t* ahi, const bf16_t* alo, const bf16_t* b, bf16_t* out,
-                     int64_t n, hipStream_t st) {
+namespace {
+template <typename T>
+hipError_t grad_out(const GradIn& in, T* out, int64_t n, hipStream_t st) {
   if (n % 8 != 0) return hipErrorInvalidValue;
-  const int64_t n8 = n / 8;
-  if (n8 == 0) return hipSuccess;
-  hipLaunchKernelGGL(add3_bf16_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, st, ahi,
-                     alo, b, out, n8);
+  if (n == 0) return hipSuccess;
+  const dim3 grid((unsigned)((n / 8 + 255) / 256)), blk(256);
+  if (in.bf) hipLaunchKernelGGL((grad_kernel<T, -1>), grid, blk, 0, st, in, out, n);
+  else if (in.b) hipLaunchKernelGGL((grad_kernel<T, 0>), grid, blk, 0, st, in, out, n);
+  else if (in.np == 2) hipLaunchKernelGGL((grad_kernel<T, 2>), grid, blk, 0, st, in, out, n);
+  else if (in.np == 4) hipLaunchKernelGGL((grad_kernel<T, 4>), grid, blk, 0, st, in, out, n);
+  else if (in.np == 6) hipLaunchKernelGGL((grad_kernel<T, 6>), grid, blk, 0, st, in, out, n);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+}  // namespace
+hipError_t grad_bf16(const GradIn& in, bf16_t* out, int64_t n, hipStream_t st) {
+  return grad_out(in, out, n, st);
+}
+hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st) {
+  return grad_out(in, out, n, st);
+}
+
+hipError_t stage_prep(const void* x, void* X, int64_t nx, const uint8_t* key_mask, uint8_t* mask,
+                      int B, int S, int* kext, hipStream_t st) {
+  const int64_t blocks = B + (nx / 16 + 1023) / 1024;
+  if (nx % 16 != 0 || blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(stage_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const u32x4_t*)x,
+                     (u32x4_t*)X, nx / 16, key_mask, mask, B, S, kext);
   return hipGetLastError();
 }
 
@@ -547,7 +643,7 @@ hipError_t ln_bwd_f32(const float* dy, const float* xhat, const float* rstd, con
   const int nc = (h / 8 + 63) / 64;
   dim3 grid(ln_bwd_blocks(rows)), blk(256);
   size_t sh = (size_t)4 * 3 * h * sizeof(float);
-  const int rpb = LN_BWD_RPB;
+  const int rpb = ln_bwd_rpb(rows);
 #define LAUNCH_LNB(NCV)                                                                        \
   hipLaunchKernelGGL((ln_bwd_kernel<float, NCV>), grid, blk, sh, st, dy, xhat, rstd, gamma, dz, \
                      part, rows, h, rpb)
@@ -590,10 +686,10 @@ hipError_t softmax_bwd(const float* dP, const T* P, T* dS, int BH, int S, int ld
   return hipGetLastError();
 }
 
-template hipError_t add_ln_fwd<float, float>(const float*, const float*, const float*, const float*,
+template hipError_t add_ln_fwd<float, float>(const float*, int, const float*, const float*, const float*,
                                              const float*, const float*, float*, float*, float*,
                                              float*, int, int, hipStream_t);
-template hipError_t add_ln_fwd<bf16_t, float>(const float*, const float*, const bf16_t*,
+template hipError_t add_ln_fwd<bf16_t, float>(const float*, int, const float*, const bf16_t*,
                                               const bf16_t*, const float*, const float*, bf16_t*,
                                               bf16_t*, bf16_t*, float*, int, int, hipStream_t);
 template hipError_t col_partial<float>(const float*, int, int, float*, int, hipStream_t);

@@ -84,19 +84,6 @@ __global__ void fill_kernel(float* out, int64_t n, float v) {
   if (i < n) out[i] = v;
 }
 
-// out = x (fp32; fp32 stages), or bf (bf16), or (hi + lo) + b (bf16), as fp32.
-__global__ void grad_record_kernel(const float* x, const bf16_t* bf, const bf16_t* hi,
-                                   const bf16_t* lo, const bf16_t* b, float* out, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  out[i] = x ? x[i] : bf ? bf2f(bf[i]) : (bf2f(hi[i]) + bf2f(lo[i])) + bf2f(b[i]);
-}
-
-__global__ void ones_u8_kernel(uint8_t* out, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = 1;
-}
-
 bool is_matrix(int which) {
   return which == STAGE_W_QKV || which == STAGE_W_O || which == STAGE_W_1 || which == STAGE_W_2;
 }
@@ -157,7 +144,7 @@ struct stage {
   std::vector<void*> act_allocs;
   std::vector<Saved> saved;
   uint8_t* mask = nullptr;
-  float* tmp = nullptr;     // [T, h] fp32 GEMM output before LayerNorm
+  float* tmp = nullptr;     // [T, h] fp32 GEMM output before LayerNorm, or its partials
   void* h1lo = nullptr;     // [T, h] H1's bf16 rounding residual (bf16 stages)
   float* scores = nullptr;  // [B*H, S, S] fp32 (scores, then dP; fp32 stages)
   int* kext = nullptr;      // [B] key extent of each sequence
@@ -394,9 +381,9 @@ stage_status grow_splitk(stage_t* s, size_t need) {
 // launches are what a layer's time is made of.
 bool f32_fused_b1(int64_t T) { return (T + 31) / 32 <= COL_PARTS; }
 
-// Rows of the db_1 column partial sums for T tokens (bf16: one per 128 rows).
+// Most rows of db_1 column partial sums a batch of up to T tokens needs.
 int64_t colpart_ffn_rows(const stage_t* s, int64_t T) {
-  if (s->dtype == STAGE_BF16) return (T + 127) / 128;
+  if (s->dtype == STAGE_BF16) return gemm_colpart_max(T);
   return f32_fused_b1(T) ? (T + 31) / 32 : COL_PARTS;
 }
 
@@ -433,7 +420,13 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
          (st = A(&v.xhat2, T * h * e)) || (st = A((void**)&v.rstd2, T * 4))))
       return st;
   }
-  if ((st = A((void**)&s->mask, T)) || (st = A((void**)&s->tmp, T * h * 4)) ||
+  // fp32 outputs that feed a LayerNorm (bf16 stages, few tokens: as up to
+  // GEMM_SPLIT_MAX partials)
+  const int64_t tmp_elems =
+      s->dtype == STAGE_BF16
+          ? std::max<int64_t>(T * h, std::min<int64_t>(GEMM_SPLIT_MAX * T * h, GEMM_SPLIT_ELEMS))
+          : T * h;
+  if ((st = A((void**)&s->mask, T)) || (st = A((void**)&s->tmp, tmp_elems * 4)) ||
       (st = A(&s->h1lo, T * h * e)) ||
       (st = A((void**)&s->scores, BSS * 4)) || (st = A(&s->dS, BSS * e)) ||
       (st = A((void**)&s->kext, (size_t)B * 4)) || (st = A((void**)&s->dsum, BHS * 4)) ||
@@ -448,7 +441,7 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
                                (st = A(&s->prod, T * h * e))))
     return st;
   const int64_t nqb = ((int64_t)S + 31) / 32;
-  const int64_t ln_part = (int64_t)ln_bwd_blocks((int)T) * 3 * h;
+  const int64_t ln_part = (int64_t)ln_bwd_blocks_max((int)T) * 3 * h;
   if ((st = A((void**)&s->colpart_ffn, colpart_ffn_rows(s, T) * f * 4)) ||
       (st = A((void**)&s->colpart_qkv, (int64_t)B * nqb * 3 * h * 4)) ||
       (st = A((void**)&s->part, ln_part * 4)) || (st = A((void**)&s->part2, ln_part * 4)))
@@ -469,19 +462,26 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
 // ---------------------------------------------------------------------------
 // Typed launch helpers
 // ---------------------------------------------------------------------------
-template <typename T> struct Gemm;
-template <> struct Gemm<bf16_t> {
-  static hipError_t run(const GemmArgs& g, bool ak, bool bk, GemmEpi epi, bool out_f32, int batch,
-                        hipStream_t st) {
-    return gemm_bf16(g, ak, bk, epi, out_f32, batch, st);
-  }
-};
-template <> struct Gemm<float> {
-  static hipError_t run(const GemmArgs& g, bool ak, bool bk, GemmEpi epi, bool, int batch,
-                        hipStream_t st) {
-    return gemm_f32(g, ak, bk, epi, batch, st);
-  }
-};
+// A @ B^T-shaped product of the forward (both operands k-major).
+hipError_t gemm_fwd(const GemmArgs& g, GemmEpi epi, bf16_t*, hipStream_t st) {
+  return gemm_bf16(g, true, epi, st);
+}
+hipError_t gemm_fwd(const GemmArgs& g, GemmEpi epi, float*, hipStream_t st) {
+  return gemm_f32(g, true, true, epi, 1, st);
+}
+// The same for a product that feeds a LayerNorm, in fp32 (C: s->tmp); *np
+// receives the number of partials it is left in (bf16 stages).
+hipError_t gemm_fwd_ln(GemmArgs g, int* np, bf16_t*, hipStream_t st) {
+  const GemmPlan p = gemm_bf16_plan(g.M, g.N, g.K, true, EPI_PARTIAL, true);
+  g = gemm_split(g, p.ks);
+  g.tile = p.tile;
+  *np = g.ksplit;
+  return gemm_bf16(g, true, EPI_PARTIAL, st);
+}
+hipError_t gemm_fwd_ln(const GemmArgs& g, int* np, float*, hipStream_t st) {
+  *np = 1;
+  return gemm_f32(g, true, true, EPI_STORE, 1, st);
+}
 
 // A weight gradient dW[M, N] = dY^T X over the stage's tokens whose launch
 // is deferred to the layer's group launch.
@@ -508,18 +508,24 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const ColJob* 
     Ms[q] = jobs[q].M;
     Ns[q] = jobs[q].N;
   }
-  const int slots = wgrad_group_slots(Ms, Ns, n, Tn);
-  if (slots < 1) return fail(s, STAGE_EINVAL, "weight-gradient group: invalid sizes");
+  const int plan = n ? wgrad_plan(Ms, Ns, n, Tn) : 0;
+  const int slots = n ? wgrad_group_slots(Ms, Ns, n, Tn) : 0;
+  if (slots < 0) return fail(s, STAGE_EINVAL, "weight-gradient group: invalid sizes");
   size_t off = 0;
   for (int q = 0; q < n; ++q) {
     const WgradJob& j = jobs[q];
     gs[q] = gemm_args(j.dy, j.ld_dy, j.x, j.ld_x, s->splitk + off, j.N, j.M, j.N, Tn);
-    gs[q].tile = 1;
     off += (size_t)slots * j.M * j.N;
     outs[q] = j.out;
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
-  SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
+  if (plan != 0) {
+    // whole gradients, then the column reductions
+    SITE(WGRAD_GROUP, gemm_mid_wgrad(gs, outs, n, plan, s->stream));
+    SITE(WGRAD_GROUP_RED, wgrad_group_reduce(nullptr, nullptr, 0, cols, ncols, s->stream));
+    return STAGE_OK;
+  }
+  if (n > 0) SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
   SITE(WGRAD_GROUP_RED, wgrad_group_reduce(gs, outs, n, cols, ncols, s->stream));
   return STAGE_OK;
 }
@@ -561,18 +567,24 @@ AttnArgs attn_args(stage_t* s, const bf16_t* qkv, bf16_t* out, float* lse) {
 }
 
 template <typename T>
-stage_status forward_impl(stage_t* s, const T* x, T* y) {
+stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y) {
   const int B = s->B, S = s->S, h = s->h, H = s->H, f = s->f;
   const int Tn = B * S;
   const int BH = B * H;
   hipStream_t st = s->stream;
   const float scale = 1.0f / sqrtf((float)HEAD_DIM);
   // The stage input is X of local layer 0, or its H1 when that layer holds
-  // only its feed-forward half.
-  HIPCK(hipMemcpyAsync(s->ffn_first ? s->saved[0].H1 : s->saved[0].X, x, (size_t)Tn * h * sizeof(T),
-                       hipMemcpyDeviceToDevice, st));
-  if (std::is_same<T, bf16_t>::value && (s->L > 1 || !s->ffn_first))
-    SITE(KEXT, key_extent(s->mask, B, S, s->kext, st));
+  // only its feed-forward half.  One launch copies it and the key mask and
+  // finds the key extents; an input that is not 16-byte aligned is copied by
+  // the runtime.
+  {
+    void* X = s->ffn_first ? s->saved[0].H1 : s->saved[0].X;
+    const int64_t nx = (int64_t)Tn * h * sizeof(T);
+    const bool aligned = ((uintptr_t)x & 15) == 0;
+    int* kext = std::is_same<T, bf16_t>::value && (s->L > 1 || !s->ffn_first) ? s->kext : nullptr;
+    if (!aligned) HIPCK(hipMemcpyAsync(X, x, (size_t)nx, hipMemcpyDeviceToDevice, st));
+    SITE(KEXT, stage_prep(x, X, aligned ? nx : 0, key_mask, s->mask, B, S, kext, st));
+  }
   for (int l = 0; l < s->L; ++l) {
     Saved& v = s->saved[l];
     auto& p = s->param[l];
@@ -589,7 +601,7 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
       {
         GemmArgs g = gemm_args(X, h, p[STAGE_W_QKV], h, QKV, 3 * h, Tn, 3 * h, h);
         g.bias = (const float*)p[STAGE_B_QKV];
-        SITE(QKV_FWD, Gemm<T>::run(g, true, true, EPI_STORE, false, 1, st));
+        SITE(QKV_FWD, gemm_fwd(g, EPI_STORE, QKV, st));
       }
       if constexpr (std::is_same<T, bf16_t>::value) {
         // Fused attention: softmax(Q K^T / 8) V per (batch, head), P stays on chip.
@@ -605,7 +617,7 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
         g.sA2 = g.sB2 = HEAD_DIM;
         g.sC1 = (int64_t)H * S * S;
         g.sC2 = (int64_t)S * S;
-        SITE(SCORES_FWD, Gemm<T>::run(g, true, true, EPI_STORE, true, BH, st));
+        SITE(SCORES_FWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
       }
       SITE(SOFTMAX_FWD, softmax_fwd<T>(s->scores, s->mask, (T*)v.P, BH, H, S, S, scale, st));
       // C[b, :, j] = P_bj V_bj
@@ -618,19 +630,20 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
         g.sB2 = HEAD_DIM;
         g.sC1 = (int64_t)S * h;
         g.sC2 = HEAD_DIM;
-        SITE(CTX_FWD, Gemm<T>::run(g, true, false, EPI_STORE, false, BH, st));
+        SITE(CTX_FWD, gemm_f32(g, true, false, EPI_STORE, BH, st));
       }
       }
       // tmp = C W_o^T (fp32);  H1 = LN(X + tmp + b_o)
+      int np = 1;
       {
         GemmArgs g = gemm_args(v.C, h, p[STAGE_W_O], h, s->tmp, h, Tn, h, h);
-        SITE(OUT_FWD, Gemm<T>::run(g, true, true, EPI_STORE, true, 1, st));
+        SITE(OUT_FWD, gemm_fwd_ln(g, &np, (T*)nullptr, st));
       }
       // The last layer of a stage that ends at an attention half writes H1
       // straight to the stage output.
       const bool to_out = !has_ffn(s, l);
       if (to_out) h1_lo = nullptr;
-      SITE(LN1_FWD, add_ln_fwd<T, float>(s->tmp, (const float*)p[STAGE_B_O], X, nullptr,
+      SITE(LN1_FWD, add_ln_fwd<T, float>(s->tmp, np, (const float*)p[STAGE_B_O], X, nullptr,
                                          (const float*)p[STAGE_G1], (const float*)p[STAGE_BE1],
                                          to_out ? y : (T*)v.H1, h1_lo, (T*)v.xhat1, v.rstd1, Tn,
                                          h, st));
@@ -641,15 +654,16 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
       GemmArgs g = gemm_args(v.H1, h, p[STAGE_W_1], h, v.G, f, Tn, f, h);
       g.bias = (const float*)p[STAGE_B_1];
       g.C2 = v.Gd;
-      SITE(FFN1_FWD, Gemm<T>::run(g, true, true, EPI_GELU, false, 1, st));
+      SITE(FFN1_FWD, gemm_fwd(g, EPI_GELU, (T*)nullptr, st));
     }
     // tmp = G W_2^T (fp32);  Y = LN(H1 + tmp + b_2)
+    int np2 = 1;
     {
       GemmArgs g = gemm_args(v.G, f, p[STAGE_W_2], f, s->tmp, h, Tn, h, f);
-      SITE(FFN2_FWD, Gemm<T>::run(g, true, true, EPI_STORE, true, 1, st));
+      SITE(FFN2_FWD, gemm_fwd_ln(g, &np2, (T*)nullptr, st));
     }
     T* Y = (l + 1 < s->L) ? (T*)s->saved[l + 1].X : y;
-    SITE(LN2_FWD, add_ln_fwd<T, float>(s->tmp, (const float*)p[STAGE_B_2], (const T*)v.H1,
+    SITE(LN2_FWD, add_ln_fwd<T, float>(s->tmp, np2, (const float*)p[STAGE_B_2], (const T*)v.H1,
                                        h1_lo, (const float*)p[STAGE_G2],
                                        (const float*)p[STAGE_BE2], Y, nullptr, (T*)v.xhat2,
                                        v.rstd2, Tn, h, st));
@@ -657,16 +671,8 @@ stage_status forward_impl(stage_t* s, const T* x, T* y) {
   return STAGE_OK;
 }
 
-// Records the gradient reaching layer l's output when recording is on.
-stage_status record_grad(stage_t* s, int l, const float* x, const bf16_t* bf, const bf16_t* hi,
-                         const bf16_t* lo, const bf16_t* b) {
-  if (!s->record_grads || (int)s->rec.size() != s->L) return STAGE_OK;
-  const int64_t n = (int64_t)s->B * s->S * s->h;
-  hipLaunchKernelGGL(grad_record_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                     s->stream, x, bf, hi, lo, b, s->rec[l], n);
-  HIPCK(hipGetLastError());
-  return STAGE_OK;
-}
+// Whether the gradient reaching each layer's output is recorded.
+bool recording(const stage_t* s) { return s->record_grads && (int)s->rec.size() == s->L; }
 
 // Backward of an fp32 stage: every tensor in fp32, the materialised attention
 // path; the four weight gradients of a layer run in one launch at its end,
@@ -693,7 +699,8 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
     T* dQKV = (T*)s->dQKV;
     const T* QKV = (const T*)v.QKV;
     const bool attn = has_attn(s, l), ffn = has_ffn(s, l);
-    if ((r = record_grad(s, l, dYcur, nullptr, nullptr, nullptr, nullptr))) return r;
+    if (recording(s))
+      HIPCK(hipMemcpyAsync(s->rec[l], dYcur, (size_t)Tn * h * 4, hipMemcpyDeviceToDevice, st));
     WgradJob wjobs[GEMM_GROUP_MAX];
     int nw = 0;
     ColJob cjobs[COLJOB_MAX];
@@ -808,36 +815,45 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
   return STAGE_OK;
 }
 
-// Gradient reaching a LayerNorm of a bf16 stage: the caller's bf16 tensor
-// (at the stage's top, or below a stage boundary), or the fp32 sum of the
-// residual branch, carried as its bf16 rounding hi plus the rounding
-// residual lo (about 16 significant bits), and the data-gradient GEMM's
-// bf16 product b.  The backward residual stream keeps that precision inside
-// a stage: rounding it to bf16 at each of a layer's two residual additions
-// is what the gradient error of a deep stage grows from (the product's own
-// rounding is not: it enters the stream once).
-struct GradIn {
-  const bf16_t* bf;
-  const bf16_t* hi;
-  const bf16_t* lo;
-  const bf16_t* b;
-};
+// A data-gradient product dX = dY W (W as stored: n-major B operand) that
+// joins the residual stream hi + lo of a bf16 stage: in bf16, or, when that
+// leaves too few work-groups, as fp32 partials in s->tmp (unused by the
+// backward otherwise).  The stream itself is never rounded to bf16 inside a
+// stage: rounding it at each of a layer's two residual additions is what the
+// gradient error of a deep stage grows from (the product's own rounding is
+// not: it enters the stream once).
+stage_status dgrad_joining(stage_t* s, int site, GemmArgs g, const bf16_t* hi, const bf16_t* lo,
+                           GradIn* out) {
+  const GemmPlan split = gemm_bf16_plan(g.M, g.N, g.K, false, EPI_PARTIAL, true);
+  if (split.ks > 1) {
+    g = gemm_split(g, split.ks);
+    g.tile = split.tile;
+    g.C = s->tmp;
+    SITE_I(site, gemm_bf16(g, false, EPI_PARTIAL, s->stream));
+    *out = GradIn{nullptr, hi, lo, nullptr, s->tmp, g.ksplit};
+  } else {
+    g.C = s->prod;
+    SITE_I(site, gemm_bf16(g, false, EPI_STORE, s->stream));
+    *out = GradIn{nullptr, hi, lo, (const bf16_t*)s->prod, nullptr, 0};
+  }
+  return STAGE_OK;
+}
 
 // Backward of a bf16 stage.  Per layer: the LayerNorm backward kernels take
-// GradIn and write dZ in bf16 (GEMM operand) and fp32 (residual branch);
-// the two data-gradient GEMMs whose output feeds a residual addition store
-// their product in bf16 (the addition happens in the next LayerNorm
-// backward); the data-gradient GEMMs read the weights as stored (n-major B
-// operand, transposing LDS reads); the four weight gradients and
-// the bias / LayerNorm column reductions run in one group launch and one
-// reduction launch at the end of the layer.
+// a GradIn and write dZ in bf16 (GEMM operand) with its rounding residual
+// (residual branch); the two data-gradient GEMMs whose output feeds a
+// residual addition leave their product for the next LayerNorm backward; the
+// data-gradient GEMMs read the weights as stored (n-major B operand,
+// transposing LDS reads); the four weight gradients and the bias / LayerNorm
+// column reductions run at the end of the layer.
 stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
   using T = bf16_t;
   const int B = s->B, S = s->S, h = s->h, f = s->f;
   const int Tn = B * S;
+  const int64_t n = (int64_t)Tn * h;
   hipStream_t st = s->stream;
   stage_status r;
-  GradIn gin{dy, nullptr, nullptr, nullptr};
+  GradIn gin{dy, nullptr, nullptr, nullptr, nullptr, 0};
   for (int l = s->L - 1; l >= 0; --l) {
     Saved& v = s->saved[l];
     auto& p = s->param[l];
@@ -848,7 +864,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
     T* dC = (T*)s->dC;
     T* dQKV = (T*)s->dQKV;
     const bool attn = has_attn(s, l), ffn = has_ffn(s, l);
-    if ((r = record_grad(s, l, nullptr, gin.bf, gin.hi, gin.lo, gin.b))) return r;
+    if (recording(s)) HIPCK(grad_f32(gin, s->rec[l], n, st));
     WgradJob wjobs[GEMM_GROUP_MAX];
     int nw = 0;
     ColJob cjobs[COLJOB_MAX];
@@ -857,10 +873,9 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
     // when the stage ends at this layer's attention half.
     GradIn gh1 = gin;
     if (ffn) {
-      // Y = LN(Z2): dZ2 (bf16 and fp32), dgamma2, dbeta2, db_2 = sum_t dZ2
-      SITE(LN2_BWD, ln_bwd_bf16(gin.bf, gin.hi, gin.lo, gin.b, (const T*)v.xhat2, v.rstd2,
-                                (const float*)p[STAGE_G2], dZ2, (T*)s->dz2lo, s->part2, Tn, h,
-                                st));
+      // Y = LN(Z2): dZ2 and its residual, dgamma2, dbeta2, db_2 = sum_t dZ2
+      SITE(LN2_BWD, ln_bwd_bf16(gin, (const T*)v.xhat2, v.rstd2, (const float*)p[STAGE_G2], dZ2,
+                                (T*)s->dz2lo, s->part2, Tn, h, st));
       cjobs[nc++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G2], gr[STAGE_BE2], gr[STAGE_B_2], nullptr}};
       // dW_2 = dZ2^T G
@@ -870,41 +885,33 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
         GemmArgs g = gemm_args(dZ2, h, p[STAGE_W_2], f, dU, f, Tn, f, h);
         g.aux = v.Gd;
         g.ldaux = f;
-        g.tile = 1;
+        g.tile = gemm_bf16_plan(Tn, f, h, false, EPI_MUL, false).tile;
         g.colpart = s->colpart_ffn;
-        SITE(FFN2_DGRAD, gemm_bf16(g, true, false, EPI_MUL, false, 1, st));
+        SITE(FFN2_DGRAD, gemm_bf16(g, false, EPI_MUL, st));
+        const int rows = gemm_colpart_rows(g.tile);
+        cjobs[nc++] = ColJob{s->colpart_ffn, (Tn + rows - 1) / rows, 1, f,
+                             {gr[STAGE_B_1], nullptr, nullptr, nullptr}};
       }
-      cjobs[nc++] = ColJob{s->colpart_ffn, (Tn + 127) / 128, 1, f,
-                           {gr[STAGE_B_1], nullptr, nullptr, nullptr}};
       // dW_1 = dU^T H1
       wjobs[nw++] = {dU, f, v.H1, h, f, h, gr[STAGE_W_1]};
-      // dH1 = dZ2 + dU W_1: the product in bf16, the sum in the first
-      // LayerNorm's backward (or here, rounded, when this half is the
-      // stage's first unit and dH1 is its dx)
-      {
-        GemmArgs g = gemm_args(dU, f, p[STAGE_W_1], h, s->prod, h, Tn, h, f);
-        SITE(FFN1_DGRAD, gemm_bf16(g, true, false, EPI_STORE, false, 1, st));
-      }
-      if (attn) {
-        gh1 = GradIn{nullptr, dZ2, (const T*)s->dz2lo, (const T*)s->prod};
-      } else {
-        HIPCK(add3_bf16(dZ2, (const T*)s->dz2lo, (const T*)s->prod, dx, (int64_t)Tn * h, st));
-      }
+      // dH1 = dZ2 + dU W_1: summed in the first LayerNorm's backward, or here,
+      // rounded, when this half is the stage's first unit and dH1 is its dx
+      if ((r = dgrad_joining(s, SITE_FFN1_DGRAD, gemm_args(dU, f, p[STAGE_W_1], h, nullptr, h, Tn, h, f),
+                             dZ2, (const T*)s->dz2lo, &gh1)))
+        return r;
+      if (!attn) HIPCK(grad_bf16(gh1, dx, n, st));
     }  // feed-forward half
     if (attn) {
-      // H1 = LN(Z1): dZ1 (bf16 and fp32), dgamma1, dbeta1, db_o
-      SITE(LN1_BWD, ln_bwd_bf16(gh1.bf, gh1.hi, gh1.lo, gh1.b, (const T*)v.xhat1, v.rstd1,
-                                (const float*)p[STAGE_G1], dZ1, (T*)s->dz1lo, s->part, Tn, h,
-                                st));
+      // H1 = LN(Z1): dZ1 and its residual, dgamma1, dbeta1, db_o
+      SITE(LN1_BWD, ln_bwd_bf16(gh1, (const T*)v.xhat1, v.rstd1, (const float*)p[STAGE_G1], dZ1,
+                                (T*)s->dz1lo, s->part, Tn, h, st));
       cjobs[nc++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G1], gr[STAGE_BE1], gr[STAGE_B_O], nullptr}};
       // dW_o = dZ1^T C
       wjobs[nw++] = {dZ1, h, v.C, h, h, h, gr[STAGE_W_O]};
       // dC = dZ1 W_o
-      {
-        GemmArgs g = gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h);
-        SITE(OUT_DGRAD, gemm_bf16(g, true, false, EPI_STORE, false, 1, st));
-      }
+      SITE(OUT_DGRAD,
+           gemm_bf16(gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h), false, EPI_STORE, st));
       // Attention backward (recomputes P from the saved log-sum-exp): dQKV
       // and the column sums of db_qkv per 32-row block.
       AttnArgs aa = attn_args(s, (const T*)v.QKV, dQKV, v.lse);
@@ -918,20 +925,15 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
       // dW_qkv = dQKV^T X
       wjobs[nw++] = {dQKV, 3 * h, v.X, h, 3 * h, h, gr[STAGE_W_QKV]};
-      // dX = dZ1 + dQKV W_qkv: the product in bf16; the sum in the previous
-      // layer's second LayerNorm backward, or here, rounded, for the stage's dx
-      {
-        GemmArgs g = gemm_args(dQKV, 3 * h, p[STAGE_W_QKV], h, s->prod, h, Tn, h, 3 * h);
-        SITE(QKV_DGRAD, gemm_bf16(g, true, false, EPI_STORE, false, 1, st));
-      }
-      if (l > 0) {
-        gin = GradIn{nullptr, dZ1, (const T*)s->dz1lo, (const T*)s->prod};
-      } else {
-        HIPCK(add3_bf16(dZ1, (const T*)s->dz1lo, (const T*)s->prod, dx, (int64_t)Tn * h, st));
-      }
+      // dX = dZ1 + dQKV W_qkv: summed in the previous layer's second
+      // LayerNorm backward, or here, rounded, for the stage's dx
+      if ((r = dgrad_joining(s, SITE_QKV_DGRAD,
+                             gemm_args(dQKV, 3 * h, p[STAGE_W_QKV], h, nullptr, h, Tn, h, 3 * h), dZ1,
+                             (const T*)s->dz1lo, &gin)))
+        return r;
+      if (l == 0) HIPCK(grad_bf16(gin, dx, n, st));
     }
     if ((r = wgrad_group(s, wjobs, nw, cjobs, nc))) return r;
-    if (!attn) break;
   }
   return STAGE_OK;
 }
@@ -1123,15 +1125,8 @@ stage_status stage_forward(stage_t* s, const void* x, const uint8_t* key_mask, i
     s->have_ctx = true;
     return STAGE_OK;
   }
-  if (key_mask) {
-    HIPCK(hipMemcpyAsync(s->mask, key_mask, (size_t)T, hipMemcpyDeviceToDevice, s->stream));
-  } else {
-    hipLaunchKernelGGL(ones_u8_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s->stream,
-                       s->mask, T);
-    HIPCK(hipGetLastError());
-  }
-  st = s->dtype == STAGE_BF16 ? forward_impl<bf16_t>(s, (const bf16_t*)x, (bf16_t*)y)
-                              : forward_impl<float>(s, (const float*)x, (float*)y);
+  st = s->dtype == STAGE_BF16 ? forward_impl<bf16_t>(s, (const bf16_t*)x, key_mask, (bf16_t*)y)
+                              : forward_impl<float>(s, (const float*)x, key_mask, (float*)y);
   if (st) return st;
   s->have_ctx = true;
   return STAGE_OK;
