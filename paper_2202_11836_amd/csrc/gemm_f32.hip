@@ -511,17 +511,18 @@ hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmA
   return hipGetLastError();
 }
 
-int gemm_f32_wgrad_splits(int M, int N, int K) {
-  // Two work-groups of 64 x 64 per CU; k ranges of at least 256.
-  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  const int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / std::max<int64_t>(tiles, 1), K / 256));
+int gemm_f32_wgrad_splits(int h, int f, int K) {
+  // Two work-groups of 64 x 64 per CU over the layer's four gradients (h and f
+  // are multiples of 64); k ranges of at least 256.
+  const int64_t hb = h / 64, fb = f / 64, tiles = 4 * hb * hb + 2 * hb * fb;
+  const int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / tiles, K / 256));
   const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
   return (K + chunk - 1) / chunk;
 }
 
-hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
-                                int ncols, hipStream_t st) {
-  if (n < 0 || n > GEMM_GROUP_MAX || ncols < 0 || ncols > COLJOB_MAX) return hipErrorInvalidValue;
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
+                                const ColJob* cols, int ncols, hipStream_t st) {
+  if (ks < 1 || n < 0 || n > GEMM_GROUP_MAX || ncols < 0 || ncols > COLJOB_MAX) return hipErrorInvalidValue;
   WgradGroup w{};
   F32Reduce rd{};
   int64_t t64 = 0;
@@ -529,8 +530,8 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, con
     GemmArgs g = p[q];
     if (g.M < 1 || g.N < 1 || g.K < 1 || g.ldc != g.N || !vec_ok(g, false, false))
       return hipErrorInvalidValue;
-    g.ksplit = gemm_f32_wgrad_splits(g.M, g.N, g.K);
-    g.kchunk = ((g.K + g.ksplit - 1) / g.ksplit + 63) / 64 * 64;
+    g = gemm_split(g, ks);
+    if (g.ksplit != ks) return hipErrorInvalidValue;
     if (!fits(g)) return hipErrorInvalidValue;
     // one split writes the gradient itself
     if (g.ksplit == 1) g.C = out[q];

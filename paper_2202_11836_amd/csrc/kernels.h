@@ -155,13 +155,15 @@ hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
 // with its reduction, else a tile of gemm_mid_wgrad (no partials).
 int wgrad_plan(const int* M, const int* N, int n, int K);
 
-// The weight gradients of one fp32 layer (both operands m/n-major) in one
-// launch, and in a second one the fixed-order sums of the problems split over
-// K (p[q].C holds gemm_f32_wgrad_splits slots of M x N partials where that is
-// more than 1) and the column reductions.
-int gemm_f32_wgrad_splits(int M, int N, int K);
-hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
-                                int ncols, hipStream_t st);
+// Weight gradients of one fp32 layer (both operands m/n-major, equal K) in one
+// launch, and in a second one the fixed-order sums of their ks splits over K
+// (ks > 1: p[q].C holds ks slots of M x N partials) and the column reductions.
+// ks: gemm_f32_wgrad_splits of the whole layer (width h, feed-forward width
+// f), also when only one half of it is computed, so that a half-layer stage
+// sums in the same order as a whole one.
+int gemm_f32_wgrad_splits(int h, int f, int K);
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
+                                const ColJob* cols, int ncols, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Row kernels (one wavefront per row), T = float or bf16_t.

@@ -325,7 +325,7 @@ stage_status dev_alloc(stage_t* s, std::vector<void*>& list, void** p, size_t by
 // tokens need.  bf16 stages compute a layer's weight gradients in one group
 // launch (stream-K over all their tiles): room for all four gradients'
 // partials, or for the feed-forward or attention half of a partial layer.
-// fp32 stages: the partials of those of a layer's gradients that are split.
+// fp32 stages: the splits of a layer's four gradients.
 // The figure is
 // not monotone in T (the stream-K piece count per tile depends on how the
 // k-tiles of all tiles divide among the work-groups), so it is evaluated for
@@ -341,11 +341,8 @@ size_t splitk_need(const stage_t* s, int64_t T) {
                      (size_t)wgrad_group_slots(Ms, Ns, 2, K) * (size_t)(2 * h * f),
                      (size_t)wgrad_group_slots(Ms + 2, Ns + 2, 2, K) * (size_t)(4 * h * h)});
   } else {
-    const int64_t shapes[4][2] = {{3 * h, h}, {h, h}, {f, h}, {h, f}};
-    for (auto& mn : shapes) {
-      const int ks = gemm_f32_wgrad_splits((int)mn[0], (int)mn[1], (int)std::max<int64_t>(T, 1));
-      if (ks > 1) need += (size_t)ks * mn[0] * mn[1];
-    }
+    const int ks = gemm_f32_wgrad_splits((int)h, (int)f, (int)std::max<int64_t>(T, 1));
+    if (ks > 1) need = (size_t)ks * (size_t)(4 * h * h + 2 * h * f);
   }
   return need;
 }
@@ -536,16 +533,16 @@ stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const ColJ
   const int Tn = s->B * s->S;
   GemmArgs gs[GEMM_GROUP_MAX];
   float* outs[GEMM_GROUP_MAX];
+  const int ks = gemm_f32_wgrad_splits(s->h, s->f, Tn);
   size_t off = 0;
   for (int q = 0; q < n; ++q) {
     const WgradJob& j = jobs[q];
     gs[q] = gemm_args(j.dy, j.ld_dy, j.x, j.ld_x, s->splitk + off, j.N, j.M, j.N, Tn);
     outs[q] = j.out;
-    const int ks = gemm_f32_wgrad_splits(j.M, j.N, Tn);
     if (ks > 1) off += (size_t)ks * j.M * j.N;
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
-  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, cols, ncols, s->stream));
+  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, ks, cols, ncols, s->stream));
   return STAGE_OK;
 }
 
@@ -1170,7 +1167,13 @@ stage_status stage_backward_noalloc(stage_t* s, const void* dy, void* dx) {
   const int64_t nlnb = ln_bwd_blocks((int)T);
   const size_t need_splitk = splitk_need(s, T);
   const size_t n_part = (size_t)(nlnb * 3 * h);
-  const size_t n_cffn = (size_t)(colpart_ffn_rows(s, T) * f);
+  // (this batch's rows, not the most of any smaller one)
+  const int cffn_rows =
+      s->dtype == STAGE_BF16 && T > 0
+          ? gemm_colpart_rows(gemm_bf16_plan((int)T, s->f, s->h, false, EPI_MUL, false).tile)
+          : 0;
+  const size_t n_cffn =
+      (size_t)((cffn_rows ? (T + cffn_rows - 1) / cffn_rows : colpart_ffn_rows(s, T)) * f);
   const size_t n_cqkv = (size_t)((int64_t)s->B * ((s->S + 31) / 32) * 3 * h);
   size_t off = 0;
   auto take = [&](size_t elems) {
