@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "gemm_tile.h"
+#include "tail.h"
 
 namespace {
 
@@ -702,38 +703,13 @@ struct SkReduce {
   int tile0[GEMM_GROUP_MAX];
   int n;
   SkSeq seq;
-  // column reductions: job j owns blocks [cblk0[j], cblk0[j + 1]) after the
-  // split-K blocks, ceil(n / 16) per output vector
-  ColJob col[COLJOB_MAX];
-  int cblk0[COLJOB_MAX + 1];
-  int ncol;
+  TailJobs tail;  // four units per work-group, after the split-K blocks
 };
 
-__global__ __launch_bounds__(256) void wgrad_group_reduce_kernel(SkReduce rd) {
+__global__ __launch_bounds__(256, 8) void wgrad_group_reduce_kernel(SkReduce rd) {
   const int b = blockIdx.x;
-  if (b >= rd.blk0[rd.n]) {  // a column-reduction block (block-uniform branch)
-    __shared__ f32x4_t sm[64][4];
-    int j = 0;
-#pragma unroll
-    for (int k = 1; k < COLJOB_MAX; ++k)
-      if (k < rd.ncol && b >= rd.cblk0[k]) j = k;
-    ColJob cj;
-    switch (j) {
-      case 0: cj = rd.col[0]; break;
-      case 1: cj = rd.col[1]; break;
-      case 2: cj = rd.col[2]; break;
-      default: cj = rd.col[3]; break;
-    }
-    const int nx = (cj.n + 15) / 16, lb = b - rd.cblk0[j];
-    const int v = lb / nx;
-    float* o;
-    switch (v) {
-      case 0: o = cj.out[0]; break;
-      case 1: o = cj.out[1]; break;
-      case 2: o = cj.out[2]; break;
-      default: o = cj.out[3]; break;
-    }
-    colred_block(cj.part, cj.nblk, cj.nvec, cj.n, v, lb - v * nx, o, sm);
+  if (b >= rd.blk0[GEMM_GROUP_MAX]) {
+    tail_unit<4>(tail_arg(offsetof(SkReduce, tail)), (b - rd.blk0[GEMM_GROUP_MAX]) * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63);
     return;
   }
   int q = 0;
@@ -1025,12 +1001,12 @@ hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
-                              int ncols, hipStream_t st) {
+hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const TailJobs& tail,
+                              hipStream_t st) {
   GemmGroup gg{};
-  if ((n != 0 && (!group_table_of(p, n, gg) || !out)) || ncols < 0 || ncols > COLJOB_MAX || (ncols && !cols))
-    return hipErrorInvalidValue;
   SkReduce rd{};
+  rd.tail = tail;
+  if (!group_table_of(p, n, gg) || !out || !tail_prepare(rd.tail)) return hipErrorInvalidValue;
   rd.n = n;
   rd.seq = {gg.work, gg.tile0[n], gg.kt, gg.kf, group_grid()};
   int64_t blocks = 0;
@@ -1046,17 +1022,8 @@ hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   }
   for (int q = n; q <= GEMM_GROUP_MAX; ++q) rd.blk0[q] = (int)blocks;
-  rd.ncol = ncols;
-  for (int j = 0; j < ncols; ++j) {
-    const ColJob& c = cols[j];
-    if (c.nvec < 1 || c.nvec > 4 || c.n < 0 || c.n % 4 != 0 || c.nblk < 0 || !c.part)
-      return hipErrorInvalidValue;
-    rd.col[j] = c;
-    rd.cblk0[j] = (int)blocks;
-    blocks += (int64_t)((c.n + 15) / 16) * c.nvec;
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  }
-  for (int j = ncols; j <= COLJOB_MAX; ++j) rd.cblk0[j] = (int)blocks;
+  blocks += (rd.tail.units + 3) / 4;
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(wgrad_group_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, rd);
   return hipGetLastError();

@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "tail.h"
 
 namespace {
 
@@ -340,11 +341,12 @@ __global__ __launch_bounds__(256) void gemm_f32_attn_bwd_kernel(Attn3 a) {
 
 // A layer's weight gradients in one launch: work-group b serves problem q
 // with blk0[q] <= b < blk0[q + 1]; a problem's work-groups are its tiles times
-// its splits.
+// its splits.  The tail's units (one split only) follow, four per work-group.
 struct WgradGroup {
   GemmArgs p[GEMM_GROUP_MAX];
   int blk0[GEMM_GROUP_MAX + 1];
   int n;
+  TailJobs tail;
 };
 template <bool SMALL>
 __global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
@@ -352,6 +354,10 @@ __global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
   __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
   constexpr int R = Cfg<SMALL>::R;
   const int b = blockIdx.x;
+  if (b >= w.blk0[GEMM_GROUP_MAX]) {
+    tail_unit<8>(tail_arg(offsetof(WgradGroup, tail)), (b - w.blk0[GEMM_GROUP_MAX]) * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63);
+    return;
+  }
   int q = 0;
 #pragma unroll
   for (int k = 1; k < GEMM_GROUP_MAX; ++k)
@@ -372,8 +378,8 @@ __global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
   tile_f32<SMALL, Rg::NS, false, false, true, EPI_PARTIAL>(g, tm, tn, 0, zs, smem);
 }
 
-// out[q] = the fixed-order sum of problem q's splits; then the column
-// reductions, ceil(n / 16) work-groups per output vector.
+// out[q] = the fixed-order sum of problem q's splits; then the tail, four
+// units per work-group.
 struct F32Reduce {
   const float* part[GEMM_GROUP_MAX];
   float* out[GEMM_GROUP_MAX];
@@ -381,34 +387,12 @@ struct F32Reduce {
   int ks[GEMM_GROUP_MAX];
   int blk0[GEMM_GROUP_MAX + 1];
   int n;
-  ColJob col[COLJOB_MAX];
-  int cblk0[COLJOB_MAX + 1];
-  int ncol;
+  TailJobs tail;
 };
-__global__ __launch_bounds__(256) void gemm_f32_group_reduce_kernel(F32Reduce rd) {
-  __shared__ f32x4_t sm[64][4];
+__global__ __launch_bounds__(256, 8) void gemm_f32_group_reduce_kernel(F32Reduce rd) {
   const int b = blockIdx.x;
   if (b >= rd.blk0[GEMM_GROUP_MAX]) {
-    int j = 0;
-#pragma unroll
-    for (int k = 1; k < COLJOB_MAX; ++k)
-      if (k < rd.ncol && b >= rd.cblk0[k]) j = k;
-    ColJob cj;
-    switch (j) {
-      case 0: cj = rd.col[0]; break;
-      case 1: cj = rd.col[1]; break;
-      case 2: cj = rd.col[2]; break;
-      default: cj = rd.col[3]; break;
-    }
-    const int nx = (cj.n + 15) / 16, lb = b - rd.cblk0[j], v = lb / nx;
-    float* o;
-    switch (v) {
-      case 0: o = cj.out[0]; break;
-      case 1: o = cj.out[1]; break;
-      case 2: o = cj.out[2]; break;
-      default: o = cj.out[3]; break;
-    }
-    colred_block(cj.part, cj.nblk, cj.nvec, cj.n, v, lb - v * nx, o, sm);
+    tail_unit<4>(tail_arg(offsetof(F32Reduce, tail)), (b - rd.blk0[GEMM_GROUP_MAX]) * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63);
     return;
   }
   int q = 0;
@@ -521,8 +505,8 @@ int gemm_f32_wgrad_splits(int h, int f, int K) {
 }
 
 hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
-                                const ColJob* cols, int ncols, hipStream_t st) {
-  if (ks < 1 || n < 0 || n > GEMM_GROUP_MAX || ncols < 0 || ncols > COLJOB_MAX) return hipErrorInvalidValue;
+                                const TailJobs& tail, hipStream_t st) {
+  if (ks < 1 || n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
   WgradGroup w{};
   F32Reduce rd{};
   int64_t t64 = 0;
@@ -558,25 +542,17 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int
   for (int q = n; q <= GEMM_GROUP_MAX; ++q) w.blk0[q] = (int)blocks;
   w.n = n;
   for (int j = rd.n; j <= GEMM_GROUP_MAX; ++j) rd.blk0[j] = (int)rblocks;
-  if (n > 0) {
-    if (small)
-      hipLaunchKernelGGL((gemm_f32_wgrad_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, st, w);
-    else
-      hipLaunchKernelGGL((gemm_f32_wgrad_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, st, w);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  rd.ncol = ncols;
-  for (int j = 0; j < ncols; ++j) {
-    const ColJob& c = cols[j];
-    if (c.nvec < 1 || c.nvec > 4 || c.n < 0 || c.n % 4 != 0 || c.nblk < 0 || !c.part)
-      return hipErrorInvalidValue;
-    rd.col[j] = c;
-    rd.cblk0[j] = (int)rblocks;
-    rblocks += (int64_t)((c.n + 15) / 16) * c.nvec;
-  }
-  for (int j = ncols; j <= COLJOB_MAX; ++j) rd.cblk0[j] = (int)rblocks;
-  if (rblocks == 0) return hipSuccess;
+  TailJobs& t = ks > 1 ? rd.tail : w.tail;
+  t = tail;
+  if (!tail_prepare(t)) return hipErrorInvalidValue;
+  (ks > 1 ? rblocks : blocks) += (t.units + 3) / 4;
+  if (blocks >= ((int64_t)1 << 31) || rblocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  if (small)
+    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+  else
+    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || ks == 1) return e;
   hipLaunchKernelGGL(gemm_f32_group_reduce_kernel, dim3((unsigned)rblocks), dim3(256), 0, st, rd);
   return hipGetLastError();
 }

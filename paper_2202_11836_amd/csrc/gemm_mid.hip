@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "gemm_tile.h"
+#include "tail.h"
 
 namespace {
 
@@ -324,16 +325,23 @@ __global__ __launch_bounds__((MidCfg<BM, BN>::THREADS), 2) void gemm_mid_kernel(
   mid_body<BM, BN, AK, BKM, EPI>(g, zs, tm, tn, smem);
 }
 
-// Weight gradients of one layer in one launch, each written whole.
+// Weight gradients of one layer in one launch, each written whole; the tail's
+// units, one per wavefront, in the work-groups after the tiles.
 struct MidGroup {
   GemmArgs g[GEMM_GROUP_MAX];
   int blk0[GEMM_GROUP_MAX + 1];
   int n;
+  TailJobs tail;
 };
 template <int BM, int BN>
 __global__ __launch_bounds__((MidCfg<BM, BN>::THREADS), 2) void gemm_mid_wgrad_kernel(MidGroup w) {
   __shared__ __attribute__((aligned(1024))) char smem[MidCfg<BM, BN>::LDS];
   const int b = blockIdx.x;
+  if (b >= w.blk0[GEMM_GROUP_MAX]) {
+    constexpr int W = MidCfg<BM, BN>::W;
+    tail_unit<8>(tail_arg(offsetof(MidGroup, tail)), (b - w.blk0[GEMM_GROUP_MAX]) * W + (int)(threadIdx.x >> 6), threadIdx.x & 63);
+    return;
+  }
   int q = 0;
 #pragma unroll
   for (int k = 1; k < GEMM_GROUP_MAX; ++k)
@@ -385,10 +393,13 @@ hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hip
   return hipErrorInvalidValue;
 }
 
-hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile, hipStream_t st) {
+hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
+                          const TailJobs& tail, hipStream_t st) {
   if (n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
   MidGroup w{};
   w.n = n;
+  w.tail = tail;
+  if (!tail_prepare(w.tail)) return hipErrorInvalidValue;
   const int bm = tile == GEMM_TILE_64x64 ? 64 : tile == GEMM_TILE_256x128 ? 256 : 128;
   const int bn = tile == GEMM_TILE_64x64 || tile == GEMM_TILE_128x64 ? 64 : 128;
   int64_t blocks = 0;
@@ -402,6 +413,9 @@ hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   }
   for (int q = n; q <= GEMM_GROUP_MAX; ++q) w.blk0[q] = (int)blocks;
+  const int waves = tile == GEMM_TILE_64x64 ? MidCfg<64, 64>::W : MidCfg<128, 128>::W;
+  blocks += (w.tail.units + waves - 1) / waves;
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
   switch (tile) {
     case GEMM_TILE_256x128:

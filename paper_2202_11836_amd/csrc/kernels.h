@@ -131,39 +131,63 @@ struct GemmGroup {
 // needs none, -1 for invalid sizes.
 int wgrad_group_slots(const int* M, const int* N, int n, int K);
 hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st);
-// A column reduction run with a group's reduction: out[v][c] = the sum over
-// the nblk partial rows b of part[(b * nvec + v) * n + c], v < nvec <= 4, in a
-// fixed order (null outputs are skipped).
+// A gradient on the backward residual stream of a bf16 stage: one bf16 tensor
+// bf, or the fp32 sum (hi + lo) + product of a residual branch carried as its
+// bf16 rounding and rounding residual and a data-gradient GEMM's product, in
+// bf16 (b) or as np fp32 partials pf, n elements apart (n: the tensor's size).
+struct GradIn {
+  const bf16_t* bf;
+  const bf16_t* hi;
+  const bf16_t* lo;
+  const bf16_t* b;
+  const float* pf;
+  int np;  // 2, 4 or 6 with pf
+};
+// Column reductions, and the rounding of a gradient, run with a layer's weight
+// gradients (tail.h): out[v][c] = the sum over the nblk partial rows b of
+// part[(b * nvec + v) * n + c], v < nvec <= 4, in a fixed order (null outputs
+// are skipped);  gout (may be null) = gin (a sum, not bf) rounded to bf16, gn
+// elements (a multiple of 8).  units, unit0: set by the launchers.
 struct ColJob {
   const float* part;
   int nblk, nvec, n;
   float* out[4];
 };
 constexpr int COLJOB_MAX = 4;
+struct TailJobs {
+  ColJob col[COLJOB_MAX];
+  int ncol;
+  int unit0[COLJOB_MAX + 1];
+  int units;
+  GradIn gin;
+  bf16_t* gout;
+  int64_t gn;
+};
 // out[q][m][n] = the sum over the pieces of (m, n)'s tile of slot j of
-// p[q].C, in k order (same p as the GEMM launch), and the ncols <=
-// COLJOB_MAX column reductions cols, in one launch (n = 0: only those).
-hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const ColJob* cols,
-                              int ncols, hipStream_t st);
+// p[q].C, in k order (same p as the GEMM launch), and the jobs of tail, in one
+// launch.
+hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const TailJobs& tail,
+                              hipStream_t st);
 
 // gemm_bf16 with one of the tiles of gemm_mid.hip.
 hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hipStream_t st);
-// n weight gradients (operands m/n-major, ldc = N), each written whole, in
-// one launch.
-hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile, hipStream_t st);
+// n weight gradients (operands m/n-major, ldc = N), each written whole, and
+// the jobs of tail, in one launch.
+hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
+                          const TailJobs& tail, hipStream_t st);
 // How a layer's weight gradients are computed: 0 = the stream-K group below
 // with its reduction, else a tile of gemm_mid_wgrad (no partials).
 int wgrad_plan(const int* M, const int* N, int n, int K);
 
-// Weight gradients of one fp32 layer (both operands m/n-major, equal K) in one
-// launch, and in a second one the fixed-order sums of their ks splits over K
-// (ks > 1: p[q].C holds ks slots of M x N partials) and the column reductions.
+// Weight gradients of one fp32 layer (both operands m/n-major, equal K) and the
+// jobs of tail, in one launch; with ks > 1 splits over K (p[q].C holds ks slots
+// of M x N partials) a second one has the splits' fixed-order sums and the tail.
 // ks: gemm_f32_wgrad_splits of the whole layer (width h, feed-forward width
 // f), also when only one half of it is computed, so that a half-layer stage
 // sums in the same order as a whole one.
 int gemm_f32_wgrad_splits(int h, int f, int K);
 hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
-                                const ColJob* cols, int ncols, hipStream_t st);
+                                const TailJobs& tail, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Row kernels (one wavefront per row), T = float or bf16_t.
@@ -188,25 +212,11 @@ int ln_bwd_blocks_max(int rows);  // the most any number of rows up to this one 
 hipError_t ln_bwd_f32(const float* dy, const float* xhat, const float* rstd, const float* gamma,
                       float* dz, float* part, int rows, int h, hipStream_t st);
 
-// A gradient on the backward residual stream of a bf16 stage: one bf16 tensor
-// bf, or the fp32 sum (hi + lo) + product of a residual branch carried as its
-// bf16 rounding and rounding residual and a data-gradient GEMM's product, in
-// bf16 (b) or as np fp32 partials pf, n elements apart (n: the tensor's size).
-struct GradIn {
-  const bf16_t* bf;
-  const bf16_t* hi;
-  const bf16_t* lo;
-  const bf16_t* b;
-  const float* pf;
-  int np;  // 2, 4 or 6 with pf
-};
 // bf16 stages: ln_bwd_f32 for such a gradient.  dz in bf16 and, when dzlo is
 // not null, dz's bf16 rounding residual.
 hipError_t ln_bwd_bf16(const GradIn& dy, const bf16_t* xhat, const float* rstd, const float* gamma,
                        bf16_t* dz, bf16_t* dzlo, float* part, int rows, int h, hipStream_t st);
-// out = the gradient (a sum, not bf) rounded to bf16, n elements (a multiple
-// of 8); or in fp32 (any form of it).
-hipError_t grad_bf16(const GradIn& in, bf16_t* out, int64_t n, hipStream_t st);
+// out = the gradient (any form of it) in fp32, n elements (a multiple of 8).
 hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st);
 
 // Start of a forward pass: X = x (nx bytes, a multiple of 16; both 16-byte

@@ -411,9 +411,9 @@ __global__ __launch_bounds__(256, (NC <= 2 ? 2 : 1)) void ln_bwd_bf16_kernel(
     P[e] = ((red[e] + red[3 * h + e]) + red[6 * h + e]) + red[9 * h + e];
 }
 
-// The gradient `in` at 8 elements per thread (n % 8 == 0), rounded to T.
-template <typename T, int NP>
-__global__ __launch_bounds__(256) void grad_kernel(GradIn in, T* __restrict__ out, int64_t n) {
+// The gradient `in` at 8 elements per thread (n % 8 == 0).
+template <int NP>
+__global__ __launch_bounds__(256) void grad_kernel(GradIn in, float* __restrict__ out, int64_t n) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
   if (i >= n) return;
   float v[8];
@@ -605,26 +605,17 @@ hipError_t ln_bwd_bf16(const GradIn& in, const bf16_t* xhat, const float* rstd, 
   return hipGetLastError();
 }
 
-namespace {
-template <typename T>
-hipError_t grad_out(const GradIn& in, T* out, int64_t n, hipStream_t st) {
+hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st) {
   if (n % 8 != 0) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
   const dim3 grid((unsigned)((n / 8 + 255) / 256)), blk(256);
-  if (in.bf) hipLaunchKernelGGL((grad_kernel<T, -1>), grid, blk, 0, st, in, out, n);
-  else if (in.b) hipLaunchKernelGGL((grad_kernel<T, 0>), grid, blk, 0, st, in, out, n);
-  else if (in.np == 2) hipLaunchKernelGGL((grad_kernel<T, 2>), grid, blk, 0, st, in, out, n);
-  else if (in.np == 4) hipLaunchKernelGGL((grad_kernel<T, 4>), grid, blk, 0, st, in, out, n);
-  else if (in.np == 6) hipLaunchKernelGGL((grad_kernel<T, 6>), grid, blk, 0, st, in, out, n);
+  if (in.bf) hipLaunchKernelGGL(grad_kernel<-1>, grid, blk, 0, st, in, out, n);
+  else if (in.b) hipLaunchKernelGGL(grad_kernel<0>, grid, blk, 0, st, in, out, n);
+  else if (in.np == 2) hipLaunchKernelGGL(grad_kernel<2>, grid, blk, 0, st, in, out, n);
+  else if (in.np == 4) hipLaunchKernelGGL(grad_kernel<4>, grid, blk, 0, st, in, out, n);
+  else if (in.np == 6) hipLaunchKernelGGL(grad_kernel<6>, grid, blk, 0, st, in, out, n);
   else return hipErrorInvalidValue;
   return hipGetLastError();
-}
-}  // namespace
-hipError_t grad_bf16(const GradIn& in, bf16_t* out, int64_t n, hipStream_t st) {
-  return grad_out(in, out, n, st);
-}
-hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st) {
-  return grad_out(in, out, n, st);
 }
 
 hipError_t stage_prep(const void* x, void* X, int64_t nx, const uint8_t* key_mask, uint8_t* mask,

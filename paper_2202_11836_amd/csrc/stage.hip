@@ -491,12 +491,12 @@ struct WgradJob {
   float* out;
 };
 
-// The queued weight gradients of one layer in one GEMM launch (stream-K
-// over all their tiles, fp32 partials side by side in the split-K buffer)
-// and one fixed-order reduction launch, which also runs the layer's queued
-// column reductions (bias, gamma and beta gradients).
-stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const ColJob* cols, int ncols) {
-  if (n == 0 && ncols == 0) return STAGE_OK;
+// The queued weight gradients of one layer, with the layer's queued column
+// reductions (bias, gamma and beta gradients) and, at the stage's first layer,
+// the rounding of its dx: one launch that writes whole gradients, or a
+// stream-K launch over all their tiles (fp32 partials side by side in the
+// split-K buffer) and one of fixed-order reductions.
+stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const TailJobs& tail) {
   const int Tn = s->B * s->S;
   GemmArgs gs[GEMM_GROUP_MAX];
   float* outs[GEMM_GROUP_MAX];
@@ -505,8 +505,8 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const ColJob* 
     Ms[q] = jobs[q].M;
     Ns[q] = jobs[q].N;
   }
-  const int plan = n ? wgrad_plan(Ms, Ns, n, Tn) : 0;
-  const int slots = n ? wgrad_group_slots(Ms, Ns, n, Tn) : 0;
+  const int plan = wgrad_plan(Ms, Ns, n, Tn);
+  const int slots = wgrad_group_slots(Ms, Ns, n, Tn);
   if (slots < 0) return fail(s, STAGE_EINVAL, "weight-gradient group: invalid sizes");
   size_t off = 0;
   for (int q = 0; q < n; ++q) {
@@ -517,19 +517,16 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const ColJob* 
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
   if (plan != 0) {
-    // whole gradients, then the column reductions
-    SITE(WGRAD_GROUP, gemm_mid_wgrad(gs, outs, n, plan, s->stream));
-    SITE(WGRAD_GROUP_RED, wgrad_group_reduce(nullptr, nullptr, 0, cols, ncols, s->stream));
+    SITE(WGRAD_GROUP, gemm_mid_wgrad(gs, outs, n, plan, tail, s->stream));
     return STAGE_OK;
   }
-  if (n > 0) SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
-  SITE(WGRAD_GROUP_RED, wgrad_group_reduce(gs, outs, n, cols, ncols, s->stream));
+  SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
+  SITE(WGRAD_GROUP_RED, wgrad_group_reduce(gs, outs, n, tail, s->stream));
   return STAGE_OK;
 }
 
 // The same on fp32 stages.
-stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const ColJob* cols, int ncols) {
-  if (n == 0 && ncols == 0) return STAGE_OK;
+stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const TailJobs& tail) {
   const int Tn = s->B * s->S;
   GemmArgs gs[GEMM_GROUP_MAX];
   float* outs[GEMM_GROUP_MAX];
@@ -542,7 +539,7 @@ stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const ColJ
     if (ks > 1) off += (size_t)ks * j.M * j.N;
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
-  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, ks, cols, ncols, s->stream));
+  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, ks, tail, s->stream));
   return STAGE_OK;
 }
 
@@ -672,9 +669,9 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
 bool recording(const stage_t* s) { return s->record_grads && (int)s->rec.size() == s->L; }
 
 // Backward of an fp32 stage: every tensor in fp32, the materialised attention
-// path; the four weight gradients of a layer run in one launch at its end,
-// and the sums of their splits with the bias / LayerNorm column reductions
-// in a second one.
+// path; the four weight gradients of a layer run in one launch at its end with
+// the bias / LayerNorm column reductions (in a second one with the sums of
+// their splits, when there are any).
 stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
   using T = float;
   const int B = s->B, S = s->S, h = s->h, H = s->H, f = s->f;
@@ -700,8 +697,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       HIPCK(hipMemcpyAsync(s->rec[l], dYcur, (size_t)Tn * h * 4, hipMemcpyDeviceToDevice, st));
     WgradJob wjobs[GEMM_GROUP_MAX];
     int nw = 0;
-    ColJob cjobs[COLJOB_MAX];
-    int nc = 0;
+    TailJobs tail{};
     // Gradient reaching H1: computed by the feed-forward half, or the
     // incoming dy when the stage ends at this layer's attention half.
     const T* dH1in = dYcur;
@@ -709,7 +705,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       // Y = LN(Z2): dZ2, dgamma2, dbeta2, and db_2 = sum_t dZ2
       SITE(LN2_BWD, ln_bwd_f32(dYcur, (const T*)v.xhat2, v.rstd2, (const float*)p[STAGE_G2], dZ2,
                                s->part2, Tn, h, st));
-      cjobs[nc++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
+      tail.col[tail.ncol++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G2], gr[STAGE_BE2], gr[STAGE_B_2], nullptr}};
       // dW_2 = dZ2^T G
       wjobs[nw++] = {dZ2, h, v.G, f, h, f, gr[STAGE_W_2]};
@@ -728,7 +724,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       }
       if (!fused)
         SITE(B1_SUM, col_partial<T>(dU, Tn, f, s->colpart_ffn, COL_PARTS, st));
-      cjobs[nc++] = ColJob{s->colpart_ffn, fused ? (Tn + 31) / 32 : COL_PARTS, 1, f,
+      tail.col[tail.ncol++] = ColJob{s->colpart_ffn, fused ? (Tn + 31) / 32 : COL_PARTS, 1, f,
                            {gr[STAGE_B_1], nullptr, nullptr, nullptr}};
       // dW_1 = dU^T H1
       wjobs[nw++] = {dU, f, v.H1, h, f, h, gr[STAGE_W_1]};
@@ -747,7 +743,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       // H1 = LN(Z1): dZ1, dgamma1, dbeta1, db_o
       SITE(LN1_BWD, ln_bwd_f32(dH1in, (const T*)v.xhat1, v.rstd1, (const float*)p[STAGE_G1], dZ1,
                                s->part, Tn, h, st));
-      cjobs[nc++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
+      tail.col[tail.ncol++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G1], gr[STAGE_BE1], gr[STAGE_B_O], nullptr}};
       // dW_o = dZ1^T C
       wjobs[nw++] = {dZ1, h, v.C, h, h, h, gr[STAGE_W_O]};
@@ -793,7 +789,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
                                        prob(s->dS, QKV + h, 3 * h, sq, 0),
                                        prob(s->dS, QKV, 3 * h, sq, 1), BH, st));
       }
-      cjobs[nc++] = ColJob{s->colpart_qkv, B * nqb, 1, 3 * h,
+      tail.col[tail.ncol++] = ColJob{s->colpart_qkv, B * nqb, 1, 3 * h,
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
       // dW_qkv = dQKV^T X
       wjobs[nw++] = {dQKV, 3 * h, v.X, h, 3 * h, h, gr[STAGE_W_QKV]};
@@ -807,7 +803,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       }
       dYcur = dXout;
     }
-    if ((r = wgrad_group_f32(s, wjobs, nw, cjobs, nc))) return r;
+    if ((r = wgrad_group_f32(s, wjobs, nw, tail))) return r;
   }
   return STAGE_OK;
 }
@@ -864,8 +860,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
     if (recording(s)) HIPCK(grad_f32(gin, s->rec[l], n, st));
     WgradJob wjobs[GEMM_GROUP_MAX];
     int nw = 0;
-    ColJob cjobs[COLJOB_MAX];
-    int nc = 0;
+    TailJobs tail{};
     // Gradient reaching H1: from the feed-forward half, or the incoming dy
     // when the stage ends at this layer's attention half.
     GradIn gh1 = gin;
@@ -873,7 +868,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
       // Y = LN(Z2): dZ2 and its residual, dgamma2, dbeta2, db_2 = sum_t dZ2
       SITE(LN2_BWD, ln_bwd_bf16(gin, (const T*)v.xhat2, v.rstd2, (const float*)p[STAGE_G2], dZ2,
                                 (T*)s->dz2lo, s->part2, Tn, h, st));
-      cjobs[nc++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
+      tail.col[tail.ncol++] = ColJob{s->part2, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G2], gr[STAGE_BE2], gr[STAGE_B_2], nullptr}};
       // dW_2 = dZ2^T G
       wjobs[nw++] = {dZ2, h, v.G, f, h, f, gr[STAGE_W_2]};
@@ -886,7 +881,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
         g.colpart = s->colpart_ffn;
         SITE(FFN2_DGRAD, gemm_bf16(g, false, EPI_MUL, st));
         const int rows = gemm_colpart_rows(g.tile);
-        cjobs[nc++] = ColJob{s->colpart_ffn, (Tn + rows - 1) / rows, 1, f,
+        tail.col[tail.ncol++] = ColJob{s->colpart_ffn, (Tn + rows - 1) / rows, 1, f,
                              {gr[STAGE_B_1], nullptr, nullptr, nullptr}};
       }
       // dW_1 = dU^T H1
@@ -896,13 +891,17 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
       if ((r = dgrad_joining(s, SITE_FFN1_DGRAD, gemm_args(dU, f, p[STAGE_W_1], h, nullptr, h, Tn, h, f),
                              dZ2, (const T*)s->dz2lo, &gh1)))
         return r;
-      if (!attn) HIPCK(grad_bf16(gh1, dx, n, st));
+      if (!attn) {
+        tail.gin = gh1;
+        tail.gout = dx;
+        tail.gn = n;
+      }
     }  // feed-forward half
     if (attn) {
       // H1 = LN(Z1): dZ1 and its residual, dgamma1, dbeta1, db_o
       SITE(LN1_BWD, ln_bwd_bf16(gh1, (const T*)v.xhat1, v.rstd1, (const float*)p[STAGE_G1], dZ1,
                                 (T*)s->dz1lo, s->part, Tn, h, st));
-      cjobs[nc++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
+      tail.col[tail.ncol++] = ColJob{s->part, ln_bwd_blocks(Tn), 3, h,
                            {gr[STAGE_G1], gr[STAGE_BE1], gr[STAGE_B_O], nullptr}};
       // dW_o = dZ1^T C
       wjobs[nw++] = {dZ1, h, v.C, h, h, h, gr[STAGE_W_O]};
@@ -918,7 +917,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
       aa.colpart = s->colpart_qkv;
       SITE(ATTN_DQ, attn_backward_dq(aa, st));
       SITE(ATTN_DKDV, attn_backward_dkdv(aa, st));
-      cjobs[nc++] = ColJob{s->colpart_qkv, B * ((S + 31) / 32), 1, 3 * h,
+      tail.col[tail.ncol++] = ColJob{s->colpart_qkv, B * ((S + 31) / 32), 1, 3 * h,
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
       // dW_qkv = dQKV^T X
       wjobs[nw++] = {dQKV, 3 * h, v.X, h, 3 * h, h, gr[STAGE_W_QKV]};
@@ -928,9 +927,13 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
                              gemm_args(dQKV, 3 * h, p[STAGE_W_QKV], h, nullptr, h, Tn, h, 3 * h), dZ1,
                              (const T*)s->dz1lo, &gin)))
         return r;
-      if (l == 0) HIPCK(grad_bf16(gin, dx, n, st));
+      if (l == 0) {
+        tail.gin = gin;
+        tail.gout = dx;
+        tail.gn = n;
+      }
     }
-    if ((r = wgrad_group(s, wjobs, nw, cjobs, nc))) return r;
+    if ((r = wgrad_group(s, wjobs, nw, tail))) return r;
   }
   return STAGE_OK;
 }
