@@ -220,15 +220,13 @@ __device__ __forceinline__ void store_rows_t(const f32x16_t acc[2], float mul, b
   }
 }
 
-// Work-group -> (row block, batch * head).  The grid is one-dimensional,
-// nq row blocks per (batch, head); consecutive work-groups go round robin
+// Work-group w of n -> (row block, batch * head), nq row blocks per (batch,
+// head); consecutive work-groups go round robin
 // over the 8 XCDs, so they are remapped such that each XCD takes a
 // contiguous range and the row blocks of one (batch, head), which stream the
 // same keys and values (or queries and output gradients), share that XCD's
 // L2.
-__device__ __forceinline__ void attn_block(int nq, int& rb, int& bh) {
-  const int n = gridDim.x;
-  int w = blockIdx.x;
+__device__ __forceinline__ void attn_block(int w, int n, int nq, int& rb, int& bh) {
   if ((n & 7) == 0) w = (w & 7) * (n >> 3) + (w >> 3);
   rb = w % nq;
   bh = w / nq;
@@ -276,7 +274,7 @@ __global__ __launch_bounds__(256, 4) void attn_fwd_kernel(AttnArgs a) {
   auto& kfull = lds.kfull;
 
   int qb, bh;
-  attn_block((a.S + 127) / 128, qb, bh);
+  attn_block(blockIdx.x, gridDim.x, (a.S + 127) / 128, qb, bh);
   const int b = bh / a.H, j = bh % a.H;
   const int S = a.S, h = a.h;
   const int64_t ld = 3 * (int64_t)h;
@@ -432,16 +430,17 @@ __global__ __launch_bounds__(256, 4) void attn_fwd_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward, dQ: wavefront = 32 queries; loops over key blocks.
+// Backward, dQ: wavefront = 32 queries; loops over key blocks.  DSUM: D =
+// rowsum(dO * O) is given.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) LdsKV lds;  // as in the forward
+template <bool DSUM>
+__device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, int n, LdsKV& lds) {
   auto& tiles = lds.tiles;
   auto& kbias = lds.kbias;
   auto& kfull = lds.kfull;
 
   int qb, bh;
-  attn_block((a.S + 127) / 128, qb, bh);
+  attn_block(w, n, (a.S + 127) / 128, qb, bh);
   const int b = bh / a.H, j = bh % a.H;
   const int S = a.S, h = a.h;
   const int64_t ld = 3 * (int64_t)h;
@@ -477,17 +476,20 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(AttnArgs a) {
   // residual: the rows of dS = P (dP - D) then sum to zero up to fp32 and
   // residual rounding, as the key-bias gradient (exactly zero) requires.
   const bf16_t* __restrict__ Olg = a.o_lo ? a.o_lo + (int64_t)b * S * h + j * HD : nullptr;
-  bf16x8_t qf[4], dof[4], of[4], olf[4];
+  bf16x8_t qf[4], dof[4], of[DSUM ? 1 : 4], olf[DSUM ? 1 : 4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int c = 16 * ks + 8 * hf;
     if (q < S) {
       qf[ks] = ld_frag(Qg + (int64_t)q * ld + c);
       dof[ks] = ld_frag(dOg + (int64_t)q * h + c);
-      of[ks] = ld_frag(Og + (int64_t)q * h + c);
-      olf[ks] = Olg ? ld_frag(Olg + (int64_t)q * h + c) : __builtin_bit_cast(bf16x8_t, zero4());
+      if constexpr (!DSUM) {
+        of[ks] = ld_frag(Og + (int64_t)q * h + c);
+        olf[ks] = Olg ? ld_frag(Olg + (int64_t)q * h + c) : __builtin_bit_cast(bf16x8_t, zero4());
+      }
     } else {
-      qf[ks] = dof[ks] = of[ks] = olf[ks] = __builtin_bit_cast(bf16x8_t, zero4());
+      qf[ks] = dof[ks] = __builtin_bit_cast(bf16x8_t, zero4());
+      if constexpr (!DSUM) of[ks] = olf[ks] = __builtin_bit_cast(bf16x8_t, zero4());
     }
   }
   const float lse_q = q < S ? a.lse[(int64_t)bh * S + q] : 0.0f;
@@ -501,16 +503,18 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(AttnArgs a) {
     }
   }
   int nraw = (tid < KT && nkb > 1) ? mask_raw(1) : 0;  // bytes of the next block
-  float dsum = 0.0f;
+  float dsum = 0.0f;  // D = rowsum(dO * O) of query q
+  if constexpr (DSUM) {
+    if (q < S) dsum = a.dsum[(int64_t)bh * S + q];
+  } else {
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) dsum += (float)dof[ks][i] * ((float)of[ks][i] + (float)olf[ks][i]);
-  {
+      for (int i = 0; i < 8; ++i) dsum += (float)dof[ks][i] * ((float)of[ks][i] + (float)olf[ks][i]);
     const HalfPair dp2 = half_pair(dsum);
-    dsum = dp2.x + dp2.y;  // D = rowsum(dO * O) of query q
+    dsum = dp2.x + dp2.y;
+    if (hf == 0 && q < S) a.dsum[(int64_t)bh * S + q] = dsum;
   }
-  if (hf == 0 && q < S) a.dsum[(int64_t)bh * S + q] = dsum;
 
   f32x16_t dq[2] = {zero16(), zero16()};  // dQ^T: dims x queries
   for (int kb = 0; kb < nkb; ++kb) {
@@ -580,18 +584,17 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(AttnArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int QB = 2 * KT;
 constexpr int QTILE = QB * HD * 2;
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(AttnArgs a) {
-  // One LDS object (see LdsKV): Q, dO per stage; lse and D per stage.
-  struct LdsQD {
-    char tiles[2][2 * QTILE];
-    float rowv[2][2][QB];
-  };
-  __shared__ __attribute__((aligned(1024))) LdsQD lds;
+// One LDS object (see LdsKV): Q, dO per stage; lse and D per stage.
+struct LdsQD {
+  char tiles[2][2 * QTILE];
+  float rowv[2][2][QB];
+};
+__device__ __forceinline__ void attn_bwd_dkdv(const AttnArgs& a, int w, int n, LdsQD& lds) {
   auto& tiles = lds.tiles;
   auto& rowv = lds.rowv;
 
   int kb128, bh;
-  attn_block((a.S + 127) / 128, kb128, bh);
+  attn_block(w, n, (a.S + 127) / 128, kb128, bh);
   const int b = bh / a.H, j = bh % a.H;
   const int S = a.S, h = a.h;
   const int64_t ld = 3 * (int64_t)h;
@@ -714,6 +717,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(AttnArgs a) {
   store_rows_t(dv, 1.0f, stage, dst + 2 * h, ld, k0, S, cp ? cp + 2 * h : nullptr);
 }
 
+__global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) LdsKV lds;
+  attn_bwd_dq<false>(a, blockIdx.x, gridDim.x, lds);
+}
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) LdsQD lds;
+  attn_bwd_dkdv(a, blockIdx.x, gridDim.x, lds);
+}
+// Both halves, given D: work-groups [0, n) dK and dV, [n, 2 n) dQ.
+__global__ __launch_bounds__(256, 2) void attn_bwd_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) union {
+    LdsQD qd;
+    LdsKV kv;
+  } lds;
+  const int n = gridDim.x >> 1, w = blockIdx.x;
+  if (w < n) attn_bwd_dkdv(a, w, n, lds.qd);
+  else attn_bwd_dq<true>(a, w - n, n, lds.kv);
+}
+
 }  // namespace
 
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
@@ -734,5 +756,12 @@ hipError_t attn_backward_dkdv(const AttnArgs& a, hipStream_t st) {
   if (a.B == 0 || a.S == 0) return hipSuccess;
   dim3 grid((unsigned)(((a.S + 127) / 128) * a.B * a.H));
   hipLaunchKernelGGL(attn_bwd_dkdv_kernel, grid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t attn_backward(const AttnArgs& a, hipStream_t st) {
+  if (a.B == 0 || a.S == 0) return hipSuccess;
+  dim3 grid((unsigned)(2 * ((a.S + 127) / 128) * a.B * a.H));
+  hipLaunchKernelGGL(attn_bwd_kernel, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -249,6 +249,9 @@ __device__ __forceinline__ void group_args(kgroup_t* gg, int p, GemmArgs& g) {
   g.C2 = a->C2;
   g.bias = a->bias;
   g.aux = a->aux;
+  g.aux2 = a->aux2;
+  g.dsum = a->dsum;
+  g.dsum_S = a->dsum_S;
   g.M = a->M;
   g.N = a->N;
   g.K = a->K;
@@ -783,6 +786,9 @@ hipError_t gemm_bf16(const GemmArgs& g0, bool b_kmajor, GemmEpi epi, hipStream_t
     return hipErrorInvalidValue;
   if (g.ksplit > 1 && (g.kchunk % 64 != 0 || epi != EPI_PARTIAL)) return hipErrorInvalidValue;
   if (epi == EPI_MUL && !g.colpart) return hipErrorInvalidValue;
+  if (epi == EPI_DSUM && (!g.aux || !g.aux2 || !g.dsum || g.dsum_S < 1 || g.M % g.dsum_S != 0 ||
+                          g.N % 64 != 0))
+    return hipErrorInvalidValue;
   // Operands are read through buffer resources with 32-bit byte extents and
   // offsets: each operand must span less than 2 GiB.
   if ((int64_t)g.M * g.lda * 2 >= ((int64_t)1 << 31) ||

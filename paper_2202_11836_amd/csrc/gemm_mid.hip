@@ -162,7 +162,7 @@ __device__ __forceinline__ void mid_body(const GemmArgs& g, int zs, int tm, int 
     b0 = *(const f32x4_t*)(g.bias + n);
     b1 = *(const f32x4_t*)(g.bias + n + 4);
   }
-  constexpr bool AUX = EPI == EPI_MUL;
+  constexpr bool AUX = EPI == EPI_MUL, DSUM = EPI == EPI_DSUM;
 
   f32x16_t acc[2][2];
 #pragma unroll
@@ -254,14 +254,23 @@ __device__ __forceinline__ void mid_body(const GemmArgs& g, int zs, int tm, int 
       }
   }
 
-  u32x4_t ax[AUX ? NCH : 1];
-  if constexpr (AUX) {
+  u32x4_t ax[AUX || DSUM ? NCH : 1], ax2[DSUM ? NCH : 1];
+  if constexpr (AUX || DSUM) {
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
       const int m = m0 + er + q * RPP;
-      ax[q] = (m < g.M && n < g.N) ? *(const u32x4_t*)((const bf16_t*)g.aux + (int64_t)m * g.ldaux + n)
-                                   : u32x4_t{0, 0, 0, 0};
+      const int64_t at = (int64_t)m * g.ldaux + n;
+      const bool in = m < g.M && n < g.N;
+      ax[q] = in ? *(const u32x4_t*)((const bf16_t*)g.aux + at) : u32x4_t{0, 0, 0, 0};
+      if constexpr (DSUM)
+        ax2[q] = in ? *(const u32x4_t*)((const bf16_t*)g.aux2 + at) : u32x4_t{0, 0, 0, 0};
     }
+  }
+  // DSUM: sequence and position of the thread's row, advanced with it.
+  int sb = 0, ss = 0;
+  if constexpr (DSUM) {
+    sb = (m0 + er) / g.dsum_S;
+    ss = m0 + er - sb * g.dsum_S;
   }
   // The k sums: [k group][row][column] fp32 over the ring.
   __syncthreads();
@@ -296,10 +305,30 @@ __device__ __forceinline__ void mid_body(const GemmArgs& g, int zs, int tm, int 
         *(u32x4_t*)((bf16_t*)g.C + (int64_t)m * g.ldc + n) = o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) cs[e] += v[e];
+      } else if constexpr (DSUM) {
+        u32x4_t o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+        *(u32x4_t*)((bf16_t*)g.C + (int64_t)m * g.ldc + n) = o;
+        // the head's 64 columns: 8 neighbouring lanes (rows of one head are
+        // all inside or all outside, N being a multiple of 64)
+        float d = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          d += __uint_as_float(o[i] << 16) *
+               (__uint_as_float(ax[q][i] << 16) + __uint_as_float(ax2[q][i] << 16));
+          d += __uint_as_float(o[i] & 0xffff0000u) *
+               (__uint_as_float(ax[q][i] & 0xffff0000u) + __uint_as_float(ax2[q][i] & 0xffff0000u));
+        }
+#pragma unroll
+        for (int x = 1; x < 8; x <<= 1) d += __shfl_xor(d, x, 64);
+        if ((tid & 7) == 0) g.dsum[((int64_t)sb * (g.N >> 6) + (n >> 6)) * g.dsum_S + ss] = d;
       } else {
         epi8<EPI, false>(g, 0, zs, m, n, v, u32x4_t{0, 0, 0, 0}, b0, b1);
       }
     }
+    if constexpr (DSUM)
+      for (ss += RPP; ss >= g.dsum_S; ss -= g.dsum_S) ++sb;
   }
   if constexpr (AUX) {
     // Column sums of the tile's stored values: one partial row per tile.
@@ -377,6 +406,7 @@ hipError_t dispatch(const GemmArgs& g, bool b_kmajor, GemmEpi epi, hipStream_t s
     if (epi == EPI_STORE) return launch<BM, BN, true, false, EPI_STORE>(g, st);
     if (epi == EPI_MUL) return launch<BM, BN, true, false, EPI_MUL>(g, st);
     if (epi == EPI_PARTIAL) return launch<BM, BN, true, false, EPI_PARTIAL>(g, st);
+    if (epi == EPI_DSUM) return launch<BM, BN, true, false, EPI_DSUM>(g, st);
   }
   return hipErrorInvalidValue;
 }

@@ -22,6 +22,8 @@ enum GemmEpi {
   EPI_MUL = 2,      // C = acc * aux[m, n]  (the FFN backward: dU = dG * GELU'(u))
   EPI_RESID = 3,    // C = acc + aux[m, n]
   EPI_PARTIAL = 4,  // fp32 C[split][m][n] = acc over this split's K range
+  EPI_DSUM = 5,     // C = acc (dO), and per row and head (64 columns) of C as stored
+                    // the sum over its columns of C * (aux + aux2): rowsum(dO * O)
 };
 
 struct GemmArgs {
@@ -31,6 +33,11 @@ struct GemmArgs {
   void* C2;
   const float* bias;
   const void* aux;
+  const void* aux2;  // EPI_DSUM: the rounding residual of aux (same layout)
+  // EPI_DSUM: receives the sums, row m = b S + s of head j at dsum[(b * (N / 64)
+  // + j) * S + s]
+  float* dsum;
+  int dsum_S;
   int M, N, K;
   int64_t lda, ldb, ldc, ldaux;
   int zdiv;
@@ -83,7 +90,8 @@ inline int gemm_colpart_rows(int tile) {
 }
 int64_t gemm_colpart_max(int64_t M);
 // bf16 operands on MFMA (fp32 accumulation), A k-major, batch 1.  b k-major:
-// EPI_STORE, EPI_GELU, EPI_PARTIAL; n-major: EPI_STORE, EPI_MUL, EPI_PARTIAL.
+// EPI_STORE, EPI_GELU, EPI_PARTIAL; n-major: EPI_STORE, EPI_MUL, EPI_PARTIAL,
+// and EPI_DSUM with the tiles of gemm_mid.hip.
 // EPI_PARTIAL writes fp32 (C[split][M][ldc], ksplit splits of kchunk), the
 // others bf16.
 hipError_t gemm_bf16(const GemmArgs& g, bool b_kmajor, GemmEpi epi, hipStream_t st);
@@ -273,7 +281,8 @@ struct AttnArgs {
 };
 // Forward pass (needs kext).
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st);
-// dsum and dQ (into out's Q block); must run before attn_backward_dkdv.
+// Backward, into out's Q, K and V blocks: dsum and dQ, then dK and dV; or all in
+// one launch, given dsum (EPI_DSUM of the product that makes dout).
 hipError_t attn_backward_dq(const AttnArgs& a, hipStream_t st);
-// dK and dV (into out's K and V blocks).
 hipError_t attn_backward_dkdv(const AttnArgs& a, hipStream_t st);
+hipError_t attn_backward(const AttnArgs& a, hipStream_t st);

@@ -40,7 +40,7 @@ constexpr int COL_PARTS = 128; // row blocks of a column-sum pass (fp32 stages, 
   X(BQKV_RED, "bqkv_colreduce") X(WQKV_WGRAD, "wqkv_wgrad_gemm")                        \
   X(WQKV_RED, "wqkv_wgrad_splitk_reduce") X(QKV_DGRAD, "qkv_dgrad_resid_gemm")            \
   X(KEXT, "key_extent") X(ATTN_FWD, "attn_fwd") X(ATTN_DQ, "attn_bwd_dq")                 \
-  X(ATTN_DKDV, "attn_bwd_dkdv")                                \
+  X(ATTN_DKDV, "attn_bwd_dkdv") X(ATTN_BWD, "attn_bwd")                                   \
   X(WGRAD_GROUP, "wgrad_group_gemm") X(WGRAD_GROUP_RED, "wgrad_group_splitk_reduce")
 
 enum Site {
@@ -905,9 +905,17 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
                            {gr[STAGE_G1], gr[STAGE_BE1], gr[STAGE_B_O], nullptr}};
       // dW_o = dZ1^T C
       wjobs[nw++] = {dZ1, h, v.C, h, h, h, gr[STAGE_W_O]};
-      // dC = dZ1 W_o
-      SITE(OUT_DGRAD,
-           gemm_bf16(gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h), false, EPI_STORE, st));
+      // dC = dZ1 W_o; with the tiles that can, also D = rowsum(dC * C) per
+      // head, so that both halves of the attention backward are one launch
+      GemmArgs g = gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h);
+      g.tile = gemm_bf16_plan(Tn, h, h, false, EPI_STORE, false).tile;
+      g.aux = v.C;
+      g.aux2 = v.Clo;
+      g.ldaux = h;
+      g.dsum = s->dsum;
+      g.dsum_S = S;
+      const bool dsum = g.tile != GEMM_TILE_256x256;
+      SITE(OUT_DGRAD, gemm_bf16(g, false, dsum ? EPI_DSUM : EPI_STORE, st));
       // Attention backward (recomputes P from the saved log-sum-exp): dQKV
       // and the column sums of db_qkv per 32-row block.
       AttnArgs aa = attn_args(s, (const T*)v.QKV, dQKV, v.lse);
@@ -915,8 +923,12 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
       aa.o_lo = (const T*)v.Clo;
       aa.dout = dC;
       aa.colpart = s->colpart_qkv;
-      SITE(ATTN_DQ, attn_backward_dq(aa, st));
-      SITE(ATTN_DKDV, attn_backward_dkdv(aa, st));
+      if (dsum) {
+        SITE(ATTN_BWD, attn_backward(aa, st));
+      } else {
+        SITE(ATTN_DQ, attn_backward_dq(aa, st));
+        SITE(ATTN_DKDV, attn_backward_dkdv(aa, st));
+      }
       tail.col[tail.ncol++] = ColJob{s->colpart_qkv, B * ((S + 31) / 32), 1, 3 * h,
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
       // dW_qkv = dQKV^T X
