@@ -776,23 +776,26 @@ hipError_t launch_bf16(const GemmArgs& g0, int batch, hipStream_t st) {
 
 }  // namespace
 
-hipError_t gemm_bf16(const GemmArgs& g0, bool b_kmajor, GemmEpi epi, hipStream_t st) {
-  GemmArgs g = g0;
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+bool gemm_bf16_ok(const GemmArgs& g, bool b_kmajor) {
   // Vector epilogue and n-major staging work in 8-column units; k-tiles of
   // 64 never straddle a split boundary, and k-major operands are read
   // without a k bound.
   if (g.N % 8 != 0 || g.ldc % 8 != 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0)
-    return hipErrorInvalidValue;
+    return false;
+  // Operands are read through buffer resources with 32-bit byte extents and
+  // offsets: each operand must span less than 2 GiB.
+  return (int64_t)g.M * g.lda * 2 < ((int64_t)1 << 31) &&
+         (int64_t)(b_kmajor ? g.N : g.K) * g.ldb * 2 < ((int64_t)1 << 31);
+}
+
+hipError_t gemm_bf16(const GemmArgs& g0, bool b_kmajor, GemmEpi epi, hipStream_t st) {
+  GemmArgs g = g0;
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (!gemm_bf16_ok(g, b_kmajor)) return hipErrorInvalidValue;
   if (g.ksplit > 1 && (g.kchunk % 64 != 0 || epi != EPI_PARTIAL)) return hipErrorInvalidValue;
   if (epi == EPI_MUL && !g.colpart) return hipErrorInvalidValue;
   if (epi == EPI_DSUM && (!g.aux || !g.aux2 || !g.dsum || g.dsum_S < 1 || g.M % g.dsum_S != 0 ||
                           g.N % 64 != 0))
-    return hipErrorInvalidValue;
-  // Operands are read through buffer resources with 32-bit byte extents and
-  // offsets: each operand must span less than 2 GiB.
-  if ((int64_t)g.M * g.lda * 2 >= ((int64_t)1 << 31) ||
-      (int64_t)(b_kmajor ? g.N : g.K) * g.ldb * 2 >= ((int64_t)1 << 31))
     return hipErrorInvalidValue;
   if (g.tile == 0) g.tile = gemm_bf16_plan(g.M, g.N, g.K, b_kmajor, epi, false).tile;
   if (g.tile == GEMM_TILE_256x256 && g.ksplit == 1) {

@@ -354,6 +354,23 @@ __global__ __launch_bounds__((MidCfg<BM, BN>::THREADS), 2) void gemm_mid_kernel(
   mid_body<BM, BN, AK, BKM, EPI>(g, zs, tm, tn, smem);
 }
 
+// The same beside the start of a forward pass, in the work-groups after the
+// tiles.
+template <int BM, int BN, int EPI>
+__global__ __launch_bounds__((MidCfg<BM, BN>::THREADS), 2) void gemm_mid_prep_kernel(GemmArgs g,
+                                                                                   PrepArgs p) {
+  __shared__ __attribute__((aligned(1024))) char smem[MidCfg<BM, BN>::LDS];
+  const int nbm = (g.M + BM - 1) / BM, nbn = (g.N + BN - 1) / BN, total = nbm * nbn;
+  if ((int)blockIdx.x >= total) {
+    prep_unit(p, ((int)blockIdx.x - total) * MidCfg<BM, BN>::W + (int)(threadIdx.x >> 6),
+              threadIdx.x & 63);
+    return;
+  }
+  int zs, tm, tn;
+  mid_tile(blockIdx.x, total, nbm, nbn, zs, tm, tn);
+  mid_body<BM, BN, true, true, EPI>(g, 0, tm, tn, smem);
+}
+
 // Weight gradients of one layer in one launch, each written whole; the tail's
 // units, one per wavefront, in the work-groups after the tiles.
 struct MidGroup {
@@ -411,7 +428,33 @@ hipError_t dispatch(const GemmArgs& g, bool b_kmajor, GemmEpi epi, hipStream_t s
   return hipErrorInvalidValue;
 }
 
+template <int BM, int BN>
+hipError_t dispatch_prep(const GemmArgs& g, GemmEpi epi, const PrepArgs& p, hipStream_t st) {
+  constexpr int W = MidCfg<BM, BN>::W;
+  const int64_t total =
+      (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) + (prep_units(p) + W - 1) / W;
+  if (total >= ((int64_t)1 << 28)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)total), blk(MidCfg<BM, BN>::THREADS);
+  if (epi == EPI_STORE)
+    hipLaunchKernelGGL((gemm_mid_prep_kernel<BM, BN, EPI_STORE>), grid, blk, 0, st, g, p);
+  else
+    hipLaunchKernelGGL((gemm_mid_prep_kernel<BM, BN, EPI_GELU>), grid, blk, 0, st, g, p);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t gemm_mid_prep(const GemmArgs& g, GemmEpi epi, const PrepArgs& p, hipStream_t st) {
+  if ((epi != EPI_STORE && epi != EPI_GELU) || g.ksplit != 1 || p.nx % 16 != 0 || !gemm_bf16_ok(g, true))
+    return hipErrorInvalidValue;
+  switch (g.tile) {
+    case GEMM_TILE_256x128: return dispatch_prep<256, 128>(g, epi, p, st);
+    case GEMM_TILE_128x128: return dispatch_prep<128, 128>(g, epi, p, st);
+    case GEMM_TILE_128x64: return dispatch_prep<128, 64>(g, epi, p, st);
+    case GEMM_TILE_64x64: return dispatch_prep<64, 64>(g, epi, p, st);
+  }
+  return hipErrorInvalidValue;
+}
 
 hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hipStream_t st) {
   switch (tile) {

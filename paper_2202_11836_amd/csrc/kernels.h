@@ -177,6 +177,8 @@ struct TailJobs {
 hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const TailJobs& tail,
                               hipStream_t st);
 
+// Whether the bf16 GEMMs take g's shapes and strides.
+bool gemm_bf16_ok(const GemmArgs& g, bool b_kmajor);
 // gemm_bf16 with one of the tiles of gemm_mid.hip.
 hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hipStream_t st);
 // n weight gradients (operands m/n-major, ldc = N), each written whole, and
@@ -230,8 +232,19 @@ hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st);
 // Start of a forward pass: X = x (nx bytes, a multiple of 16; both 16-byte
 // aligned); mask = key_mask, or all ones when that is null; when kext is not
 // null, kext[b] = 1 + last s with mask[b][s] != 0 (0 if none).
-hipError_t stage_prep(const void* x, void* X, int64_t nx, const uint8_t* key_mask, uint8_t* mask,
-                      int B, int S, int* kext, hipStream_t st);
+struct PrepArgs {
+  const void* x;
+  void* X;
+  int64_t nx;
+  const uint8_t* key_mask;
+  uint8_t* mask;
+  int B, S;
+  int* kext;
+};
+hipError_t stage_prep(const PrepArgs& p, hipStream_t st);
+// The same beside gemm_bf16(g, true, epi, st) in its launch (EPI_STORE or
+// EPI_GELU with a tile of gemm_mid.hip; g may read x, not X).
+hipError_t gemm_mid_prep(const GemmArgs& g, GemmEpi epi, const PrepArgs& p, hipStream_t st);
 
 // part[blk][n] = sum over the block's rows of x[row][n].
 template <typename T>

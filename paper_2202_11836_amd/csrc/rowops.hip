@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "tail.h"
 
 namespace {
 
@@ -431,37 +432,9 @@ __global__ __launch_bounds__(256) void grad_kernel(GradIn in, float* __restrict_
   store8(out + i, v);
 }
 
-// Work-groups [0, B): one sequence's mask (and key extent); the others copy x.
-__global__ __launch_bounds__(256) void stage_prep_kernel(const u32x4_t* __restrict__ x,
-                                                         u32x4_t* __restrict__ X, int64_t n16,
-                                                         const uint8_t* __restrict__ key_mask,
-                                                         uint8_t* __restrict__ mask, int B, int S,
-                                                         int* __restrict__ kext) {
-  if ((int)blockIdx.x < B) {
-    __shared__ int sm[4];
-    const int64_t b0 = (int64_t)blockIdx.x * S;
-    int last = 0;
-    for (int s = threadIdx.x; s < S; s += 256) {
-      const uint8_t v = key_mask ? key_mask[b0 + s] : 1;
-      mask[b0 + s] = v;
-      if (v) last = max(last, s + 1);
-    }
-    if (!kext) return;
-    for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = last;
-    __syncthreads();
-    if (threadIdx.x == 0) kext[blockIdx.x] = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
-    return;
-  }
-  // four 16-byte chunks per thread, a work-group's chunks side by side
-  const int64_t i0 = (int64_t)(blockIdx.x - B) * 1024 + threadIdx.x;
-  u32x4_t v[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (i0 + 256 * k < n16) v[k] = x[i0 + 256 * k];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (i0 + 256 * k < n16) X[i0 + 256 * k] = v[k];
+// Four units per work-group.
+__global__ __launch_bounds__(256) void stage_prep_kernel(PrepArgs p) {
+  prep_unit(p, blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
 }
 
 template <typename T>
@@ -618,12 +591,10 @@ hipError_t grad_f32(const GradIn& in, float* out, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t stage_prep(const void* x, void* X, int64_t nx, const uint8_t* key_mask, uint8_t* mask,
-                      int B, int S, int* kext, hipStream_t st) {
-  const int64_t blocks = B + (nx / 16 + 1023) / 1024;
-  if (nx % 16 != 0 || blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(stage_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const u32x4_t*)x,
-                     (u32x4_t*)X, nx / 16, key_mask, mask, B, S, kext);
+hipError_t stage_prep(const PrepArgs& p, hipStream_t st) {
+  const int64_t blocks = (prep_units(p) + 3) / 4;
+  if (p.nx % 16 != 0 || blocks >= ((int64_t)1 << 29)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(stage_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 

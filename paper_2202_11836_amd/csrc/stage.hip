@@ -568,17 +568,30 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
   hipStream_t st = s->stream;
   const float scale = 1.0f / sqrtf((float)HEAD_DIM);
   // The stage input is X of local layer 0, or its H1 when that layer holds
-  // only its feed-forward half.  One launch copies it and the key mask and
-  // finds the key extents; an input that is not 16-byte aligned is copied by
-  // the runtime.
-  {
-    void* X = s->ffn_first ? s->saved[0].H1 : s->saved[0].X;
-    const int64_t nx = (int64_t)Tn * h * sizeof(T);
-    const bool aligned = ((uintptr_t)x & 15) == 0;
-    int* kext = std::is_same<T, bf16_t>::value && (s->L > 1 || !s->ffn_first) ? s->kext : nullptr;
-    if (!aligned) HIPCK(hipMemcpyAsync(X, x, (size_t)nx, hipMemcpyDeviceToDevice, st));
-    SITE(KEXT, stage_prep(x, X, aligned ? nx : 0, key_mask, s->mask, B, S, kext, st));
+  // only its feed-forward half.  It and the key mask are copied and the key
+  // extents found beside the first GEMM, which then reads x itself (bf16,
+  // tiles of gemm_mid.hip), else by a launch of their own; an input that is
+  // not 16-byte aligned is copied by the runtime first.
+  PrepArgs prep{x, s->ffn_first ? s->saved[0].H1 : s->saved[0].X, (int64_t)Tn * h * (int)sizeof(T),
+                key_mask, s->mask, B, S, nullptr};
+  if (std::is_same<T, bf16_t>::value && (s->L > 1 || !s->ffn_first)) prep.kext = s->kext;
+  if (((uintptr_t)x & 15) != 0) {
+    HIPCK(hipMemcpyAsync(prep.X, x, (size_t)prep.nx, hipMemcpyDeviceToDevice, st));
+    prep.x = prep.X;
+    prep.nx = 0;
   }
+  const GemmEpi epi0 = s->ffn_first ? EPI_GELU : EPI_STORE;
+  const int tile0 = gemm_bf16_plan(Tn, s->ffn_first ? f : 3 * h, h, true, epi0, false).tile;
+  const bool prep_beside = std::is_same<T, bf16_t>::value && tile0 != GEMM_TILE_256x256;
+  if (!prep_beside) SITE(KEXT, stage_prep(prep, st));
+  // A product with the layer's input or H1 as A, the first of the pass with
+  // the above.
+  auto gemm_in = [&](GemmArgs g, GemmEpi epi, bool first) -> hipError_t {
+    if (!first || !prep_beside) return gemm_fwd(g, epi, (T*)nullptr, st);
+    g.A = prep.x;
+    g.tile = tile0;
+    return gemm_mid_prep(g, epi, prep, st);
+  };
   for (int l = 0; l < s->L; ++l) {
     Saved& v = s->saved[l];
     auto& p = s->param[l];
@@ -595,7 +608,7 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
       {
         GemmArgs g = gemm_args(X, h, p[STAGE_W_QKV], h, QKV, 3 * h, Tn, 3 * h, h);
         g.bias = (const float*)p[STAGE_B_QKV];
-        SITE(QKV_FWD, gemm_fwd(g, EPI_STORE, QKV, st));
+        SITE(QKV_FWD, gemm_in(g, EPI_STORE, l == 0));
       }
       if constexpr (std::is_same<T, bf16_t>::value) {
         // Fused attention: softmax(Q K^T / 8) V per (batch, head), P stays on chip.
@@ -648,7 +661,7 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
       GemmArgs g = gemm_args(v.H1, h, p[STAGE_W_1], h, v.G, f, Tn, f, h);
       g.bias = (const float*)p[STAGE_B_1];
       g.C2 = v.Gd;
-      SITE(FFN1_FWD, gemm_fwd(g, EPI_GELU, (T*)nullptr, st));
+      SITE(FFN1_FWD, gemm_in(g, EPI_GELU, l == 0 && s->ffn_first));
     }
     // tmp = G W_2^T (fp32);  Y = LN(H1 + tmp + b_2)
     int np2 = 1;

@@ -1,10 +1,10 @@
-// Small reductions and conversions at the end of a layer's backward, as units
-// of one wavefront that the weight-gradient kernels take on in extra
-// work-groups.
+// Small work around a stage's GEMMs, as units of one wavefront that the GEMM
+// kernels take on in extra work-groups: the reductions and conversions at the
+// end of a layer's backward, and the copies at the start of a forward pass.
 //
-// On their own they are a launch or two of 3 to 5 us whose work is 1 to 2 us.
-// Behind the tiles of a weight-gradient launch they run on CUs that its last
-// round leaves idle.  No LDS, so a unit fits beside any kernel.
+// On their own they are launches of 3 to 5 us whose work is 1 to 2 us.  Behind
+// the tiles of a GEMM launch they run on CUs that its last round leaves idle.
+// No LDS, so a unit fits beside any kernel.
 #pragma once
 #include <cstddef>
 
@@ -116,7 +116,49 @@ __device__ __forceinline__ void tail_unit(ktail_t* t, int u, int lane) {
   colred_unit<D>(c->part, c->nblk, c->nvec, n, v, r - v * nx, c->out[v], lane);
 }
 
+// Unit u of a forward pass's start: one sequence's mask and key extent, or
+// PREP_CHUNKS chunks of x.
+constexpr int PREP_CHUNKS = 256;  // 16-byte chunks of x per wavefront
+__device__ __forceinline__ void prep_unit(const PrepArgs& p, int u, int lane) {
+  if (u < p.B) {
+    const int64_t b0 = (int64_t)u * p.S;
+    int last = 0;
+    for (int s0 = 0; s0 < p.S; s0 += 512) {
+      int v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = 1;
+      if (p.key_mask) {  // (positions clamped: no load waits for another)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = p.key_mask[b0 + min(s0 + 64 * k + lane, p.S - 1)];
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int s = s0 + 64 * k + lane;
+        if (s < p.S) p.mask[b0 + s] = (uint8_t)v[k];
+        if (s < p.S && v[k]) last = s + 1;
+      }
+    }
+    if (!p.kext) return;
+    for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+    if (lane == 0) p.kext[u] = last;
+    return;
+  }
+  const int64_t n16 = p.nx / 16, i0 = (int64_t)(u - p.B) * PREP_CHUNKS + lane;
+  const u32x4_t* x = (const u32x4_t*)p.x;
+  u32x4_t v[PREP_CHUNKS / 64];
+#pragma unroll
+  for (int k = 0; k < PREP_CHUNKS / 64; ++k)
+    if (i0 + 64 * k < n16) v[k] = x[i0 + 64 * k];
+#pragma unroll
+  for (int k = 0; k < PREP_CHUNKS / 64; ++k)
+    if (i0 + 64 * k < n16) ((u32x4_t*)p.X)[i0 + 64 * k] = v[k];
+}
+
 }  // namespace
+
+inline int64_t prep_units(const PrepArgs& p) {
+  return p.B + (p.nx / 16 + PREP_CHUNKS - 1) / PREP_CHUNKS;
+}
 
 // Checks t's jobs and numbers their units; false for invalid ones.
 inline bool tail_prepare(TailJobs& t) {
