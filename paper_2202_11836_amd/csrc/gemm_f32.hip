@@ -5,21 +5,24 @@
 // TFLOP/s), so a wavefront's MFMAs take 64 cycles each and everything else
 // fits underneath if the loads are requested early enough.  k-tiles go from
 // HBM straight into a ring of LDS slots with direct-to-LDS buffer loads, up
-// to NS - 1 of them in flight, one barrier per k-tile; each wavefront owns
-// one 32 x 32 output block.  Two work-group shapes:
+// to NS of them in flight, one barrier per k-tile; each wavefront owns
+// one 32 x 32 output block.  Three work-group shapes:
 //   64 x 64, 2 x 2 wavefronts, k-tiles of 32, four slots (64 KB, two
-//     work-groups per CU, so a second wavefront per SIMD covers waits);
+//     work-groups per CU);
+//   64 x 32, 2 x 1 wavefronts times two that split every k-tile by k, four
+//     slots (48 KB, three work-groups per CU), where 64 x 64 tiles leave the
+//     last round of CUs part idle;
 //   32 x 32, four wavefronts splitting every k-tile of 64 by k (their sums
 //     are added in wavefront order at the end), eight slots: for outputs with
 //     few 64 x 64 tiles, where the chain of MFMAs of one wavefront and the
 //     memory latency are the time.
-// Measured against the vector-ALU kernel this replaced (64 x 64 tiles, 4 x 4
-// outputs per thread, one global load -> LDS -> barrier per 16 k): a BERT-base
-// layer at 16 x 128 tokens, forward and backward, 3689 -> 1090 us, its FFN1
-// (2048 x 3072 x 768) 236 -> 105 us (92 TFLOP/s), its weight gradients 102
-// TFLOP/s; two layers of width 128 at 64 tokens 1086 -> 186 us.  Largest
-// relative error against 64 bits 1.2e-6 -> 7e-7 and 3.2e-7 -> 2.3e-7.
+// Measured against a vector-ALU kernel (64 x 64 tiles, 4 x 4 outputs per
+// thread, one global load -> LDS -> barrier per 16 k): a BERT-base layer at 16 x
+// 128 tokens, forward and backward, 3689 -> 948 us; two layers of width 128 at
+// 64 tokens 1086 -> 164 us.  Largest relative error against 64 bits 1.2e-6 ->
+// 7e-7 and 3.2e-7 -> 2.3e-7.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 #include "tail.h"
@@ -33,13 +36,14 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // kernel's time.
 constexpr int64_t SMALL_TILES = 256;
 
-template <bool SMALL>
+enum F32Tile { T64x64, T64x32, T32x32 };
+template <F32Tile T>
 struct Cfg {
-  static constexpr int R = SMALL ? 32 : 64;     // tile rows and columns
-  static constexpr int KG = SMALL ? 4 : 1;      // wavefront groups along k
-  static constexpr int BK = SMALL ? 64 : 32;    // k-tile depth
-  static constexpr int OP = R * BK * 4;         // bytes of one operand's k-tile
-  static constexpr int STAGE = 2 * OP;          // 16 KB
+  static constexpr int BM = T == T32x32 ? 32 : 64, BN = T == T64x64 ? 64 : 32;
+  static constexpr int MB = BM / 32, NB = BN / 32;  // wavefronts along m and n
+  static constexpr int KG = 4 / (MB * NB);          // and along k
+  static constexpr int BK = T == T32x32 ? 64 : 32;  // k-tile depth
+  static constexpr int A_BYTES = BM * BK * 4, STAGE = (BM + BN) * BK * 4;
 };
 
 // Buffer resource from base on; lanes that must read 0 use offset OOB.
@@ -87,33 +91,48 @@ __device__ __forceinline__ void wait_after(int after) {
 //   m/n-major: [BK][R], as in memory.
 // VEC: 16 bytes per lane (operand 16-byte aligned, its contiguous extent a
 // multiple of 4); else 4 bytes per lane.
+// What does not change from k-tile to k-tile is worked out once: per
+// instruction i of the wavefront's N, its first element's address p, the
+// lane's byte offset vo from there and its k in the tile, kx (too large for
+// any range where the row or column is outside).
 template <int R, int BK, bool KMAJ, bool VEC>
-__device__ __forceinline__ void dma_op(const float* base, int64_t ld, int nr, int k0, int kend,
-                                       char* dst, int wave, int lane) {
-  constexpr int BYTES = VEC ? 16 : 4, PERI = 64 * BYTES;
-  constexpr int NI = R * BK * 4 / PERI / 4;  // instructions per wavefront
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int q = wave * NI + i;
-    const int e0 = q * (PERI / 4);  // the instruction's first element
+struct DmaOp {
+  static constexpr int BYTES = VEC ? 16 : 4, PERI = 64 * BYTES;
+  static constexpr int N = R * BK * 4 / PERI / 4;
+  const float* p[N];
+  int vo[N], kx[N];
+  __device__ __forceinline__ void init(const float* base, int64_t ld, int nr, int wave, int lane) {
     const int el = lane * (BYTES / 4);
-    if constexpr (KMAJ) {
-      const int sub = e0 / (R * 32), row0 = (e0 % (R * 32)) / 32;  // whole rows of 32
-      const int dr = el >> 5, row = row0 + dr;
-      const int k = k0 + 32 * sub + 4 * (((el & 31) >> 2) ^ ((row >> 1) & 7)) + (el & 3);
-      const __amdgpu_buffer_rsrc_t rs = rsrc_of(base + (int64_t)row0 * ld);
-      const int vo = (row < nr && k < kend) ? (dr * (int)ld + k) * 4 : OOB;
-      load_lds<VEC>(rs, dst + q * PERI, vo);
-    } else {
-      const int kr0 = e0 / R, c0 = e0 % R;  // c0 != 0: a part of one k-row
-      const int dk = (c0 + el) / R, col = (c0 + el) % R;
-      const int k = k0 + kr0 + dk;
-      const __amdgpu_buffer_rsrc_t rs = rsrc_of(base + (int64_t)(k0 + kr0) * ld);
-      const int vo = (col < nr && k < kend) ? (dk * (int)ld + col) * 4 : OOB;
-      load_lds<VEC>(rs, dst + q * PERI, vo);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int e0 = (wave * N + i) * (PERI / 4);  // the instruction's first element
+      bool in;
+      if constexpr (KMAJ) {
+        const int sub = e0 / (R * 32), row0 = (e0 % (R * 32)) / 32;  // whole rows of 32
+        const int dr = el >> 5, row = row0 + dr;
+        kx[i] = 32 * sub + 4 * (((el & 31) >> 2) ^ ((row >> 1) & 7)) + (el & 3);
+        p[i] = base + row0 * ld;
+        vo[i] = (dr * (int)ld + kx[i]) * 4;
+        in = row < nr;
+      } else {
+        const int kr0 = e0 / R, c0 = e0 % R;  // c0 != 0: a part of one k-row
+        const int dk = (c0 + el) / R, col = (c0 + el) % R;
+        kx[i] = kr0 + dk;
+        p[i] = base + kr0 * ld;
+        vo[i] = (dk * (int)ld + col) * 4;
+        in = col < nr;
+      }
+      if (!in) kx[i] = 1 << 30;
     }
   }
-}
+  // Instruction i of the k-tile at k0.
+  __device__ __forceinline__ void issue(int i, int64_t ld, int k0, int kend, char* dst, int wave) const {
+    const bool in = k0 + kx[i] < kend;
+    char* to = dst + (wave * N + i) * PERI;
+    if constexpr (KMAJ) load_lds<VEC>(rsrc_of(p[i]), to, in ? vo[i] + k0 * 4 : OOB);
+    else load_lds<VEC>(rsrc_of(p[i] + k0 * ld), to, in ? vo[i] : OOB);
+  }
+};
 
 // Four consecutive k's of the lane's row (k-major) or column: k = 8 g + 4 hf
 // + j of the k range starting at kk (a multiple of 8) of the tile.  Both
@@ -182,15 +201,18 @@ __device__ __forceinline__ float epilogue(const GemmArgs& g, int64_t offC, int z
 }
 
 // One output tile (tm, tn) of batch entry zb over split zs of K.
-template <bool SMALL, int NS, bool AK, bool BKM, bool VEC, int EPI>
+template <F32Tile TILE, int NS, bool AK, bool BKM, bool VEC, int EPI>
 __device__ __forceinline__ void tile_f32(const GemmArgs& g, int tm, int tn, int zb, int zs, char* smem) {
-  using C = Cfg<SMALL>;
-  constexpr int R = C::R, BK = C::BK, KG = C::KG;
-  constexpr int PER = C::STAGE / (VEC ? 1024 : 256) / 4;  // loads per k-tile and wavefront
-  static_assert(PER * (NS - 2) <= 63, "vmcnt range");
+  using C = Cfg<TILE>;
+  constexpr int BM = C::BM, BN = C::BN, BK = C::BK, KG = C::KG, BLK = C::MB * C::NB;
+  using DA = DmaOp<BM, BK, AK, VEC>;
+  using DB = DmaOp<BN, BK, BKM, VEC>;
+  constexpr int PA = DA::N, PER = PA + DB::N;
+  constexpr int FIRST = TILE == T32x32 ? NS - 1 : NS;  // k-tiles requested ahead
+  static_assert(PER * (FIRST - 1) <= 63, "vmcnt range");
   const int lane = threadIdx.x & 63, hf = lane >> 5, rr = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m0 = tm * R, n0 = tn * R;
+  const int m0 = tm * BM, n0 = tn * BN;
   const int kbeg = zs * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
   const int64_t za = zb / g.zdiv, zr = zb % g.zdiv;
   const int nt = (kend - kbeg + BK - 1) / BK;
@@ -199,101 +221,179 @@ __device__ __forceinline__ void tile_f32(const GemmArgs& g, int tm, int tn, int 
   if constexpr (AK) A += (int64_t)m0 * g.lda; else A += m0;
   if constexpr (BKM) B += (int64_t)n0 * g.ldb; else B += n0;
   const int nk = kend - kbeg, nm = g.M - m0, nn = g.N - n0;
-  auto issue = [&](int t) {
-    char* d = smem + (t % NS) * C::STAGE;
-    dma_op<R, BK, AK, VEC>(A, g.lda, nm, t * BK, nk, d, wave, lane);
-    dma_op<R, BK, BKM, VEC>(B, g.ldb, nn, t * BK, nk, d + C::OP, wave, lane);
+  DA da;
+  DB db;
+  da.init(A, g.lda, nm, wave, lane);
+  db.init(B, g.ldb, nn, wave, lane);
+  // Load d (0 .. PER - 1) of k-tile t: A's, then B's.
+  auto load = [&](int t, int d, char* slot) {
+    if (d < PA) da.issue(d, g.lda, t * BK, nk, slot, wave);
+    else db.issue(d - PA, g.ldb, t * BK, nk, slot + C::A_BYTES, wave);
   };
 #pragma unroll
-  for (int t = 0; t < NS - 1; ++t)
-    if (t < nt) issue(t);
-  const int wm = SMALL ? 0 : (wave >> 1) * 32, wn = SMALL ? 0 : (wave & 1) * 32;
-  const int kw = SMALL ? wave * (BK / KG) : 0;  // the wavefront's k's of a k-tile
+  for (int t = 0; t < FIRST; ++t)
+    if (t < nt) {
+#pragma unroll
+      for (int d = 0; d < PER; ++d) load(t, d, smem + t * C::STAGE);
+    }
+  const int kg = wave / BLK, blk = wave % BLK;
+  const int wm = (blk / C::NB) * 32, wn = (blk % C::NB) * 32;
+  const int kw = kg * (BK / KG);  // the wavefront's k's of a k-tile
   // One accumulator per group of 8 k's in a k-tile, added at the end: a chain
   // of K / 8 additions per value instead of K / 2 (and, with one wavefront per
   // SIMD, MFMAs that do not wait for one another).
-  constexpr int NF = BK / KG / 8;
+  constexpr int NF = BK / KG / 8, NM = 4 * NF;
   f32x16_t accs[NF];
 #pragma unroll
   for (int s = 0; s < NF; ++s)
 #pragma unroll
     for (int r = 0; r < 16; ++r) accs[s][r] = 0.0f;
-  for (int t = 0; t < nt; ++t) {
-    // k-tile t has landed for everyone, and nobody reads k-tile t - 1 any more.
-    wait_after<PER, NS - 2>(min(nt - 1, t + NS - 2) - t);
-    ring_barrier();
-    if (t + NS - 1 < nt) issue(t + NS - 1);
-    const uint32_t At = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem +
-                        (t % NS) * C::STAGE;
-    const uint32_t Bt = At + C::OP;
-    // All of the k-tile's fragments first, so that one wavefront per SIMD
-    // waits for LDS once per k-tile and not once per four MFMAs.
-    f32x4_t a[NF], b[NF];
+  // Few k-tiles and one wavefront per SIMD: each k-tile's MFMAs start as soon
+  // as it has landed.  (The loop below took 0.3 us more per product of two
+  // layers of width 128 at 64 tokens, 164 -> 175 us.)
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  if constexpr (TILE == T32x32) {
+    for (int t = 0; t < nt; ++t) {
+      // k-tile t has landed for everyone, and nobody reads k-tile t - 1 any
+      // more.
+      wait_after<PER, NS - 2>(min(nt - 1, t + NS - 2) - t);
+      ring_barrier();
+      if (t + NS - 1 < nt) {
 #pragma unroll
-    for (int s = 0; s < NF; ++s) {
-      a[s] = frag4<R, AK>(At, wm + rr, kw + 8 * s, hf);
-      b[s] = frag4<R, BKM>(Bt, wn + rr, kw + 8 * s, hf);
+        for (int d = 0; d < PER; ++d) load(t + NS - 1, d, smem + ((t + NS - 1) % NS) * C::STAGE);
+      }
+      // All of the k-tile's fragments first, so that the wavefront waits for
+      // LDS once per k-tile and not once per four MFMAs.
+      const uint32_t slot = lds0 + (t % NS) * C::STAGE;
+      f32x4_t a[NF], b[NF];
+#pragma unroll
+      for (int s = 0; s < NF; ++s) {
+        a[s] = frag4<BM, AK>(slot, wm + rr, kw + 8 * s, hf);
+        b[s] = frag4<BN, BKM>(slot + C::A_BYTES, wn + rr, kw + 8 * s, hf);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int s = 0; s < NF; ++s)
+          accs[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][j], b[s][j], accs[s], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    // While the MFMAs of k-tile t run, the fragments of k-tile t + 1 are read
+    // (two register sets) and k-tile t + NS is requested, each between two
+    // MFMAs, so that a wavefront alone on its SIMD keeps the matrix core busy.
+    // (Read and requested ahead of the MFMAs, two wavefronts per SIMD fell into
+    // step and waited together: 57% of the matrix rate, see the figures above.)
+    // At the barrier of step t everyone holds k-tile t's fragments, so its slot
+    // takes k-tile t + NS, and k-tile t + 1 has landed.
+    f32x4_t fa[2][NF], fb[2][NF];
+    auto read = [&](auto set, auto fc, uint32_t slot) {
+      constexpr int S = decltype(set)::value, F = decltype(fc)::value, s = F / 2;
+      if constexpr (F % 2 == 0) fa[S][s] = frag4<BM, AK>(lds0 + slot, wm + rr, kw + 8 * s, hf);
+      else fb[S][s] = frag4<BN, BKM>(lds0 + slot + C::A_BYTES, wn + rr, kw + 8 * s, hf);
+    };
+    wait_after<PER, NS - 1>(min(nt - 1, NS - 1));
+    ring_barrier();
+    static_for<0, 2 * NF>([&](auto f) { read(std::integral_constant<int, 0>(), f, 0); });
+    uint32_t slot = 0;
+    // ISSUE: 1 = request k-tile t + NS between the MFMAs, 0 = nothing left to
+    // request, 2 = request it if there is one.
+    auto step = [&](auto par, auto issue_c, int t) {
+      constexpr int cur = decltype(par)::value;
+      constexpr int ISSUE = decltype(issue_c)::value;
+      using Next = std::integral_constant<int, cur ^ 1>;
+      if constexpr (ISSUE == 1) wait_vm<PER * (NS - 2)>();
+      else wait_after<PER, NS - 2>(max(0, min(nt - 1, t + NS - 1) - (t + 1)));
+      ring_barrier();
+      char* const free_slot = smem + slot;
+      // (after the last k-tile these reads fetch a stale slot, never used)
+      slot = slot == (NS - 1) * C::STAGE ? 0 : slot + C::STAGE;
+      if (ISSUE == 2 && t + NS < nt) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int d = 0; d < PER; ++d) load(t + NS, d, free_slot);
+      }
+      static_for<0, NM>([&](auto mc) {
+        constexpr int m = decltype(mc)::value, s = m % NF, j = m / NF;
+        accs[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[cur][s][j], fb[cur][s][j], accs[s], 0, 0, 0);
+        if constexpr (m % 2 == 0) read(Next(), std::integral_constant<int, m / 2>(), slot);
+        if constexpr (ISSUE == 1) {
 #pragma unroll
-      for (int s = 0; s < NF; ++s)
-        accs[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][j], b[s][j], accs[s], 0, 0, 0);
+          for (int d = 0; d < PER; ++d)
+            if (d * NM / PER == m) load(t + NS, d, free_slot);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    int t = 0;
+    for (; t + 1 + NS < nt; t += 2) {
+      step(I0(), I1(), t);
+      step(I1(), I1(), t + 1);
+    }
+    for (; t < nt; t += 2) {
+      step(I0(), I2(), t);
+      if (t + 1 < nt) step(I1(), I0(), t + 1);
+    }
   }
   f32x16_t acc = accs[0];
 #pragma unroll
   for (int s = 1; s < NF; ++s) acc += accs[s];
-  // The four wavefronts' k sums, added in wavefront order; wavefront w then
-  // owns accumulator registers 4 w .. 4 w + 3 (rows 8 w + 4 hf + 0..3).
-  if constexpr (SMALL) {
+  const int64_t offC = za * g.sC1 + zr * g.sC2;
+  const int n = n0 + wn + rr;
+  // The k groups' sums, added in their order; each of a block's wavefronts
+  // then owns NR accumulator registers (register r: row 8 (r / 4) + 4 hf +
+  // r % 4 of the block).
+  constexpr int NR = 16 / KG;
+  float v[NR];
+  if constexpr (KG > 1) {
     __syncthreads();  // the ring becomes the exchange area: [wave][16][64]
     float* ex = (float*)smem;
 #pragma unroll
     for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = acc[r];
     __syncthreads();
-    float v[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float* p = ex + (4 * wave + j) * 64 + lane;
-      v[j] = ((p[0] + p[1024]) + p[2048]) + p[3072];
-    }
-    const int64_t offC = za * g.sC1 + zr * g.sC2;
-    const int n = n0 + rr, mb = m0 + 8 * wave + 4 * hf;
-    const float cs = epilogue<EPI, 4>(g, offC, zs, [&](int j) { return mb + j; }, n, v);
-    if (g.colpart) {  // column sums of the tile's 32 rows, in a fixed order
-      __syncthreads();
-      ex[(wave * 2 + hf) * 32 + rr] = cs;
-      __syncthreads();
-      if (threadIdx.x < 32 && n < g.N) {
-        float s = ex[rr];
+    for (int j = 0; j < NR; ++j) {
+      const float* p = ex + (blk * 16 + NR * kg + j) * 64 + lane;
+      v[j] = p[0];
 #pragma unroll
-        for (int i = 1; i < 8; ++i) s += ex[i * 32 + rr];
-        g.colpart[(zb / g.zdiv) * g.cp_batch + (int64_t)tm * g.cp_ld + (zb % g.zdiv) * g.sC2 + n] = s;
-      }
+      for (int k = 1; k < KG; ++k) v[j] += p[k * BLK * 1024];
     }
   } else {
-    const int64_t offC = za * g.sC1 + zr * g.sC2;
-    const int n = n0 + wn + rr, mb = m0 + wm + 4 * hf;
-    float v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = acc[r];
-    float cs = epilogue<EPI, 16>(
-        g, offC, zs, [&](int r) { return mb + 8 * (r >> 2) + (r & 3); }, n, v);
-    if (g.colpart) {  // column sums per 32-row block: both lane halves' rows
-      cs += __shfl_xor(cs, 32, 64);
-      const int blk = (m0 + wm) / 32;
-      if (hf == 0 && n < g.N && m0 + wm < g.M)
-        g.colpart[(zb / g.zdiv) * g.cp_batch + (int64_t)blk * g.cp_ld + (zb % g.zdiv) * g.sC2 + n] = cs;
+  }
+  const int mb = m0 + wm + 4 * hf;
+  const float cs = epilogue<EPI, NR>(
+      g, offC, zs, [&](int j) { return mb + 8 * ((NR * kg + j) >> 2) + (j & 3); }, n, v);
+  if (g.colpart) {  // column sums per block of 32 rows, in a fixed order
+    float* P = g.colpart + (zb / g.zdiv) * g.cp_batch + (zb % g.zdiv) * g.sC2;
+    if constexpr (KG > 1) {
+      float* ex = (float*)smem;
+      __syncthreads();
+      ex[((blk * KG + kg) * 2 + hf) * 32 + rr] = cs;
+      __syncthreads();
+      if (kg == 0 && hf == 0 && n < g.N && m0 + wm < g.M) {
+        const float* p = ex + blk * KG * 64 + rr;
+        float sum = p[0];
+#pragma unroll
+        for (int i = 1; i < 2 * KG; ++i) sum += p[i * 32];
+        P[(int64_t)((m0 + wm) / 32) * g.cp_ld + n] = sum;
+      }
+    } else {
+      const float sum = cs + __shfl_xor(cs, 32, 64);
+      if (hf == 0 && n < g.N && m0 + wm < g.M) P[(int64_t)((m0 + wm) / 32) * g.cp_ld + n] = sum;
     }
   }
 }
 
-template <bool SMALL, bool VEC>
+template <F32Tile T, bool VEC>
 struct Ring {
-  // 4-byte loads: four slots keep the outstanding count within vmcnt's range
-  static constexpr int NS = SMALL && VEC ? 8 : 4;
-  static constexpr int LDS = NS * Cfg<SMALL>::STAGE;
+  // 4-byte loads: as many slots as keep the outstanding count within vmcnt's
+  // range
+  static constexpr int NS = T == T32x32 && VEC ? 8 : 4;
+  static constexpr int LDS = NS * Cfg<T>::STAGE;
 };
 
 // Consecutive work-groups go round robin over the 8 XCDs: each XCD takes a
@@ -308,14 +408,14 @@ __device__ __forceinline__ void tile_of(int bid, int nbm, int nbn, int& tm, int&
   tn = r / size;
 }
 
-template <bool SMALL, bool AK, bool BKM, bool VEC, int EPI>
+template <F32Tile T, bool AK, bool BKM, bool VEC, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  using Rg = Ring<SMALL, VEC>;
+  using Rg = Ring<T, VEC>;
   __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
-  constexpr int R = Cfg<SMALL>::R;
+  constexpr int BM = Cfg<T>::BM, BN = Cfg<T>::BN;
   int tm, tn;
-  tile_of(blockIdx.x, (g.M + R - 1) / R, (g.N + R - 1) / R, tm, tn);
-  tile_f32<SMALL, Rg::NS, AK, BKM, VEC, EPI>(g, tm, tn, blockIdx.z / g.ksplit, blockIdx.z % g.ksplit,
+  tile_of(blockIdx.x, (g.M + BM - 1) / BM, (g.N + BN - 1) / BN, tm, tn);
+  tile_f32<T, Rg::NS, AK, BKM, VEC, EPI>(g, tm, tn, blockIdx.z / g.ksplit, blockIdx.z % g.ksplit,
                                              smem);
 }
 
@@ -324,19 +424,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 struct Attn3 {
   GemmArgs p[3];
 };
-template <bool SMALL, bool VEC>
+template <F32Tile T, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_attn_bwd_kernel(Attn3 a) {
-  using Rg = Ring<SMALL, VEC>;
+  using Rg = Ring<T, VEC>;
   __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
-  constexpr int R = Cfg<SMALL>::R;
+  constexpr int R = Cfg<T>::BM;
+  static_assert(R == Cfg<T>::BN, "square tiles");
   const int nbn = (a.p[0].N + R - 1) / R;
   const int tm = blockIdx.x / nbn, tn = blockIdx.x % nbn;
   if (blockIdx.y == 1)
-    tile_f32<SMALL, Rg::NS, true, false, VEC, EPI_STORE>(a.p[1], tm, tn, blockIdx.z, 0, smem);
+    tile_f32<T, Rg::NS, true, false, VEC, EPI_STORE>(a.p[1], tm, tn, blockIdx.z, 0, smem);
   else if (blockIdx.y == 0)
-    tile_f32<SMALL, Rg::NS, false, false, VEC, EPI_STORE>(a.p[0], tm, tn, blockIdx.z, 0, smem);
+    tile_f32<T, Rg::NS, false, false, VEC, EPI_STORE>(a.p[0], tm, tn, blockIdx.z, 0, smem);
   else
-    tile_f32<SMALL, Rg::NS, false, false, VEC, EPI_STORE>(a.p[2], tm, tn, blockIdx.z, 0, smem);
+    tile_f32<T, Rg::NS, false, false, VEC, EPI_STORE>(a.p[2], tm, tn, blockIdx.z, 0, smem);
 }
 
 // A layer's weight gradients in one launch: work-group b serves problem q
@@ -348,11 +449,12 @@ struct WgradGroup {
   int n;
   TailJobs tail;
 };
-template <bool SMALL>
+template <F32Tile T>
 __global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
-  using Rg = Ring<SMALL, true>;
+  using Rg = Ring<T, true>;
   __shared__ __attribute__((aligned(1024))) char smem[Rg::LDS];
-  constexpr int R = Cfg<SMALL>::R;
+  constexpr int R = Cfg<T>::BM;
+  static_assert(R == Cfg<T>::BN, "square tiles");
   const int b = blockIdx.x;
   if (b >= w.blk0[GEMM_GROUP_MAX]) {
     tail_unit<8>(tail_arg(offsetof(WgradGroup, tail)), (b - w.blk0[GEMM_GROUP_MAX]) * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63);
@@ -375,7 +477,7 @@ __global__ __launch_bounds__(256) void gemm_f32_wgrad_kernel(WgradGroup w) {
   const int lb = b - w.blk0[q], zs = lb / (nbm * nbn);
   int tm, tn;
   tile_of(lb - zs * nbm * nbn, nbm, nbn, tm, tn);
-  tile_f32<SMALL, Rg::NS, false, false, true, EPI_PARTIAL>(g, tm, tn, 0, zs, smem);
+  tile_f32<T, Rg::NS, false, false, true, EPI_PARTIAL>(g, tm, tn, 0, zs, smem);
 }
 
 // out[q] = the fixed-order sum of problem q's splits; then the tail, four
@@ -428,29 +530,43 @@ bool fits(const GemmArgs& g) {
   const int64_t k = g.K;
   return std::max(g.lda, g.ldb) < ((int64_t)1 << 25) && k * 4 < ((int64_t)1 << 30);
 }
-int64_t tiles_of(const GemmArgs& g, int r) {
-  return (int64_t)((g.M + r - 1) / r) * ((g.N + r - 1) / r);
+int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
+  return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+}
+// 32 x 32 tiles below SMALL_TILES tiles of 64 x 64.  Otherwise a CU works
+// through its share of the tiles two or three at a time, and the fullest CU
+// is the time: 64 x 32 tiles (5% slower for their size) where they divide more
+// evenly.
+F32Tile f32_tile(const GemmArgs& g, int64_t batch) {
+  constexpr int64_t CUS = 256;
+  const int64_t t64 = tiles_of(g, 64, 64) * batch, t32 = tiles_of(g, 64, 32) * batch;
+  if (t64 < SMALL_TILES) return T32x32;
+  return ((t32 + CUS - 1) / CUS) * 21 < ((t64 + CUS - 1) / CUS) * 40 ? T64x32 : T64x64;
 }
 
 template <bool AK, bool BKM, int EPI>
 hipError_t launch(const GemmArgs& g, int batch, hipStream_t st) {
   const bool vec = vec_ok(g, AK, BKM);
-  const bool small = tiles_of(g, 64) * batch * g.ksplit < SMALL_TILES;
-  const dim3 grid((unsigned)tiles_of(g, small ? 32 : 64), 1, (unsigned)(batch * g.ksplit));
+  const F32Tile t = f32_tile(g, (int64_t)batch * g.ksplit);
+  auto grid = [&](int bm, int bn) {
+    return dim3((unsigned)tiles_of(g, bm, bn), 1, (unsigned)(batch * g.ksplit));
+  };
   if (vec) {
-    if (small)
-      hipLaunchKernelGGL((gemm_f32_kernel<true, AK, BKM, true, EPI>), grid, dim3(256), 0, st, g);
+    if (t == T32x32)
+      hipLaunchKernelGGL((gemm_f32_kernel<T32x32, AK, BKM, true, EPI>), grid(32, 32), dim3(256), 0, st, g);
+    else if (t == T64x32)
+      hipLaunchKernelGGL((gemm_f32_kernel<T64x32, AK, BKM, true, EPI>), grid(64, 32), dim3(256), 0, st, g);
     else
-      hipLaunchKernelGGL((gemm_f32_kernel<false, AK, BKM, true, EPI>), grid, dim3(256), 0, st, g);
+      hipLaunchKernelGGL((gemm_f32_kernel<T64x64, AK, BKM, true, EPI>), grid(64, 64), dim3(256), 0, st, g);
     return hipGetLastError();
   }
   // Operands with rows that are not 16-byte aligned: the score matrix of a
   // sequence length that is not a multiple of 4 (EPI_STORE, P V).
   if constexpr (EPI == EPI_STORE && AK && !BKM) {
-    if (small)
-      hipLaunchKernelGGL((gemm_f32_kernel<true, AK, BKM, false, EPI>), grid, dim3(256), 0, st, g);
+    if (t == T32x32)
+      hipLaunchKernelGGL((gemm_f32_kernel<T32x32, AK, BKM, false, EPI>), grid(32, 32), dim3(256), 0, st, g);
     else
-      hipLaunchKernelGGL((gemm_f32_kernel<false, AK, BKM, false, EPI>), grid, dim3(256), 0, st, g);
+      hipLaunchKernelGGL((gemm_f32_kernel<T64x64, AK, BKM, false, EPI>), grid(64, 64), dim3(256), 0, st, g);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -482,16 +598,16 @@ hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmA
   if (!fits(dv) || !fits(dq) || !fits(dk))
     return hipErrorInvalidValue;
   const bool vec = vec_ok(dv, false, false) && vec_ok(dq, true, false) && vec_ok(dk, false, false);
-  const bool small = tiles_of(dv, 64) * batch * 3 < SMALL_TILES;
-  const dim3 grid((unsigned)tiles_of(dv, small ? 32 : 64), 3, (unsigned)batch);
+  const bool small = tiles_of(dv, 64, 64) * batch * 3 < SMALL_TILES;
+  const dim3 grid((unsigned)tiles_of(dv, small ? 32 : 64, small ? 32 : 64), 3, (unsigned)batch);
   if (small && vec)
-    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<true, true>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<T32x32, true>), grid, dim3(256), 0, st, a);
   else if (small)
-    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<true, false>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<T32x32, false>), grid, dim3(256), 0, st, a);
   else if (vec)
-    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<false, true>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<T64x64, true>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<false, false>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<T64x64, false>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -520,14 +636,14 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int
     // one split writes the gradient itself
     if (g.ksplit == 1) g.C = out[q];
     w.p[q] = g;
-    t64 += tiles_of(g, 64) * g.ksplit;
+    t64 += tiles_of(g, 64, 64) * g.ksplit;
   }
   const bool small = t64 < SMALL_TILES;
   int64_t blocks = 0, rblocks = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = w.p[q];
     w.blk0[q] = (int)blocks;
-    blocks += tiles_of(g, small ? 32 : 64) * g.ksplit;
+    blocks += tiles_of(g, small ? 32 : 64, small ? 32 : 64) * g.ksplit;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     if (g.ksplit > 1) {
       const int j = rd.n++;
@@ -548,9 +664,9 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int
   (ks > 1 ? rblocks : blocks) += (t.units + 3) / 4;
   if (blocks >= ((int64_t)1 << 31) || rblocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   if (small)
-    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<T32x32>), dim3((unsigned)blocks), dim3(256), 0, st, w);
   else
-    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, st, w);
+    hipLaunchKernelGGL((gemm_f32_wgrad_kernel<T64x64>), dim3((unsigned)blocks), dim3(256), 0, st, w);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || ks == 1) return e;
   hipLaunchKernelGGL(gemm_f32_group_reduce_kernel, dim3((unsigned)rblocks), dim3(256), 0, st, rd);
