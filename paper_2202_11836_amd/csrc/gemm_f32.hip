@@ -419,8 +419,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
                                              smem);
 }
 
-// The three contractions of the attention backward in one launch (grid y):
-// p[0] dV = P^T dC, p[1] dQ = dS K, p[2] dK = dS^T Q, per (batch, head).
+// Contractions of the attention backward in one launch (grid y), per (batch,
+// head): p[0] dV = P^T dC, p[1] dK = dS^T Q, and p[2] dQ = dS K.
 struct Attn3 {
   GemmArgs p[3];
 };
@@ -432,12 +432,12 @@ __global__ __launch_bounds__(256) void gemm_f32_attn_bwd_kernel(Attn3 a) {
   static_assert(R == Cfg<T>::BN, "square tiles");
   const int nbn = (a.p[0].N + R - 1) / R;
   const int tm = blockIdx.x / nbn, tn = blockIdx.x % nbn;
-  if (blockIdx.y == 1)
-    tile_f32<T, Rg::NS, true, false, VEC, EPI_STORE>(a.p[1], tm, tn, blockIdx.z, 0, smem);
+  if (blockIdx.y == 2)
+    tile_f32<T, Rg::NS, true, false, VEC, EPI_STORE>(a.p[2], tm, tn, blockIdx.z, 0, smem);
   else if (blockIdx.y == 0)
     tile_f32<T, Rg::NS, false, false, VEC, EPI_STORE>(a.p[0], tm, tn, blockIdx.z, 0, smem);
   else
-    tile_f32<T, Rg::NS, false, false, VEC, EPI_STORE>(a.p[2], tm, tn, blockIdx.z, 0, smem);
+    tile_f32<T, Rg::NS, false, false, VEC, EPI_STORE>(a.p[1], tm, tn, blockIdx.z, 0, smem);
 }
 
 // A layer's weight gradients in one launch: work-group b serves problem q
@@ -589,17 +589,20 @@ hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi
   return hipErrorInvalidValue;
 }
 
-hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmArgs& dk, int batch,
+hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dk, const GemmArgs* dq, int batch,
                              hipStream_t st) {
   if (dv.M <= 0 || batch <= 0) return hipSuccess;
-  Attn3 a = {{dv, dq, dk}};
-  for (const GemmArgs& g : a.p)
-    if (g.M != dv.M || g.N != dv.N || g.ksplit != 1) return hipErrorInvalidValue;
-  if (!fits(dv) || !fits(dq) || !fits(dk))
-    return hipErrorInvalidValue;
-  const bool vec = vec_ok(dv, false, false) && vec_ok(dq, true, false) && vec_ok(dk, false, false);
-  const bool small = tiles_of(dv, 64, 64) * batch * 3 < SMALL_TILES;
-  const dim3 grid((unsigned)tiles_of(dv, small ? 32 : 64, small ? 32 : 64), 3, (unsigned)batch);
+  const unsigned n = dq ? 3 : 2;
+  Attn3 a = {{dv, dk, dq ? *dq : dk}};
+  bool vec = true;
+  for (unsigned i = 0; i < n; ++i) {
+    const GemmArgs& g = a.p[i];
+    if (g.M != dv.M || g.N != dv.N || g.ksplit != 1 || !fits(g)) return hipErrorInvalidValue;
+    vec = vec && vec_ok(g, i == 2, false);
+  }
+  const bool small = tiles_of(dv, 64, 64) * batch * n < SMALL_TILES;
+  const int r = small ? 32 : 64;
+  const dim3 grid((unsigned)tiles_of(dv, r, r), n, (unsigned)batch);
   if (small && vec)
     hipLaunchKernelGGL((gemm_f32_attn_bwd_kernel<T32x32, true>), grid, dim3(256), 0, st, a);
   else if (small)

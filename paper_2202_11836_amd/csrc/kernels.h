@@ -106,9 +106,9 @@ inline GemmArgs gemm_split(GemmArgs g, int ks) {
 // EPI_RESID.
 hipError_t gemm_f32(const GemmArgs& g, bool a_kmajor, bool b_kmajor, GemmEpi epi, int batch,
                     hipStream_t st);
-// The attention backward's dV = P^T dC, dQ = dS K and dK = dS^T Q of every
-// (batch, head) in one launch (equal M and N, EPI_STORE).
-hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dq, const GemmArgs& dk, int batch,
+// The attention backward's dV = P^T dC, dK = dS^T Q and, unless null, dQ = dS K
+// of every (batch, head) in one launch (equal M and N, EPI_STORE).
+hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dk, const GemmArgs* dq, int batch,
                              hipStream_t st);
 
 // Up to GEMM_GROUP_MAX weight-gradient GEMMs in one launch, stream-K: each
@@ -299,3 +299,27 @@ hipError_t attn_forward(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward_dq(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward_dkdv(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward(const AttnArgs& a, hipStream_t st);
+
+// ---------------------------------------------------------------------------
+// Attention of fp32 stages with S <= ATTN_F32_MAX_S (attn_f32.hip).
+//   qkv [B*S, 3h], mask [B, S] as above; P, dS: [B*H, S, S]
+//   forward: P = masked softmax(scale Q K^T), out = P V (row stride ldo)
+//   backward_rows: dS = scale P (dC V^T - rowsum(P dC V^T)), out = dQ = dS K,
+//   and its column sums per 32-row block of each sequence,
+//   colpart[b * ceil(S / 32) + s / 32][3h] (the first h columns)
+// ---------------------------------------------------------------------------
+constexpr int ATTN_F32_MAX_S = 512;
+struct AttnF32Args {
+  const float* qkv;
+  const uint8_t* mask;
+  float* P;
+  const float* dC;
+  float* dS;
+  float* out;
+  int64_t ldo;
+  float* colpart;
+  int S, H, h;
+  float scale;
+};
+hipError_t attn_f32_forward(const AttnF32Args& a, int B, hipStream_t st);
+hipError_t attn_f32_backward_rows(const AttnF32Args& a, int B, hipStream_t st);

@@ -560,6 +560,20 @@ AttnArgs attn_args(stage_t* s, const bf16_t* qkv, bf16_t* out, float* lse) {
   return a;
 }
 
+AttnF32Args attn_f32_args(stage_t* s, const float* qkv, void* P, float* out, int64_t ldo) {
+  AttnF32Args a{};
+  a.qkv = qkv;
+  a.mask = s->mask;
+  a.P = (float*)P;
+  a.out = out;
+  a.ldo = ldo;
+  a.S = s->S;
+  a.H = s->H;
+  a.h = s->h;
+  a.scale = 1.0f / sqrtf((float)HEAD_DIM);
+  return a;
+}
+
 template <typename T>
 stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y) {
   const int B = s->B, S = s->S, h = s->h, H = s->H, f = s->f;
@@ -615,30 +629,33 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
         AttnArgs aa = attn_args(s, (const bf16_t*)QKV, (bf16_t*)v.C, v.lse);
         aa.out_lo = (bf16_t*)v.Clo;
         SITE(ATTN_FWD, attn_forward(aa, st));
+      } else if (S <= ATTN_F32_MAX_S) {
+        SITE(ATTN_FWD, attn_f32_forward(attn_f32_args(s, QKV, v.P, (float*)v.C, h), B, st));
       } else {
-      // scores[b, j] = Q_bj K_bj^T  (fp32)
-      {
-        GemmArgs g = gemm_args(QKV, 3 * h, QKV + h, 3 * h, s->scores, S, S, S, HEAD_DIM);
-        g.zdiv = H;
-        g.sA1 = g.sB1 = (int64_t)S * 3 * h;
-        g.sA2 = g.sB2 = HEAD_DIM;
-        g.sC1 = (int64_t)H * S * S;
-        g.sC2 = (int64_t)S * S;
-        SITE(SCORES_FWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
-      }
-      SITE(SOFTMAX_FWD, softmax_fwd<T>(s->scores, s->mask, (T*)v.P, BH, H, S, S, scale, st));
-      // C[b, :, j] = P_bj V_bj
-      {
-        GemmArgs g = gemm_args(v.P, S, QKV + 2 * h, 3 * h, v.C, h, S, HEAD_DIM, S);
-        g.zdiv = H;
-        g.sA1 = (int64_t)H * S * S;
-        g.sA2 = (int64_t)S * S;
-        g.sB1 = (int64_t)S * 3 * h;
-        g.sB2 = HEAD_DIM;
-        g.sC1 = (int64_t)S * h;
-        g.sC2 = HEAD_DIM;
-        SITE(CTX_FWD, gemm_f32(g, true, false, EPI_STORE, BH, st));
-      }
+        // Long sequences: the score matrix in memory.
+        // scores[b, j] = Q_bj K_bj^T  (fp32)
+        {
+          GemmArgs g = gemm_args(QKV, 3 * h, QKV + h, 3 * h, s->scores, S, S, S, HEAD_DIM);
+          g.zdiv = H;
+          g.sA1 = g.sB1 = (int64_t)S * 3 * h;
+          g.sA2 = g.sB2 = HEAD_DIM;
+          g.sC1 = (int64_t)H * S * S;
+          g.sC2 = (int64_t)S * S;
+          SITE(SCORES_FWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
+        }
+        SITE(SOFTMAX_FWD, softmax_fwd<T>(s->scores, s->mask, (T*)v.P, BH, H, S, S, scale, st));
+        // C[b, :, j] = P_bj V_bj
+        {
+          GemmArgs g = gemm_args(v.P, S, QKV + 2 * h, 3 * h, v.C, h, S, HEAD_DIM, S);
+          g.zdiv = H;
+          g.sA1 = (int64_t)H * S * S;
+          g.sA2 = (int64_t)S * S;
+          g.sB1 = (int64_t)S * 3 * h;
+          g.sB2 = HEAD_DIM;
+          g.sC1 = (int64_t)S * h;
+          g.sC2 = HEAD_DIM;
+          SITE(CTX_FWD, gemm_f32(g, true, false, EPI_STORE, BH, st));
+        }
       }
       // tmp = C W_o^T (fp32);  H1 = LN(X + tmp + b_o)
       int np = 1;
@@ -765,21 +782,31 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
         GemmArgs g = gemm_args(dZ1, h, p[STAGE_W_O], h, dC, h, Tn, h, h);
         SITE(OUT_DGRAD, gemm_f32(g, true, false, EPI_STORE, 1, st));
       }
-      // dP[b, j] = dC_bj V_bj^T (fp32, into the score buffer)
-      {
-        GemmArgs g = gemm_args(dC, h, QKV + 2 * h, 3 * h, s->scores, S, S, S, HEAD_DIM);
-        g.zdiv = H;
-        g.sA1 = (int64_t)S * h;
-        g.sA2 = HEAD_DIM;
-        g.sB1 = (int64_t)S * 3 * h;
-        g.sB2 = HEAD_DIM;
-        g.sC1 = (int64_t)H * S * S;
-        g.sC2 = (int64_t)S * S;
-        SITE(DP_BWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
+      const bool rows = S <= ATTN_F32_MAX_S;
+      if (rows) {
+        // dS, dQ and its column sums
+        AttnF32Args aa = attn_f32_args(s, QKV, v.P, dQKV, 3 * h);
+        aa.dC = dC;
+        aa.dS = (float*)s->dS;
+        aa.colpart = s->colpart_qkv;
+        SITE(ATTN_DQ, attn_f32_backward_rows(aa, B, st));
+      } else {
+        // dP[b, j] = dC_bj V_bj^T (fp32, into the score buffer)
+        {
+          GemmArgs g = gemm_args(dC, h, QKV + 2 * h, 3 * h, s->scores, S, S, S, HEAD_DIM);
+          g.zdiv = H;
+          g.sA1 = (int64_t)S * h;
+          g.sA2 = HEAD_DIM;
+          g.sB1 = (int64_t)S * 3 * h;
+          g.sB2 = HEAD_DIM;
+          g.sC1 = (int64_t)H * S * S;
+          g.sC2 = (int64_t)S * S;
+          SITE(DP_BWD, gemm_f32(g, true, true, EPI_STORE, BH, st));
+        }
+        // dS = scale * P * (dP - rowsum(dP * P))
+        SITE(SOFTMAX_BWD, softmax_bwd<T>(s->scores, (const T*)v.P, (T*)s->dS, BH, S, S, scale, st));
       }
-      // dS = scale * P * (dP - rowsum(dP * P))
-      SITE(SOFTMAX_BWD, softmax_bwd<T>(s->scores, (const T*)v.P, (T*)s->dS, BH, S, S, scale, st));
-      // dV_bj = P_bj^T dC_bj, dQ_bj = dS_bj K_bj, dK_bj = dS_bj^T Q_bj, and
+      // dV_bj = P_bj^T dC_bj, dK_bj = dS_bj^T Q_bj (and dQ_bj = dS_bj K_bj), and
       // their column sums per 32 rows of each sequence (db_qkv)
       const int nqb = (S + 31) / 32;
       {
@@ -798,9 +825,9 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
           return g;
         };
         const int64_t sq = (int64_t)S * 3 * h;
+        const GemmArgs dq = prob(s->dS, QKV + h, 3 * h, sq, 0);
         SITE(DV_BWD, gemm_f32_attn_bwd(prob(v.P, dC, h, (int64_t)S * h, 2),
-                                       prob(s->dS, QKV + h, 3 * h, sq, 0),
-                                       prob(s->dS, QKV, 3 * h, sq, 1), BH, st));
+                                       prob(s->dS, QKV, 3 * h, sq, 1), rows ? nullptr : &dq, BH, st));
       }
       tail.col[tail.ncol++] = ColJob{s->colpart_qkv, B * nqb, 1, 3 * h,
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
