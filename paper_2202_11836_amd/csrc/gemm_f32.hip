@@ -6,7 +6,8 @@
 // fits underneath if the loads are requested early enough.  k-tiles go from
 // HBM straight into a ring of LDS slots with direct-to-LDS buffer loads, up
 // to NS of them in flight, one barrier per k-tile; each wavefront owns
-// one 32 x 32 output block.  Three work-group shapes:
+// one 32 x 32 output block.  Three work-group shapes (and one more for the
+// smallest outputs, gemm_f32_16_kernel):
 //   64 x 64, 2 x 2 wavefronts, k-tiles of 32, four slots (64 KB, two
 //     work-groups per CU);
 //   64 x 32, 2 x 1 wavefronts times two that split every k-tile by k, four
@@ -18,8 +19,8 @@
 //     memory latency are the time.
 // Measured against a vector-ALU kernel (64 x 64 tiles, 4 x 4 outputs per
 // thread, one global load -> LDS -> barrier per 16 k): a BERT-base layer at 16 x
-// 128 tokens, forward and backward, 3689 -> 948 us; two layers of width 128 at
-// 64 tokens 1086 -> 164 us.  Largest relative error against 64 bits 1.2e-6 ->
+// 128 tokens, forward and backward, 3689 -> 910 us; two layers of width 128 at
+// 64 tokens 1086 -> 128 us.  Largest relative error against 64 bits 1.2e-6 ->
 // 7e-7 and 3.2e-7 -> 2.3e-7.
 #include <algorithm>
 #include <type_traits>
@@ -282,8 +283,8 @@ __device__ __forceinline__ void tile_f32(const GemmArgs& g, int tm, int tn, int 
     // While the MFMAs of k-tile t run, the fragments of k-tile t + 1 are read
     // (two register sets) and k-tile t + NS is requested, each between two
     // MFMAs, so that a wavefront alone on its SIMD keeps the matrix core busy.
-    // (Read and requested ahead of the MFMAs, two wavefronts per SIMD fell into
-    // step and waited together: 57% of the matrix rate, see the figures above.)
+    // (With reads and requests ahead of the MFMAs a BERT-base layer at 16 x 128
+    // took 967 us instead of 910.)
     // At the barrier of step t everyone holds k-tile t's fragments, so its slot
     // takes k-tile t + NS, and k-tile t + 1 has landed.
     f32x4_t fa[2][NF], fb[2][NF];
@@ -388,14 +389,6 @@ __device__ __forceinline__ void tile_f32(const GemmArgs& g, int tm, int tn, int 
   }
 }
 
-template <F32Tile T, bool VEC>
-struct Ring {
-  // 4-byte loads: as many slots as keep the outstanding count within vmcnt's
-  // range
-  static constexpr int NS = T == T32x32 && VEC ? 8 : 4;
-  static constexpr int LDS = NS * Cfg<T>::STAGE;
-};
-
 // Consecutive work-groups go round robin over the 8 XCDs: each XCD takes a
 // contiguous range of tiles, walked in groups of 8 tile-rows that share B.
 __device__ __forceinline__ void tile_of(int bid, int nbm, int nbn, int& tm, int& tn) {
@@ -407,6 +400,81 @@ __device__ __forceinline__ void tile_of(int bid, int nbm, int nbn, int& tm, int&
   tm = first + r % size;
   tn = r / size;
 }
+
+// One 16 x 16 output tile (v_mfma_f32_16x16x4_f32, four wavefronts splitting
+// each k-tile of 64 by k), for outputs so small that even 32 x 32 tiles leave
+// most CUs idle: a wavefront's chain of MFMAs is a quarter as long (K = 512: 1024
+// cycles against 4096).  64 x 128 x 512 7.4 -> 4.6 us, two layers of width 128
+// at 64 tokens 156 -> 128 us a step.  Operands 16-byte aligned, batch 1, no
+// column sums.
+constexpr int T16_NS = 8;
+constexpr int T16_STAGE = 2 * 16 * 64 * 4;
+template <bool AK, bool BKM, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_16_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) char smem[T16_NS * T16_STAGE];
+  constexpr int NS = T16_NS, BK = 64, OP = T16_STAGE / 2;
+  const int lane = threadIdx.x & 63, kq = lane >> 4, rr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tm, tn;
+  tile_of(blockIdx.x, (g.M + 15) / 16, (g.N + 15) / 16, tm, tn);
+  const int m0 = tm * 16, n0 = tn * 16, nt = (g.K + BK - 1) / BK;
+  DmaOp<16, BK, AK, true> da;
+  DmaOp<16, BK, BKM, true> db;
+  static_assert(decltype(da)::N == 1 && decltype(db)::N == 1, "one load each");
+  da.init((const float*)g.A + (AK ? m0 * g.lda : m0), g.lda, g.M - m0, wave, lane);
+  db.init((const float*)g.B + (BKM ? n0 * g.ldb : n0), g.ldb, g.N - n0, wave, lane);
+  auto issue = [&](int t) {
+    char* slot = smem + (t % NS) * T16_STAGE;
+    da.issue(0, g.lda, t * BK, g.K, slot, wave);
+    db.issue(0, g.ldb, t * BK, g.K, slot + OP, wave);
+  };
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < nt) issue(t);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  // Lane's operand values: k = 16 wave + 4 kq + i of its row or column.
+  auto frag = [&](auto kmaj, uint32_t tile) {
+    const int k = 16 * wave + 4 * kq;
+    if constexpr (decltype(kmaj)::value) {
+      return *(lds_cf32x4_t*)(uintptr_t)(tile + (k >> 5) * (16 * 128) + rr * 128 +
+                                         16 * (((k & 31) >> 2) ^ ((rr >> 1) & 7)));
+    } else {
+      lds_cfloat_t* p = (lds_cfloat_t*)(uintptr_t)(tile + (k * 16 + rr) * 4);
+      return f32x4_t{p[0], p[16], p[32], p[48]};
+    }
+  };
+  f32x4_t acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  for (int t = 0; t < nt; ++t) {
+    // k-tile t has landed for everyone, and nobody reads k-tile t - 1 any more.
+    wait_after<2, NS - 2>(min(nt - 1, t + NS - 2) - t);
+    ring_barrier();
+    if (t + NS - 1 < nt) issue(t + NS - 1);
+    const uint32_t slot = lds0 + (t % NS) * T16_STAGE;
+    const f32x4_t a = frag(std::integral_constant<bool, AK>(), slot);
+    const f32x4_t b = frag(std::integral_constant<bool, BKM>(), slot + OP);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], acc[i & 1], 0, 0, 0);
+  }
+  // Sums over the wavefronts, in their order; wavefront w owns register w (row
+  // 4 kq + w).
+  __syncthreads();
+  float* ex = (float*)smem;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) ex[(wave * 4 + r) * 64 + lane] = acc[0][r] + acc[1][r];
+  __syncthreads();
+  const float* p = ex + wave * 64 + lane;
+  const float v[1] = {((p[0] + p[256]) + p[512]) + p[768]};
+  epilogue<EPI, 1>(g, 0, 0, [&](int) { return m0 + 4 * kq + wave; }, n0 + rr, v);
+}
+
+template <F32Tile T, bool VEC>
+struct Ring {
+  // 4-byte loads: as many slots as keep the outstanding count within vmcnt's
+  // range
+  static constexpr int NS = T == T32x32 && VEC ? 8 : 4;
+  static constexpr int LDS = NS * Cfg<T>::STAGE;
+};
 
 template <F32Tile T, bool AK, bool BKM, bool VEC, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
@@ -552,7 +620,10 @@ hipError_t launch(const GemmArgs& g, int batch, hipStream_t st) {
     return dim3((unsigned)tiles_of(g, bm, bn), 1, (unsigned)(batch * g.ksplit));
   };
   if (vec) {
-    if (t == T32x32)
+    // 16 x 16 tiles while they are one per CU (the line 32 x 32 tiles have too)
+    if (tiles_of(g, 16, 16) <= 256 && batch * g.ksplit == 1 && !g.colpart)
+      hipLaunchKernelGGL((gemm_f32_16_kernel<AK, BKM, EPI>), grid(16, 16), dim3(256), 0, st, g);
+    else if (t == T32x32)
       hipLaunchKernelGGL((gemm_f32_kernel<T32x32, AK, BKM, true, EPI>), grid(32, 32), dim3(256), 0, st, g);
     else if (t == T64x32)
       hipLaunchKernelGGL((gemm_f32_kernel<T64x32, AK, BKM, true, EPI>), grid(64, 32), dim3(256), 0, st, g);
