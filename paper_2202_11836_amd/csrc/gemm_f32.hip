@@ -685,21 +685,23 @@ hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dk, const GemmA
   return hipGetLastError();
 }
 
-int gemm_f32_wgrad_splits(int h, int f, int K) {
+F32WgradPlan gemm_f32_wgrad_plan(int h, int f, int K) {
   // Two work-groups of 64 x 64 per CU over the layer's four gradients (h and f
   // are multiples of 64); k ranges of at least 256.
   const int64_t hb = h / 64, fb = f / 64, tiles = 4 * hb * hb + 2 * hb * fb;
-  const int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / tiles, K / 256));
+  int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / tiles, K / 256));
   const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
-  return (K + chunk - 1) / chunk;
+  ks = (K + chunk - 1) / chunk;
+  return {ks, tiles * ks < SMALL_TILES};
 }
 
-hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, F32WgradPlan plan,
                                 const TailJobs& tail, hipStream_t st) {
+  const int ks = plan.ks;
+  const bool small = plan.small;
   if (ks < 1 || n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
   WgradGroup w{};
   F32Reduce rd{};
-  int64_t t64 = 0;
   for (int q = 0; q < n; ++q) {
     GemmArgs g = p[q];
     if (g.M < 1 || g.N < 1 || g.K < 1 || g.ldc != g.N || !vec_ok(g, false, false))
@@ -710,9 +712,7 @@ hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int
     // one split writes the gradient itself
     if (g.ksplit == 1) g.C = out[q];
     w.p[q] = g;
-    t64 += tiles_of(g, 64, 64) * g.ksplit;
   }
-  const bool small = t64 < SMALL_TILES;
   int64_t blocks = 0, rblocks = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = w.p[q];

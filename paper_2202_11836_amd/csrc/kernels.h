@@ -192,11 +192,15 @@ int wgrad_plan(const int* M, const int* N, int n, int K);
 // Weight gradients of one fp32 layer (both operands m/n-major, equal K) and the
 // jobs of tail, in one launch; with ks > 1 splits over K (p[q].C holds ks slots
 // of M x N partials) a second one has the splits' fixed-order sums and the tail.
-// ks: gemm_f32_wgrad_splits of the whole layer (width h, feed-forward width
-// f), also when only one half of it is computed, so that a half-layer stage
-// sums in the same order as a whole one.
-int gemm_f32_wgrad_splits(int h, int f, int K);
-hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, int ks,
+// plan: gemm_f32_wgrad_plan of the whole layer (width h, feed-forward width f),
+// also when only one half of it is computed: splits and tiles set the order of
+// the sums, and a half-layer stage sums in the same order as a whole one.
+struct F32WgradPlan {
+  int ks;      // splits over K
+  bool small;  // 32 x 32 tiles (else 64 x 64)
+};
+F32WgradPlan gemm_f32_wgrad_plan(int h, int f, int K);
+hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, F32WgradPlan plan,
                                 const TailJobs& tail, hipStream_t st);
 
 // ---------------------------------------------------------------------------

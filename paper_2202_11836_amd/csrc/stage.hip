@@ -341,7 +341,7 @@ size_t splitk_need(const stage_t* s, int64_t T) {
                      (size_t)wgrad_group_slots(Ms, Ns, 2, K) * (size_t)(2 * h * f),
                      (size_t)wgrad_group_slots(Ms + 2, Ns + 2, 2, K) * (size_t)(4 * h * h)});
   } else {
-    const int ks = gemm_f32_wgrad_splits((int)h, (int)f, (int)std::max<int64_t>(T, 1));
+    const int ks = gemm_f32_wgrad_plan((int)h, (int)f, (int)std::max<int64_t>(T, 1)).ks;
     if (ks > 1) need = (size_t)ks * (size_t)(4 * h * h + 2 * h * f);
   }
   return need;
@@ -530,16 +530,16 @@ stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const Tail
   const int Tn = s->B * s->S;
   GemmArgs gs[GEMM_GROUP_MAX];
   float* outs[GEMM_GROUP_MAX];
-  const int ks = gemm_f32_wgrad_splits(s->h, s->f, Tn);
+  const F32WgradPlan plan = gemm_f32_wgrad_plan(s->h, s->f, Tn);
   size_t off = 0;
   for (int q = 0; q < n; ++q) {
     const WgradJob& j = jobs[q];
     gs[q] = gemm_args(j.dy, j.ld_dy, j.x, j.ld_x, s->splitk + off, j.N, j.M, j.N, Tn);
     outs[q] = j.out;
-    if (ks > 1) off += (size_t)ks * j.M * j.N;
+    if (plan.ks > 1) off += (size_t)plan.ks * j.M * j.N;
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
-  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, ks, tail, s->stream));
+  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, plan, tail, s->stream));
   return STAGE_OK;
 }
 

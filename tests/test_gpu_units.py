@@ -257,3 +257,30 @@ def test_single_unit_stages_chain():
             assert torch.equal(g[j][name], whole.grad(j, IDX[name])), (j, name)
     for st in stages + [whole]:
         st.close()
+
+
+# Weight-gradient tiles of fp32 layers: 64 x 64 for a whole layer of 300 tiles
+# whose halves have 100 and 200; 468 tiles, halves 144 and 324; 192 tiles in 2
+# splits (halves 64 and 128); and a layer that takes 32 x 32 tiles.
+@pytest.mark.parametrize("hidden,ffn,batch,seq", [(320, 1280, 3, 41), (384, 1728, 2, 50),
+                                                  (256, 1024, 6, 100), (192, 768, 1, 70)])
+def test_half_layer_gradients_fp32_bitwise(hidden, ffn, batch, seq):
+    """A half-layer stage's weight gradients are summed in the whole layer's
+    order, whatever shares their launch."""
+    import torch
+    _say(f"case units fp32 halves h {hidden} f {ffn} B {batch} S {seq}")
+    cfg = synth.StageConfig("halves", 1, hidden, hidden // 64, ffn, batch, seq, seq // 2, seq, "f32", 23)
+    inp, params = synth.make_inputs(cfg), synth.make_params(cfg, perturb=True)
+    x, dy = to_torch(inp["x"], "f32"), to_torch(inp["dy"], "f32")
+    mask = torch.from_numpy(np.ascontiguousarray(inp["mask"], dtype=np.uint8)).cuda()
+    cuts = [(0, 1), (1, 1)]
+    whole, halves = make_stage(cfg, params), [make_unit_stage(cfg, params, u, 1) for u, _ in cuts]
+    y = whole.forward(x, mask)
+    dx = whole.backward(dy)
+    acts, d = run_chain(halves, x, mask, dy)
+    assert torch.equal(acts[-1], y) and torch.equal(d, dx)
+    g = chain_grads(halves, cuts, 1)[0]
+    differ = [n for n in synth.PARAM_NAMES if not torch.equal(g[n], whole.grad(0, IDX[n]))]
+    for st in halves + [whole]:
+        st.close()
+    assert not differ, differ
