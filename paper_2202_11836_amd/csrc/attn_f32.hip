@@ -101,7 +101,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnF32Args a) {
     for (int c = tid; c < 16 * ng; c += 256) msk[c] = c < S ? a.mask[(int64_t)b * S + c] : 0;
   __syncthreads();
 
-  // Rows 8 wave .. + 7: P = softmax(scale * sc) over the valid keys (none: 0),
+  // Rows 8 wave .. + 7: P = softmax(scale * sc) over the valid keys (none, or a
+  // sum that is not a positive number: a row of zeros, as in softmax_fwd),
   // or dS = scale * P * (sc - rowsum(sc * P)); columns S .. 16 ng - 1 get 0.
   float* rows = sc + 8 * wave * LD;
   if constexpr (!BWD) {
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnF32Args a) {
     for (int c = lane; c < S; c += 64) {
       float p[8];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) p[r] = rows[r * LD + c] * f[r];
+      for (int r = 0; r < 8; ++r) p[r] = f[r] > 0.0f ? rows[r * LD + c] * f[r] : 0.0f;
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
         rows[r * LD + c] = p[r];
