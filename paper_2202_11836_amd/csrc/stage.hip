@@ -574,6 +574,22 @@ AttnF32Args attn_f32_args(stage_t* s, const float* qkv, void* P, float* out, int
   return a;
 }
 
+// Whether kernels may read n bytes at p in place: device memory of this device,
+// all of them inside its allocation.  Anything else (host, managed or another
+// device's memory; an extent the runtime has to judge) goes through a runtime
+// copy, which reads it or refuses it.
+bool reads_in_place(const void* p, size_t n, int device) {
+  hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  const bool ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice &&
+                  !at.isManaged && at.device == device &&
+                  hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) == hipSuccess &&
+                  (size_t)((const char*)p - (const char*)base) + n <= size;
+  if (!ok) (void)hipGetLastError();  // (a failed query leaves an error behind)
+  return ok;
+}
+
 template <typename T>
 stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y) {
   const int B = s->B, S = s->S, h = s->h, H = s->H, f = s->f;
@@ -585,14 +601,19 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
   // only its feed-forward half.  It and the key mask are copied and the key
   // extents found beside the first GEMM, which then reads x itself (bf16,
   // tiles of gemm_mid.hip), else by a launch of their own; an input that is
-  // not 16-byte aligned is copied by the runtime first.
+  // not 16-byte aligned, and what the kernels may not read in place, is copied
+  // by the runtime first.
   PrepArgs prep{x, s->ffn_first ? s->saved[0].H1 : s->saved[0].X, (int64_t)Tn * h * (int)sizeof(T),
                 key_mask, s->mask, B, S, nullptr};
   if (std::is_same<T, bf16_t>::value && (s->L > 1 || !s->ffn_first)) prep.kext = s->kext;
-  if (((uintptr_t)x & 15) != 0) {
-    HIPCK(hipMemcpyAsync(prep.X, x, (size_t)prep.nx, hipMemcpyDeviceToDevice, st));
+  if (((uintptr_t)x & 15) != 0 || !reads_in_place(x, (size_t)prep.nx, s->device)) {
+    HIPCK(hipMemcpyAsync(prep.X, x, (size_t)prep.nx, hipMemcpyDefault, st));
     prep.x = prep.X;
     prep.nx = 0;
+  }
+  if (key_mask && !reads_in_place(key_mask, (size_t)Tn, s->device)) {
+    HIPCK(hipMemcpyAsync(s->mask, key_mask, (size_t)Tn, hipMemcpyDefault, st));
+    prep.key_mask = s->mask;
   }
   const GemmEpi epi0 = s->ffn_first ? EPI_GELU : EPI_STORE;
   const int tile0 = gemm_bf16_plan(Tn, s->ffn_first ? f : 3 * h, h, true, epi0, false).tile;

@@ -96,3 +96,78 @@ def test_ffn_half_dx(hidden, ffn, batch, seq):
     assert rel_l2(dx2.double().cpu().numpy(), dx.double().cpu().numpy()) <= 1e-2
     for s in (whole, attn, half):
         s.close()
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("dtype,hidden,batch,seq", [("bf16", 128, 3, 77), ("bf16", 1024, 32, 384),
+                                                    ("f32", 128, 2, 40)])
+def test_forward_from_host_memory(dtype, hidden, batch, seq, pinned):
+    """x and the key mask in host memory: copied by the runtime, not read by the
+    kernels (a first GEMM that reads x itself, one that does not, fp32)."""
+    import torch
+    from paper_2202_11836_amd import Stage, stage_forward
+    print(f"case host input {dtype} h {hidden} B {batch} S {seq} pinned {pinned}", flush=True)
+    cfg = synth.StageConfig("host", 1, hidden, hidden // 64, 256, batch, seq, max(1, seq // 2), seq,
+                            dtype, 3)
+    inp = synth.make_inputs(cfg)
+    x = to_torch(inp["x"], dtype, "cpu")
+    mask = torch.from_numpy(np.ascontiguousarray(inp["mask"], dtype=np.uint8))
+    dy = to_torch(inp["dy"], dtype)
+    if pinned:
+        x, mask = (torch.empty_like(t, pin_memory=True).copy_(t) for t in (x, mask))
+    st = Stage(1, hidden, hidden // 64, 256, seed=5, dtype=dtype)
+
+    def run(x, mask):
+        y = torch.empty(batch, seq, hidden, dtype=dy.dtype, device="cuda")
+        st._sync_stream()
+        stage_forward(st.handle, x, mask, batch, seq, y)
+        dx = st.backward(dy)
+        torch.cuda.synchronize()
+        return [y, dx.clone()] + [st.grad(0, i) for i in range(12)]
+
+    ref = run(x.cuda(), mask.cuda())
+    for a in (run(x.cuda(), mask), run(x, mask.cuda()), run(x, mask)):
+        for t, r in zip(a, ref):
+            assert torch.equal(t, r)
+    st.close()
+
+
+@pytest.mark.parametrize("dtype,hidden,batch,seq", [("bf16", 128, 3, 77), ("f32", 128, 2, 40)])
+def test_step_in_a_captured_graph(dtype, hidden, batch, seq):
+    """A forward and a backward_noalloc recorded in a graph: every replay, on new
+    inputs and with eager passes between them, gives the eager result."""
+    import torch
+    from paper_2202_11836_amd import Stage
+    print(f"case graph {dtype} h {hidden} B {batch} S {seq}", flush=True)
+    cfg = synth.StageConfig("graph", 2, hidden, hidden // 64, 256, batch, seq, max(1, seq // 2), seq,
+                            dtype, 3)
+    st = Stage(2, hidden, hidden // 64, 256, seed=5, dtype=dtype)
+    inps = [synth.make_inputs(cfg, seed=s) for s in (1, 2, 3)]
+    x, dy = to_torch(inps[0]["x"], dtype), to_torch(inps[0]["dy"], dtype)
+    mask = torch.from_numpy(np.ascontiguousarray(inps[0]["mask"], dtype=np.uint8)).cuda()
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+
+    def step():
+        st.forward(x, mask, out=y)
+        st.backward_noalloc(dy, dx)
+
+    def results():
+        torch.cuda.synchronize()
+        return [y.clone(), dx.clone()] + [st.grad(l, i) for l in range(2) for i in range(12)]
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for inp in inps:
+        x.copy_(to_torch(inp["x"], dtype))
+        dy.copy_(to_torch(inp["dy"], dtype))
+        mask.copy_(torch.from_numpy(np.ascontiguousarray(inp["mask"], dtype=np.uint8)))
+        step()
+        eager = results()
+        y.zero_(), dx.zero_()
+        graph.replay()
+        for a, b in zip(results(), eager):
+            assert torch.equal(a, b)
+    st.close()
