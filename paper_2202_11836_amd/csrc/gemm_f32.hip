@@ -690,6 +690,11 @@ F32WgradPlan gemm_f32_wgrad_plan(int h, int f, int K) {
   // are multiples of 64); k ranges of at least 256.
   const int64_t hb = h / 64, fb = f / 64, tiles = 4 * hb * hb + 2 * hb * fb;
   int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / tiles, K / 256));
+  // Width 64 over so many tokens that the column partials of one-token sequences
+  // fill the no-alloc backward's scratch: 6.3 MB of partials, what the scratch
+  // has left for them (h = f = 64: 64 splits, not 85).
+  if (h == 64 && K > 262144)
+    ks = (int)std::max<int64_t>(1, std::min<int64_t>(ks, 128 * 3 * 64 * 64 / (tiles * 4096)));
   const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
   ks = (K + chunk - 1) / chunk;
   return {ks, tiles * ks < SMALL_TILES};

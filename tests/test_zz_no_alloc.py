@@ -70,3 +70,24 @@ def test_noalloc_backward_rejects_a_batch_beyond_the_scratch():
         torch.cuda.synchronize()
     finally:
         st.close()
+
+
+def test_noalloc_f32_many_one_token_sequences():
+    """The narrowest fp32 layer on 320000 sequences of one token: 246 MB of db_qkv
+    and 15 MB of LayerNorm column partials, which leaves 7.3 MB of the scratch for
+    the weight gradients' partials."""
+    import torch
+    from paper_2202_11836_amd import Stage
+    _say("case no-alloc backward f32 h 64, f 64, B320000 x S1")
+    st = Stage(1, 64, 1, 64, seed=3, dtype="f32")
+    try:
+        x = torch.randn(320000, 1, 64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+        st.forward(x)
+        dx = st.backward_noalloc(x, torch.empty_like(x))
+        got = [st.grad(0, i) for i in range(12)]
+        st.forward(x)
+        assert torch.equal(dx, st.backward(x))
+        for i in range(12):
+            assert torch.equal(got[i], st.grad(0, i)), i
+    finally:
+        st.close()
