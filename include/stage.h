@@ -266,7 +266,10 @@ size_t stage_tensor_bytes(stage_t* s, int kind, int layer, int which);
  * devices, section V-B).  stage_trace_site(s, site) makes every later launch
  * of kernel site `site` (0 <= site < stage_site_count(); -1 = off) record a
  * pair of HIP events on the stage stream around it, and clears earlier
- * records.  stage_trace_read synchronises the stream and returns how many
+ * records.  A launch that does the work of several sites (a layer's weight
+ * gradients with their reductions, for instance) belongs to each of them and
+ * is recorded once when any is traced, so the times of sites traced one by
+ * one can add up to more than those of all traced together.  stage_trace_read synchronises the stream and returns how many
  * traced launches ran and their summed event time in ms, then clears the
  * records.  Tracing adds two event records per traced launch and nothing
  * to untraced ones.

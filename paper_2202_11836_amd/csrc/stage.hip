@@ -23,7 +23,8 @@ namespace {
 constexpr int HEAD_DIM = 64;
 constexpr int COL_PARTS = 128; // row blocks of a column-sum pass (fp32 stages, db_1)
 
-// Kernel launch sites of one layer, for event tracing (stage_trace_site).
+// Sites of one layer's work, for event tracing (stage_trace_site).  A launch that
+// does the work of several sites is traced when any of them is.
 #define STAGE_SITES(X)                                                              \
   X(QKV_FWD, "qkv_gemm_fwd") X(SCORES_FWD, "scores_gemm_fwd")                         \
   X(SOFTMAX_FWD, "softmax_fwd") X(CTX_FWD, "context_gemm_fwd")                        \
@@ -242,10 +243,10 @@ stage_status fail(stage_t* s, stage_status st, const std::string& msg) {
       return fail(s, STAGE_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_));   \
   } while (0)
 
-// Records a start event before a traced site's launch; returns the pool
-// index of the event pair, or -1 when the site is not traced.
-int trace_begin(stage_t* s, int site) {
-  if (!((s->trace_mask >> site) & 1) || s->no_alloc) return -1;
+// Records a start event before the launch of a set of sites; returns the pool
+// index of the event pair, or -1 when none of them is traced.
+int trace_begin(stage_t* s, uint64_t sites) {
+  if (!(s->trace_mask & sites) || s->no_alloc) return -1;
   while (s->events.size() < s->events_used + 2) {
     hipEvent_t e;
     if (hipEventCreate(&e) != hipSuccess) return -1;
@@ -264,16 +265,23 @@ void trace_end(stage_t* s, int idx) {
   (void)hipEventRecord(s->events[idx + 1], s->stream);
 }
 
-// Launch expression (a hipError_t) as traced site number `site`.
-#define SITE_I(site, ...)                                                         \
+// The set of some sites.
+template <typename... I>
+constexpr uint64_t site_set(I... i) {
+  return (((uint64_t)1 << i) | ... | 0);
+}
+// Launch expression (a hipError_t) of site number `site`, which also does the
+// work of the sites of the set `also`.
+#define SITE_SET(site, also, ...)                                                 \
   do {                                                                            \
-    int tr_ = trace_begin(s, (site));                                             \
+    int tr_ = trace_begin(s, site_set(site) | (also));                            \
     hipError_t e_ = (__VA_ARGS__);                                                \
     trace_end(s, tr_);                                                            \
     if (e_ != hipSuccess)                                                         \
       return fail(s, STAGE_EHIP,                                                  \
                   std::string(SITE_NAMES[(site)]) + ": " + hipGetErrorString(e_)); \
   } while (0)
+#define SITE_I(site, ...) SITE_SET(site, 0, __VA_ARGS__)
 #define SITE(id, ...) SITE_I(SITE_##id, __VA_ARGS__)
 
 int64_t param_numel(const stage_t* s, int which) {
@@ -517,7 +525,8 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const TailJobs
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
   if (plan != 0) {
-    SITE(WGRAD_GROUP, gemm_mid_wgrad(gs, outs, n, plan, tail, s->stream));
+    SITE_SET(SITE_WGRAD_GROUP, site_set(SITE_WGRAD_GROUP_RED),
+             gemm_mid_wgrad(gs, outs, n, plan, tail, s->stream));
     return STAGE_OK;
   }
   SITE(WGRAD_GROUP, gemm_bf16_wgrad_group(gs, n, s->stream));
@@ -525,8 +534,9 @@ stage_status wgrad_group(stage_t* s, const WgradJob* jobs, int n, const TailJobs
   return STAGE_OK;
 }
 
-// The same on fp32 stages.
-stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const TailJobs& tail) {
+// The same on fp32 stages.  Traced as the gradients and reductions it holds.
+stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const TailJobs& tail, bool attn,
+                             bool ffn) {
   const int Tn = s->B * s->S;
   GemmArgs gs[GEMM_GROUP_MAX];
   float* outs[GEMM_GROUP_MAX];
@@ -539,7 +549,12 @@ stage_status wgrad_group_f32(stage_t* s, const WgradJob* jobs, int n, const Tail
     if (plan.ks > 1) off += (size_t)plan.ks * j.M * j.N;
   }
   if (off > s->splitk_elems) return fail(s, STAGE_EHIP, "split-K buffer too small");
-  SITE(WGRAD_GROUP, gemm_f32_wgrad_group(gs, outs, n, plan, tail, s->stream));
+  uint64_t also = site_set(SITE_WGRAD_GROUP_RED);
+  if (ffn) also |= site_set(SITE_W2_WGRAD, SITE_W1_WGRAD, SITE_LN2_RED, SITE_B1_RED);
+  if (attn) also |= site_set(SITE_WO_WGRAD, SITE_WQKV_WGRAD, SITE_LN1_RED, SITE_BQKV_RED);
+  if (plan.ks > 1 && ffn) also |= site_set(SITE_W2_RED, SITE_W1_RED);
+  if (plan.ks > 1 && attn) also |= site_set(SITE_WO_RED, SITE_WQKV_RED);
+  SITE_SET(SITE_WGRAD_GROUP, also, gemm_f32_wgrad_group(gs, outs, n, plan, tail, s->stream));
   return STAGE_OK;
 }
 
@@ -619,6 +634,7 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
   const int tile0 = gemm_bf16_plan(Tn, s->ffn_first ? f : 3 * h, h, true, epi0, false).tile;
   const bool prep_beside = std::is_same<T, bf16_t>::value && tile0 != GEMM_TILE_256x256;
   if (!prep_beside) SITE(KEXT, stage_prep(prep, st));
+  const uint64_t prep_site = prep_beside ? site_set(SITE_KEXT) : 0;  // of the first product
   // A product with the layer's input or H1 as A, the first of the pass with
   // the above.
   auto gemm_in = [&](GemmArgs g, GemmEpi epi, bool first) -> hipError_t {
@@ -643,7 +659,7 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
       {
         GemmArgs g = gemm_args(X, h, p[STAGE_W_QKV], h, QKV, 3 * h, Tn, 3 * h, h);
         g.bias = (const float*)p[STAGE_B_QKV];
-        SITE(QKV_FWD, gemm_in(g, EPI_STORE, l == 0));
+        SITE_SET(SITE_QKV_FWD, l == 0 ? prep_site : 0, gemm_in(g, EPI_STORE, l == 0));
       }
       if constexpr (std::is_same<T, bf16_t>::value) {
         // Fused attention: softmax(Q K^T / 8) V per (batch, head), P stays on chip.
@@ -651,7 +667,8 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
         aa.out_lo = (bf16_t*)v.Clo;
         SITE(ATTN_FWD, attn_forward(aa, st));
       } else if (S <= ATTN_F32_MAX_S) {
-        SITE(ATTN_FWD, attn_f32_forward(attn_f32_args(s, QKV, v.P, (float*)v.C, h), B, st));
+        SITE_SET(SITE_ATTN_FWD, site_set(SITE_SCORES_FWD, SITE_SOFTMAX_FWD, SITE_CTX_FWD),
+                 attn_f32_forward(attn_f32_args(s, QKV, v.P, (float*)v.C, h), B, st));
       } else {
         // Long sequences: the score matrix in memory.
         // scores[b, j] = Q_bj K_bj^T  (fp32)
@@ -699,7 +716,8 @@ stage_status forward_impl(stage_t* s, const T* x, const uint8_t* key_mask, T* y)
       GemmArgs g = gemm_args(v.H1, h, p[STAGE_W_1], h, v.G, f, Tn, f, h);
       g.bias = (const float*)p[STAGE_B_1];
       g.C2 = v.Gd;
-      SITE(FFN1_FWD, gemm_in(g, EPI_GELU, l == 0 && s->ffn_first));
+      const bool first = l == 0 && s->ffn_first;
+      SITE_SET(SITE_FFN1_FWD, first ? prep_site : 0, gemm_in(g, EPI_GELU, first));
     }
     // tmp = G W_2^T (fp32);  Y = LN(H1 + tmp + b_2)
     int np2 = 1;
@@ -771,7 +789,8 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
           g.colpart = s->colpart_ffn;
           g.cp_ld = f;
         }
-        SITE(FFN2_DGRAD, gemm_f32(g, true, false, EPI_MUL, 1, st));
+        SITE_SET(SITE_FFN2_DGRAD, fused ? site_set(SITE_B1_SUM) : 0,
+                 gemm_f32(g, true, false, EPI_MUL, 1, st));
       }
       if (!fused)
         SITE(B1_SUM, col_partial<T>(dU, Tn, f, s->colpart_ffn, COL_PARTS, st));
@@ -810,7 +829,8 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
         aa.dC = dC;
         aa.dS = (float*)s->dS;
         aa.colpart = s->colpart_qkv;
-        SITE(ATTN_DQ, attn_f32_backward_rows(aa, B, st));
+        SITE_SET(SITE_ATTN_DQ, site_set(SITE_DP_BWD, SITE_SOFTMAX_BWD, SITE_DQ_BWD, SITE_BQKV_SUM),
+                 attn_f32_backward_rows(aa, B, st));
       } else {
         // dP[b, j] = dC_bj V_bj^T (fp32, into the score buffer)
         {
@@ -847,8 +867,9 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
         };
         const int64_t sq = (int64_t)S * 3 * h;
         const GemmArgs dq = prob(s->dS, QKV + h, 3 * h, sq, 0);
-        SITE(DV_BWD, gemm_f32_attn_bwd(prob(v.P, dC, h, (int64_t)S * h, 2),
-                                       prob(s->dS, QKV, 3 * h, sq, 1), rows ? nullptr : &dq, BH, st));
+        SITE_SET(SITE_DV_BWD, site_set(SITE_DK_BWD, SITE_BQKV_SUM, rows ? SITE_DV_BWD : SITE_DQ_BWD),
+                 gemm_f32_attn_bwd(prob(v.P, dC, h, (int64_t)S * h, 2),
+                                   prob(s->dS, QKV, 3 * h, sq, 1), rows ? nullptr : &dq, BH, st));
       }
       tail.col[tail.ncol++] = ColJob{s->colpart_qkv, B * nqb, 1, 3 * h,
                            {gr[STAGE_B_QKV], nullptr, nullptr, nullptr}};
@@ -864,7 +885,7 @@ stage_status backward_f32(stage_t* s, const float* dy, float* dx) {
       }
       dYcur = dXout;
     }
-    if ((r = wgrad_group_f32(s, wjobs, nw, tail))) return r;
+    if ((r = wgrad_group_f32(s, wjobs, nw, tail, attn, ffn))) return r;
   }
   return STAGE_OK;
 }
@@ -985,7 +1006,7 @@ stage_status backward_bf16(stage_t* s, const bf16_t* dy, bf16_t* dx) {
       aa.dout = dC;
       aa.colpart = s->colpart_qkv;
       if (dsum) {
-        SITE(ATTN_BWD, attn_backward(aa, st));
+        SITE_SET(SITE_ATTN_BWD, site_set(SITE_ATTN_DQ, SITE_ATTN_DKDV), attn_backward(aa, st));
       } else {
         SITE(ATTN_DQ, attn_backward_dq(aa, st));
         SITE(ATTN_DKDV, attn_backward_dkdv(aa, st));
