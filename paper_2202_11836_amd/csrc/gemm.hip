@@ -849,6 +849,21 @@ double tile_time(int tile, int64_t M, int64_t N, int64_t K, int ks, GemmEpi epi)
 
 }  // namespace
 
+bool wgrad_args_ok(const GemmArgs* p, int n) {
+  if (n < 1 || n > GEMM_GROUP_MAX || !p) return false;
+  for (int q = 0; q < n; ++q) {
+    const GemmArgs& g = p[q];
+    // the checks gemm_bf16 makes, for two m/n-major operands; one K for all
+    if (g.M < 0 || g.N < 0 || g.K < 1 || g.K != p[0].K) return false;
+    if (g.N % 8 != 0 || g.ldc % 8 != 0 || g.M % 8 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0)
+      return false;
+    if ((int64_t)g.K * g.lda * 2 >= ((int64_t)1 << 31) ||
+        (int64_t)g.K * g.ldb * 2 >= ((int64_t)1 << 31))
+      return false;
+  }
+  return true;
+}
+
 GemmPlan gemm_bf16_plan(int M, int N, int K, bool b_kmajor, GemmEpi epi, bool split) {
   const int64_t cus = device_cus();
   const int64_t t1 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
@@ -908,21 +923,14 @@ SkSeq group_seq(int64_t tiles, int K) {
   return {tiles * kt, (int)tiles, kt, first_phase(tiles, kt), group_grid()};
 }
 
-// Checks and the stream-K table of a group; false for invalid problems.
+// The stream-K table of a group; false for invalid problems.
 bool group_table_of(const GemmArgs* p, int n, GemmGroup& gg) {
-  if (n < 1 || n > GEMM_GROUP_MAX || !p) return false;
+  if (!wgrad_args_ok(p, n)) return false;
   gg = GemmGroup{};
   gg.n = n;
   int64_t tiles = 0;
   for (int q = 0; q < n; ++q) {
     GemmArgs g = p[q];
-    // the checks gemm_bf16 makes for two m/n-major operands; one K for all
-    if (g.M < 0 || g.N < 0 || g.K < 1 || g.K != p[0].K) return false;
-    if (g.N % 8 != 0 || g.ldc % 8 != 0 || g.M % 8 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0)
-      return false;
-    if ((int64_t)g.K * g.lda * 2 >= ((int64_t)1 << 31) ||
-        (int64_t)g.K * g.ldb * 2 >= ((int64_t)1 << 31))
-      return false;
     g.zdiv = 1;
     g.ksplit = 1;
     g.kchunk = g.K;

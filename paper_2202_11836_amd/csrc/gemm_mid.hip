@@ -468,7 +468,7 @@ hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hip
 
 hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
                           const TailJobs& tail, hipStream_t st) {
-  if (n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
+  if (!wgrad_args_ok(p, n) || !out) return hipErrorInvalidValue;
   MidGroup w{};
   w.n = n;
   w.tail = tail;
@@ -477,6 +477,7 @@ hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
   const int bn = tile == GEMM_TILE_64x64 || tile == GEMM_TILE_128x64 ? 64 : 128;
   int64_t blocks = 0;
   for (int q = 0; q < n; ++q) {
+    if (p[q].ldc != p[q].N) return hipErrorInvalidValue;
     w.g[q] = p[q];
     w.g[q].C = out[q];
     w.g[q].ksplit = 1;

@@ -181,11 +181,14 @@ hipError_t wgrad_group_reduce(const GemmArgs* p, float* const* out, int n, const
 bool gemm_bf16_ok(const GemmArgs& g, bool b_kmajor);
 // gemm_bf16 with one of the tiles of gemm_mid.hip.
 hipError_t gemm_mid(const GemmArgs& g, bool b_kmajor, GemmEpi epi, int tile, hipStream_t st);
+// Whether the weight-gradient launches take n problems (both operands m/n-major,
+// one K) of these shapes and strides.
+bool wgrad_args_ok(const GemmArgs* p, int n);
 // n weight gradients (operands m/n-major, ldc = N), each written whole, and
 // the jobs of tail, in one launch.
 hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
                           const TailJobs& tail, hipStream_t st);
-// How a layer's weight gradients are computed: 0 = the stream-K group below
+// How a layer's weight gradients are computed: 0 = the stream-K group above
 // with its reduction, else a tile of gemm_mid_wgrad (no partials).
 int wgrad_plan(const int* M, const int* N, int n, int K);
 
