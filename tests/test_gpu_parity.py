@@ -271,9 +271,9 @@ def test_bf16_mid_width_sequence_subset():
     """Two layers of width 512 (8 heads, FFN 2048) on B32 x S512 with valid
     lengths in [384, 512].  On a 256-CU device the GEMMs with N = h = 512
     (out-projection, FFN2, the FFN1 / QKV / out-projection data gradients)
-    take 256 x 128 tiles, the three-slot ring with its k-tile requests split
-    between the two halves of the work-group, which none of the other
-    configurations selects.  dy is zero outside three sequences (the first,
+    take the 256 x 128 tiles of the few-tile kernels, the wider ones 256 x 256
+    tiles, and the weight gradients a stream-K group with partials, a mix
+    that none of the other configurations selects.  dy is zero outside three sequences (the first,
     the shortest and the last); the oracle runs only those."""
     cfg = synth.StageConfig("mid_width", 2, 512, 8, 2048, 32, 512, 384, 512, "bf16", 7)
     _say(f"case bf16 subset {cfg}")
@@ -294,19 +294,21 @@ def test_bf16_smaller_batches_after_the_full_batch():
     """One BERT-large-shaped layer run on B32 x S512 and then, on the same
     stage, on smaller batches.  The weight-gradient stream-K schedule of a
     smaller token count can need more split-K partials than the full batch
-    (T = 384 needs 201 MB against 101 MB at T = 16384): every call must still
-    match the oracle.  The full batch is checked on sequences {0, 31} (dy
-    zero elsewhere), the smaller ones whole."""
+    (T = 8200 needs 201 MB against 101 MB at T = 16384), and the smallest
+    write their gradients whole: every call must still match the oracle.  The
+    two large batches are checked on their first and last sequence (dy zero
+    elsewhere), the smaller ones whole."""
     from _parity import make_stage
     base = synth.CONFIGS["bert_large_4"].with_(L=1)
     params = synth.make_params(base, perturb=True)
     st = make_stage(base, params)
     try:
-        for batch, seq in ((32, 512), (1, 384), (1, 192), (3, 96)):
+        for batch, seq in ((32, 512), (20, 410), (1, 384), (1, 192), (3, 96)):
             cfg = base.with_(batch=batch, seq=seq, len_lo=seq // 2, len_hi=seq)
             _say(f"case bf16 B{batch} x S{seq} after the full batch")
             inp = synth.make_inputs(cfg, seed=batch * 1000 + seq)
-            if batch == 32:
+            held = st.device_bytes()
+            if batch >= 20:
                 sel = np.zeros(batch, bool)
                 sel[[0, batch - 1]] = True
                 dy = inp["dy"].copy()
@@ -320,5 +322,7 @@ def test_bf16_smaller_batches_after_the_full_batch():
                 got = run_gpu(cfg, inp, params, stage=st, saved=(0, 3))
                 lw = check_bf16_layerwise(cfg, inp, params, got)
                 assert_bf16(lw, check_bf16(cfg, got, run_oracle(cfg, inp, params)))
+            # the partial buffer grows for the second batch, and only there
+            assert batch == 32 or (st.device_bytes() > held) == (batch == 20)
     finally:
         st.close()
