@@ -201,7 +201,7 @@ stage_status stage_memory_model(int hidden, int heads, int ffn, int batch, int s
  * The same per allocation unit (see stage_init_units): a stage of units
  * [u0, u0 + n) holds shared + (its attention units) * attn_unit + (its
  * feed-forward units) * ffn_unit bytes, and per_layer = attn_unit +
- * ffn_unit.  The attention unit counts X, QKV, the score or log-sum-exp
+ * ffn_unit.  The attention unit counts X, QKV, the probability or log-sum-exp
  * record, the context and the first LayerNorm's saved rows; the
  * feed-forward unit counts its input H1, GELU'(U), G and the second
  * LayerNorm's saved rows; each counts its own parameters and gradients.

@@ -140,14 +140,13 @@ struct stage {
   int64_t bytes_param = 0, bytes_act = 0;
   bool dry_run = false;
 
-  // Activation memory, sized for cap_T tokens and cap_BSS score entries.
+  // Activation memory, sized for cap_T tokens and cap_BSS probabilities.
   int64_t cap_T = -1, cap_BSS = -1, cap_B = -1, cap_NQB = -1;
   std::vector<void*> act_allocs;
   std::vector<Saved> saved;
   uint8_t* mask = nullptr;
   float* tmp = nullptr;     // [T, h] fp32 GEMM output before LayerNorm, or its partials
   void* h1lo = nullptr;     // [T, h] H1's bf16 rounding residual (bf16 stages)
-  float* scores = nullptr;  // [B*H, S, S] fp32 (scores, then dP; fp32 stages)
   int* kext = nullptr;      // [B] key extent of each sequence
   float* dsum = nullptr;    // [B*H, S] rowsum(dO * O) (bf16 stages)
   void* dS = nullptr;       // [B*H, S, S]
@@ -170,6 +169,8 @@ struct stage {
   float* splitk = nullptr;  // split-K partials of the weight gradients
   size_t splitk_elems = 0;  // elements it holds
   size_t splitk_bytes = 0;  // bytes counted for it in bytes_act
+  float* scores = nullptr;  // [B*H, S, S] scores, then dP (fp32 stages, S > ATTN_F32_MAX_S)
+  size_t scores_elems = 0, scores_bytes = 0;
 
   // Optional record of the gradient reaching each layer's output in the
   // latest backward (fp32 [T, h] per layer), for layer-wise checks.
@@ -306,9 +307,9 @@ void free_activations(stage_t* s) {
   s->rec.clear();
   s->rec_valid = false;
   s->bytes_act = 0;
-  s->splitk = nullptr;
-  s->splitk_elems = 0;
-  s->splitk_bytes = 0;
+  s->splitk = s->scores = nullptr;
+  s->splitk_elems = s->scores_elems = 0;
+  s->splitk_bytes = s->scores_bytes = 0;
   s->cap_T = s->cap_BSS = s->cap_B = s->cap_NQB = -1;
   s->have_ctx = false;
 }
@@ -355,19 +356,19 @@ size_t splitk_need(const stage_t* s, int64_t T) {
   return need;
 }
 
-// (Re)allocates the split-K partial buffer for at least `need` elements.
-stage_status grow_splitk(stage_t* s, size_t need) {
-  if (s->splitk) {
-    auto it = std::find(s->act_allocs.begin(), s->act_allocs.end(), (void*)s->splitk);
+// (Re)allocates a buffer whose size does not follow the token count (*elems
+// elements, *held bytes counted for it) for `need` elements.
+stage_status grow(stage_t* s, float** buf, size_t* elems, size_t* held, size_t need) {
+  if (*buf) {
+    auto it = std::find(s->act_allocs.begin(), s->act_allocs.end(), (void*)*buf);
     if (it != s->act_allocs.end()) s->act_allocs.erase(it);
-    (void)hipFree(s->splitk);
-    s->splitk = nullptr;
+    (void)hipFree(*buf);
+    *buf = nullptr;
   }
-  s->bytes_act -= (int64_t)s->splitk_bytes;
-  s->splitk_elems = 0;
-  s->splitk_bytes = 0;
+  s->bytes_act -= (int64_t)*held;
+  *elems = *held = 0;
   const size_t bytes = std::max<size_t>(need, 1) * 4;
-  stage_status st = dev_alloc(s, s->act_allocs, (void**)&s->splitk, bytes);
+  stage_status st = dev_alloc(s, s->act_allocs, (void**)buf, bytes);
   if (st) {
     // leave no half-built record: the next forward allocates from scratch
     std::string msg = s->err;
@@ -375,9 +376,15 @@ stage_status grow_splitk(stage_t* s, size_t need) {
     s->err = msg;
     return st;
   }
-  s->splitk_elems = need;
-  s->splitk_bytes = bytes;
+  *elems = need;
+  *held = bytes;
   return STAGE_OK;
+}
+stage_status grow_splitk(stage_t* s, size_t need) {
+  return grow(s, &s->splitk, &s->splitk_elems, &s->splitk_bytes, need);
+}
+stage_status grow_scores(stage_t* s, size_t need) {
+  return grow(s, &s->scores, &s->scores_elems, &s->scores_bytes, need);
 }
 
 // fp32 stages: the db_1 column sums are taken per 32 rows in the FFN2
@@ -394,14 +401,20 @@ int64_t colpart_ffn_rows(const stage_t* s, int64_t T) {
 
 stage_status ensure_activations(stage_t* s, int B, int S) {
   const int64_t T = (int64_t)B * S;
-  // The score matrix is materialised only on fp32 stages.
+  // Probabilities (and their gradient) are stored only on fp32 stages, scores
+  // only where their rows do not stay on chip.
   const int64_t BSS = s->dtype == STAGE_F32 ? (int64_t)B * s->H * S * S : 0;
+  const size_t n_scores = S > ATTN_F32_MAX_S ? (size_t)BSS : 0;
   const int64_t BHS = (int64_t)B * s->H * S;
   const int64_t NQB = (int64_t)B * ((S + 31) / 32);
   const size_t need = splitk_need(s, T);
   if (T <= s->cap_T && BSS <= s->cap_BSS && B <= s->cap_B && NQB <= s->cap_NQB &&
-      (int)s->saved.size() == s->L)
-    return need <= s->splitk_elems ? STAGE_OK : grow_splitk(s, need);
+      (int)s->saved.size() == s->L) {
+    stage_status st = STAGE_OK;
+    if (need > s->splitk_elems) st = grow_splitk(s, need);
+    if (!st && n_scores > s->scores_elems) st = grow_scores(s, n_scores);
+    return st;
+  }
   free_activations(s);
   const size_t e = s->esz;
   const int64_t h = s->h, f = s->f;
@@ -433,7 +446,7 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
           : T * h;
   if ((st = A((void**)&s->mask, T)) || (st = A((void**)&s->tmp, tmp_elems * 4)) ||
       (st = A(&s->h1lo, T * h * e)) ||
-      (st = A((void**)&s->scores, BSS * 4)) || (st = A(&s->dS, BSS * e)) ||
+      (st = A(&s->dS, BSS * e)) ||
       (st = A((void**)&s->kext, (size_t)B * 4)) || (st = A((void**)&s->dsum, BHS * 4)) ||
       (st = A(&s->dQKV, T * 3 * h * e)) || (st = A(&s->dZ2, T * h * e)) ||
       (st = A(&s->dU, T * f * e)) || (st = A(&s->dZ1, T * h * e)) || (st = A(&s->dC, T * h * e)))
@@ -456,7 +469,7 @@ stage_status ensure_activations(stage_t* s, int B, int S) {
     for (int l = 0; l < s->L; ++l)
       if ((st = A((void**)&s->rec[l], T * h * 4))) return st;
   }
-  if ((st = grow_splitk(s, need))) return st;
+  if ((st = grow_splitk(s, need)) || (st = grow_scores(s, n_scores))) return st;
   s->cap_T = T;
   s->cap_BSS = BSS;
   s->cap_B = B;

@@ -146,3 +146,45 @@ def test_memory_model_units_matches_allocations():
     torch.cuda.synchronize()
     assert st.device_bytes() == shared + attn + 2 * ffn
     st.close()
+
+
+def test_memory_model_scores_only_past_on_chip_rows():
+    """fp32 stages keep a score matrix beside the probabilities only for sequences
+    whose rows do not stay on chip (more than 512 tokens): the workspace then
+    grows by its B H S S floats, here from 512 to 513 tokens."""
+    import paper_2202_11836_amd as P
+    try:
+        P.load_library()
+    except RuntimeError as e:
+        pytest.skip(str(e))
+    h, H, f, B = 1024, 16, 4096, 32
+    at = {S: P.stage_memory_model(h, H, f, B, S, P.STAGE_F32)[1] for S in (511, 512, 513)}
+    scores = 4 * B * H * 513 * 513
+    step = at[512] - at[511]  # one more token everywhere else (dS and the [T, h] tensors)
+    assert scores < at[513] - at[512] - step / 2 < scores + step
+    # and at 512 tokens only one such matrix, dS
+    T = B * 512
+    assert at[512] < 4 * B * H * 512 * 512 + 4 * T * (10 * h + 2 * f) + (256 << 20)
+
+
+@pytest.mark.gpu
+def test_scores_grow_alone():
+    """Short and long sequences in turn on one fp32 stage: the score matrix is
+    allocated for the first long ones and kept."""
+    import torch
+
+    import paper_2202_11836_amd as P
+    print("case fp32 scores 16x512, 8x640 in turn", flush=True)
+    st = P.Stage(1, 128, 2, 256, seed=1, dtype="f32")
+    g = torch.Generator("cuda").manual_seed(7)
+    xs = [torch.randn(B, S, 128, device="cuda", generator=g) for B, S in ((16, 512), (8, 640))]
+    held, outs = [], []
+    for i in (0, 1, 0, 1):
+        y = st.forward(xs[i])
+        outs.append((y, st.backward(y)))
+        held.append(st.device_bytes())
+    torch.cuda.synchronize()
+    assert held[1] - held[0] >= 4 * 8 * 2 * 640 * 640 - 4 and held[1] == held[2] == held[3]
+    for a, b in ((0, 2), (1, 3)):
+        assert all(torch.equal(s, t) for s, t in zip(outs[a], outs[b]))
+    st.close()
