@@ -748,17 +748,20 @@ __global__ __launch_bounds__(256, 8) void wgrad_group_reduce_kernel(SkReduce rd)
   *(f32x4_t*)(out + i) = s;
 }
 
+}  // namespace
+
 int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
+  static const int cus = [] {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
       n = 256;
-    cus = n;
-  }
+    return n;
+  }();
   return cus;
 }
+
+namespace {
 
 template <int BM, int BN, bool AK, bool BKM, int EPI, bool OUTF32>
 hipError_t launch_bf16(const GemmArgs& g0, int batch, hipStream_t st) {

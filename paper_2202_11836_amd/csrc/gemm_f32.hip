@@ -32,10 +32,9 @@ namespace {
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// Largest number of 64 x 64 tiles for which 32 x 32 work-groups are used:
-// below one tile per CU the chip is part idle and a tile's latency is the
-// kernel's time.
-constexpr int64_t SMALL_TILES = 256;
+// 32 x 32 work-groups are used below one 64 x 64 tile per CU: the chip is part
+// idle then and a tile's latency is the kernel's time.
+inline bool few_tiles(int64_t t64) { return t64 < device_cus(); }
 
 enum F32Tile { T64x64, T64x32, T32x32 };
 template <F32Tile T>
@@ -601,15 +600,14 @@ bool fits(const GemmArgs& g) {
 int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
   return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
 }
-// 32 x 32 tiles below SMALL_TILES tiles of 64 x 64.  Otherwise a CU works
-// through its share of the tiles two or three at a time, and the fullest CU
-// is the time: 64 x 32 tiles (5% slower for their size) where they divide more
-// evenly.
+// 32 x 32 tiles below one 64 x 64 tile per CU.  Otherwise a CU works through its
+// share of the tiles two or three at a time, and the fullest CU is the time: 64 x
+// 32 tiles (5% slower for their size) where they divide more evenly.
 F32Tile f32_tile(const GemmArgs& g, int64_t batch) {
-  constexpr int64_t CUS = 256;
+  const int64_t cus = device_cus();
   const int64_t t64 = tiles_of(g, 64, 64) * batch, t32 = tiles_of(g, 64, 32) * batch;
-  if (t64 < SMALL_TILES) return T32x32;
-  return ((t32 + CUS - 1) / CUS) * 21 < ((t64 + CUS - 1) / CUS) * 40 ? T64x32 : T64x64;
+  if (few_tiles(t64)) return T32x32;
+  return ((t32 + cus - 1) / cus) * 21 < ((t64 + cus - 1) / cus) * 40 ? T64x32 : T64x64;
 }
 
 template <bool AK, bool BKM, int EPI>
@@ -621,7 +619,7 @@ hipError_t launch(const GemmArgs& g, int batch, hipStream_t st) {
   };
   if (vec) {
     // 16 x 16 tiles while they are one per CU (the line 32 x 32 tiles have too)
-    if (tiles_of(g, 16, 16) <= 256 && batch * g.ksplit == 1 && !g.colpart)
+    if (tiles_of(g, 16, 16) <= device_cus() && batch * g.ksplit == 1 && !g.colpart)
       hipLaunchKernelGGL((gemm_f32_16_kernel<AK, BKM, EPI>), grid(16, 16), dim3(256), 0, st, g);
     else if (t == T32x32)
       hipLaunchKernelGGL((gemm_f32_kernel<T32x32, AK, BKM, true, EPI>), grid(32, 32), dim3(256), 0, st, g);
@@ -671,7 +669,7 @@ hipError_t gemm_f32_attn_bwd(const GemmArgs& dv, const GemmArgs& dk, const GemmA
     if (g.M != dv.M || g.N != dv.N || g.ksplit != 1 || !fits(g)) return hipErrorInvalidValue;
     vec = vec && vec_ok(g, i == 2, false);
   }
-  const bool small = tiles_of(dv, 64, 64) * batch * n < SMALL_TILES;
+  const bool small = few_tiles(tiles_of(dv, 64, 64) * batch * n);
   const int r = small ? 32 : 64;
   const dim3 grid((unsigned)tiles_of(dv, r, r), n, (unsigned)batch);
   if (small && vec)
@@ -689,7 +687,7 @@ F32WgradPlan gemm_f32_wgrad_plan(int h, int f, int K) {
   // Two work-groups of 64 x 64 per CU over the layer's four gradients (h and f
   // are multiples of 64); k ranges of at least 256.
   const int64_t hb = h / 64, fb = f / 64, tiles = 4 * hb * hb + 2 * hb * fb;
-  int ks = (int)std::max<int64_t>(1, std::min<int64_t>(512 / tiles, K / 256));
+  int ks = (int)std::max<int64_t>(1, std::min<int64_t>(2 * device_cus() / tiles, K / 256));
   // Width 64 over so many tokens that the column partials of one-token sequences
   // fill the no-alloc backward's scratch: 6.3 MB of partials, what the scratch
   // has left for them (h = f = 64: 64 splits, not 85).
@@ -697,7 +695,7 @@ F32WgradPlan gemm_f32_wgrad_plan(int h, int f, int K) {
     ks = (int)std::max<int64_t>(1, std::min<int64_t>(ks, 128 * 3 * 64 * 64 / (tiles * 4096)));
   const int chunk = ((K + ks - 1) / ks + 63) / 64 * 64;
   ks = (K + chunk - 1) / chunk;
-  return {ks, tiles * ks < SMALL_TILES};
+  return {ks, few_tiles(tiles * ks)};
 }
 
 hipError_t gemm_f32_wgrad_group(const GemmArgs* p, float* const* out, int n, F32WgradPlan plan,

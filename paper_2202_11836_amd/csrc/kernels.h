@@ -64,6 +64,9 @@ inline GemmArgs gemm_args(const void* A, int64_t lda, const void* B, int64_t ldb
   return g;
 }
 
+// Compute units of the device (256 without one), asked once.
+int device_cus();
+
 // Tile shapes of the bf16 GEMMs: the first in gemm.hip (persistent work-
 // groups), the others in gemm_mid.hip.
 enum GemmTile {
