@@ -31,11 +31,11 @@ ROOFLINE_KERNELS = {
     # the four weight-gradient GEMMs of a layer, dW = dY^T X over all tokens
     # (split over tokens, fp32 partials), in one group launch: the kernel
     # with the largest share of step time
-    "wgrad_gemm": ("gemm_bf16_kernel<256, 256, false, false, 4, true, true>",
+    "wgrad_gemm": ("gemm_bf16_kernel<256, 256, false, false, 4, true>",
                    ["wgrad_group_gemm"]),
-    "ffn1_gelu_gemm": ("gemm_bf16_kernel<256, 256, true, true, 1, false, false>",
+    "ffn1_gelu_gemm": ("gemm_bf16_kernel<256, 256, true, true, 1, false>",
                        ["ffn1_gelu_gemm_fwd"]),
-    "ffn2_dgrad_dgelu_gemm": ("gemm_bf16_kernel<256, 256, true, true, 2, false, false>",
+    "ffn2_dgrad_dgelu_gemm": ("gemm_bf16_kernel<256, 256, true, false, 2, false>",
                               ["ffn2_dgrad_dgelu_gemm"]),
 }
 

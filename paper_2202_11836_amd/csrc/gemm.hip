@@ -1,9 +1,8 @@
-// Dense contractions of bf16 stages: MFMA GEMM (fp32 accumulate) with fused
-// epilogues.
+// Dense contractions of bf16 stages with many output tiles: MFMA GEMM (fp32
+// accumulate) with fused epilogues, and the tile rules of all bf16 GEMMs.
 //
-// A persistent work-group per CU walks BM x BN output tiles; its
-// wavefronts (8 for 256 x 256 tiles, two per SIMD; 4 otherwise) form a
-// 2 x (waves / 2) grid, each owning a sub-tile computed with
+// A persistent work-group per CU walks 256 x 256 output tiles; its 8 wavefronts
+// (two per SIMD) form a 2 x 4 grid, each owning a 128 x 64 sub-tile computed with
 // v_mfma_f32_32x32x16_bf16.  k-tiles of 64 go straight from HBM into a ring
 // of LDS slots with direct-to-LDS buffer loads, issued ahead of use, so no
 // staging registers and no LDS store instructions sit in the main loop, and
@@ -25,28 +24,21 @@ namespace {
 // -1.2% per stage step.)
 constexpr int TILE_GM = 4;
 
-// Linear tile index -> (z, m tile, n tile) for a persistent grid.  Work-group
+// Linear tile index -> (m tile, n tile) for a persistent grid.  Work-group
 // w starts on XCD w % 8 and keeps it (the grid is a multiple of 8), so the
 // tile ranges are dealt out per XCD as above.
-__device__ __forceinline__ void decode_tile(int vt, int total, int nbm, int nbn, int& z, int& tm,
-                                            int& tn, bool xcd_remap = true) {
+__device__ __forceinline__ void decode_tile(int vt, int total, int nbm, int nbn, int& tm, int& tn,
+                                            bool xcd_remap = true) {
   int bid = vt;
   if (xcd_remap && (total & 7) == 0) bid = (vt & 7) * (total >> 3) + (vt >> 3);
-  const int per_z = nbm * nbn;
-  z = bid / per_z;
-  const int r0 = bid - z * per_z;
   constexpr int GM = TILE_GM;
   const int per_group = GM * nbn;
-  const int group = r0 / per_group;
+  const int group = bid / per_group;
   const int first_m = group * GM;
   const int gsize = min(nbm - first_m, GM);
-  const int r = r0 - group * per_group;
+  const int r = bid - group * per_group;
   tm = first_m + r % gsize;
   tn = r / gsize;
-}
-
-__device__ __forceinline__ int64_t batch_off(int zb, int zdiv, int64_t s1, int64_t s2) {
-  return (int64_t)(zb / zdiv) * s1 + (int64_t)(zb % zdiv) * s2;
 }
 
 // ---------------------------------------------------------------------------
@@ -54,45 +46,31 @@ __device__ __forceinline__ int64_t batch_off(int zb, int zdiv, int64_t s1, int64
 //
 // Block = 2 x (waves / 2) wavefronts over a BM x BN tile; each wavefront
 // owns a (BM/2) x (BN/(waves/2)) sub-tile = TM x TN accumulators of 32 x 32.
-// k-tiles of 64 sit in a ring of NS LDS slots (with the epilogue staging
-// area, up to the full 160 KB of a gfx950 CU), one barrier per k-tile.  The
+// k-tiles of 64 sit in a ring of two LDS slots (with the epilogue staging
+// area, the full 160 KB of a gfx950 CU), one barrier per k-tile.  The
 // epilogue stages each 16-row half of a wavefront's 32-row slab through LDS
-// (fp32) so that bias / activation / residual operands are read and the
-// results written as 16-byte row segments.
+// (fp32) so that bias / activation operands are read and the results written
+// as 16-byte row segments.
 // ---------------------------------------------------------------------------
-// k-tile depth and ring depth per tile shape: a ring of NS k-tiles of BK
-// keeps NS - 1 k-tiles in flight behind the one being consumed.
-// (A deeper ring of k-tiles of 32 was measured slower for 256 x 256: twice
-// the barriers per k, and the loads are not the limit at this depth.)
+// (A deeper ring of k-tiles of 32 was measured slower: twice the barriers per
+// k, and the loads are not the limit at this depth.)
 template <int BM, int BN>
-struct RingShape {
-  static constexpr int BK = 64;
-  static constexpr int NS = BN == 256 ? 2 : 3;
-  // Wavefronts per work-group: 2 along m times WAVES / 2 along n.  The
-  // 256 x 256 tile runs 8 (two per SIMD, 128 x 64 each): while one
-  // wavefront waits on loads, a barrier or its epilogue, the other's MFMAs
-  // keep the matrix core busy.
-  static constexpr int WAVES = (BM == 256 && BN == 256) ? 8 : 4;
-};
-
-template <int BM, int BN, bool AK, bool BKM>
 struct TileCfg {
-  static constexpr int BK = RingShape<BM, BN>::BK;
-  static constexpr int NS = RingShape<BM, BN>::NS;
-  static constexpr int WAVES = RingShape<BM, BN>::WAVES;
+  static constexpr int BK = 64;
+  static constexpr int NS = 2;
+  // 8 wavefronts, two per SIMD: while one waits on loads, a barrier or its
+  // epilogue, the other's MFMAs keep the matrix core busy.
+  static constexpr int WAVES = 8;
   static constexpr int WGN = WAVES / 2;
   static constexpr int THREADS = 64 * WAVES;
   static constexpr int WM = BM / 2, WN = BN / WGN;
   static constexpr int TM = WM / 32, TN = WN / 32;
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  // direct-to-LDS load instructions per k-tile per wavefront (1 KB each)
-  static constexpr int DMA_PER_TILE = STAGE_BYTES / 1024 / WAVES;
   // Epilogue staging, beside the ring: 16 rows x WN fp32 per wavefront.
   static constexpr int EPI_BYTES = WAVES * 16 * WN * 4;
   static constexpr int LDS_BYTES = NS * STAGE_BYTES + EPI_BYTES;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
-  static_assert((NS - 2) * DMA_PER_TILE <= 63, "vmcnt range");
   static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0,
                 "whole 1 KB blocks per wavefront");
 };
@@ -102,22 +80,20 @@ struct TileOps {
   __amdgpu_buffer_rsrc_t rsA, rsB;
   int kA0, kB0;     // first k of the range, relative to each resource
   int ntiles;       // k-tiles
-  int m0, n0, zs, zb;
+  int m0, n0, zs;
 };
 
-// Operands of output tile (tm, tn) of batch entry zb over k in [kbeg, kend),
-// partial slot zs.
+// Operands of output tile (tm, tn) over k in [kbeg, kend), partial slot zs.
 template <int BM, int BN, bool AK, bool BKM>
-__device__ __forceinline__ TileOps tile_ops_at(const GemmArgs& g, int zs, int zb, int tm, int tn,
+__device__ __forceinline__ TileOps tile_ops_at(const GemmArgs& g, int zs, int tm, int tn,
                                                int kbeg, int kend) {
   TileOps o;
   o.zs = zs;
-  o.zb = zb;
   o.m0 = tm * BM;
   o.n0 = tn * BN;
-  const bf16_t* A = (const bf16_t*)g.A + batch_off(o.zb, g.zdiv, g.sA1, g.sA2);
-  const bf16_t* B = (const bf16_t*)g.B + batch_off(o.zb, g.zdiv, g.sB1, g.sB2);
-  constexpr int BK = TileCfg<BM, BN, AK, BKM>::BK;
+  const bf16_t* A = (const bf16_t*)g.A;
+  const bf16_t* B = (const bf16_t*)g.B;
+  constexpr int BK = TileCfg<BM, BN>::BK;
   o.ntiles = (kend - kbeg + BK - 1) / BK;
   // k-major: from the tile's first row to the operand's last row (rows past
   // it read 0; K is a multiple of 64).  m/n-major: from the range's first
@@ -143,32 +119,19 @@ __device__ __forceinline__ TileOps tile_ops_at(const GemmArgs& g, int zs, int zb
 
 template <int BM, int BN, bool AK, bool BKM>
 __device__ __forceinline__ TileOps tile_ops(const GemmArgs& g, int vt, int total, int nbm, int nbn) {
-  int z, tm, tn;
-  decode_tile(vt, total, nbm, nbn, z, tm, tn);
-  const int kbeg = (z % g.ksplit) * g.kchunk;
-  return tile_ops_at<BM, BN, AK, BKM>(g, z % g.ksplit, z / g.ksplit, tm, tn, kbeg,
-                                      min(g.K, kbeg + g.kchunk));
+  int tm, tn;
+  decode_tile(vt, total, nbm, nbn, tm, tn);
+  return tile_ops_at<BM, BN, AK, BKM>(g, 0, tm, tn, 0, g.K);
 }
 
 // k-tile t of an output tile -> ring slot t % NS.
 template <int BM, int BN, bool AK, bool BKM>
 __device__ __forceinline__ void issue_ktile(const GemmArgs& g, const TileOps& T, int t, char* smem,
                                             int wave, int lane) {
-  using C = TileCfg<BM, BN, AK, BKM>;
+  using C = TileCfg<BM, BN>;
   char* b = smem + (t % C::NS) * C::STAGE_BYTES;
   dma_tile<BM, AK, C::BK, C::WAVES>(T.rsA, g.lda, T.kA0 + t * C::BK, b, wave, lane);
   dma_tile<BN, BKM, C::BK, C::WAVES>(T.rsB, g.ldb, T.kB0 + t * C::BK, b + C::A_BYTES, wave, lane);
-}
-
-// Wait until k-tile t + 1 has landed, given that `after` later k-tiles
-// (0 .. NS - 2) have been requested since: the loads complete in order.
-template <int PER, int NS>
-__device__ __forceinline__ void wait_ktile(int after) {
-  if (NS > 5 && after >= 4) wait_vm_lgkm0<(NS > 5 ? 4 * PER : 0)>();
-  else if (NS > 4 && after >= 3) wait_vm_lgkm0<(NS > 4 ? 3 * PER : 0)>();
-  else if (NS > 3 && after >= 2) wait_vm_lgkm0<(NS > 3 ? 2 * PER : 0)>();
-  else if (NS > 2 && after >= 1) wait_vm_lgkm0<(NS > 2 ? PER : 0)>();
-  else wait_vm_lgkm0<0>();
 }
 
 // Group launch (stream-K).  Range r of the G work-groups covers k-tiles
@@ -226,7 +189,7 @@ __host__ __device__ __forceinline__ void sk_tile_ranges(const SkSeq& q, int t, i
 }
 
 // Position of tile (tm, tn) in a problem's tile order (the inverse of
-// decode_tile for one z slice, without the XCD remap).
+// decode_tile, without the XCD remap).
 __host__ __device__ __forceinline__ int tile_pos(int tm, int tn, int nbm, int nbn) {
   const int group = tm / TILE_GM, first_m = group * TILE_GM;
   const int gsize = min(nbm - first_m, TILE_GM);
@@ -241,49 +204,28 @@ __device__ __forceinline__ kgroup_t* group_table() {
   return (kgroup_t*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// What a weight gradient uses of problem p's arguments.
 __device__ __forceinline__ void group_args(kgroup_t* gg, int p, GemmArgs& g) {
   const __attribute__((address_space(4))) GemmArgs* a = &gg->g[p];
   g.A = a->A;
   g.B = a->B;
   g.C = a->C;
-  g.C2 = a->C2;
-  g.bias = a->bias;
-  g.aux = a->aux;
-  g.aux2 = a->aux2;
-  g.dsum = a->dsum;
-  g.dsum_S = a->dsum_S;
   g.M = a->M;
   g.N = a->N;
   g.K = a->K;
   g.lda = a->lda;
   g.ldb = a->ldb;
   g.ldc = a->ldc;
-  g.ldaux = a->ldaux;
-  g.zdiv = a->zdiv;
-  g.sA1 = a->sA1;
-  g.sA2 = a->sA2;
-  g.sB1 = a->sB1;
-  g.sB2 = a->sB2;
-  g.sC1 = a->sC1;
-  g.sC2 = a->sC2;
-  g.ksplit = a->ksplit;
-  g.kchunk = a->kchunk;
-  g.alpha = a->alpha;
-  g.tile = a->tile;
-  g.colpart = a->colpart;
-  g.cp_batch = a->cp_batch;
-  g.cp_ld = a->cp_ld;
-  g.zdiv_total = a->zdiv_total;
 }
 
 // Persistent kernel: each work-group walks output tiles vt = blockIdx.x,
 // + gridDim.x, ... (GROUP: the pieces of its stream-K range, see sk_begin).
 // The first NS k-tiles of the next output tile are loaded while the current
 // tile's epilogue runs.
-template <int BM, int BN, bool AK, bool BKM, int EPI, bool OUTF32, bool GROUP = false>
-__global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_kernel(
+template <int BM, int BN, bool AK, bool BKM, int EPI, bool GROUP = false>
+__global__ __launch_bounds__((TileCfg<BM, BN>::THREADS), 1) void gemm_bf16_kernel(
     typename std::conditional<GROUP, GemmGroup, GemmArgs>::type ka) {
-  using C = TileCfg<BM, BN, AK, BKM>;
+  using C = TileCfg<BM, BN>;
   constexpr int TM = C::TM, TN = C::TN, NS = C::NS;
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
 
@@ -311,12 +253,12 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     group_args(gt, q, g);
     nbm = (g.M + BM - 1) / BM;
     nbn = (g.N + BN - 1) / BN;
-    int z, tm, tn;
-    decode_tile(t - gt->tile0[q], nbm * nbn, nbm, nbn, z, tm, tn, false);
+    int tm, tn;
+    decode_tile(t - gt->tile0[q], nbm * nbn, nbm, nbn, tm, tn, false);
     int a1, n1, a2, n2;
     sk_tile_ranges(sq, t, a1, n1, a2, n2);
     const int slot = k0 < gt->kf ? rg - a1 : n1 + rg - a2;
-    T = tile_ops_at<BM, BN, AK, BKM>(g, slot, 0, tm, tn, k0 * C::BK,
+    T = tile_ops_at<BM, BN, AK, BKM>(g, slot, tm, tn, k0 * C::BK,
                                      min(g.K, (k0 + plen) * C::BK));
   };
   if constexpr (GROUP) {
@@ -332,7 +274,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     vt = blockIdx.x;
     nbm = (g.M + BM - 1) / BM;
     nbn = (g.N + BN - 1) / BN;
-    total = nbm * nbn * g.zdiv_total;
+    total = nbm * nbn;
     if (vt >= total) return;
     T = tile_ops<BM, BN, AK, BKM>(g, vt, total, nbm, nbn);
   }
@@ -378,24 +320,12 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     constexpr int ECH = C::WN / 8;  // 8-column chunks per staged row
     static_assert(64 % ECH == 0, "a lane's chunks share their columns");
     constexpr bool BIAS = EPI == EPI_STORE || EPI == EPI_GELU;
-    // fp32 outputs are stored straight from the accumulators (see the
-    // epilogue): the lane's bias is then one value per 32-column block.
-    constexpr bool DIRECT = EPI == EPI_PARTIAL || (EPI == EPI_STORE && OUTF32);
-    static_assert(TN <= 4, "one bias value per 32-column block");
     f32x4_t bias0 = {0, 0, 0, 0}, bias1 = {0, 0, 0, 0};
     if (BIAS && g.bias) {
-      if constexpr (DIRECT) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int bn = T.n0 + wn * C::WN + 32 * j + (lane & 31);
-          bias0[j] = bn < g.N ? g.bias[bn] : 0.0f;
-        }
-      } else {
-        const int bn = T.n0 + wn * C::WN + (lane % ECH) * 8;
-        if (bn < g.N) {
-          bias0 = *(const f32x4_t*)(g.bias + bn);
-          bias1 = *(const f32x4_t*)(g.bias + bn + 4);
-        }
+      const int bn = T.n0 + wn * C::WN + (lane % ECH) * 8;
+      if (bn < g.N) {
+        bias0 = *(const f32x4_t*)(g.bias + bn);
+        bias1 = *(const f32x4_t*)(g.bias + bn + 4);
       }
     }
     wait_vm_lgkm0<0>();
@@ -417,17 +347,15 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     // request their part of k-tile t + NS right after that barrier; the
     // other half request theirs at the start of k-tile t + 1.  Issuing the
     // direct-to-LDS loads stalls a wavefront until the CU's address unit
-    // takes them (64 KB per k-tile for 256 x 256), and wavefronts w and
+    // takes them (64 KB per k-tile), and wavefronts w and
     // w + 4 share a SIMD: split this way, one of each pair issues MFMAs
     // while the other issues its loads, instead of both stalling at once.
     // The slot is free for both halves: its last reads (k-tile t) completed
     // before the barrier.  Before the wait at the end of any k-tile both
     // halves have requested the same k-tiles, so that wait is unchanged.
-    // Measured (same box): 256 x 256 encoder GEMM set -3.9%, weight-
-    // gradient group -5%, 8192^3 -3%, 256 x 128 tiles at 4096 tokens -2% to
-    // -11%; splitting the pairs the other way (even / odd wavefronts) or each
-    // wavefront's own loads in two gave
-    // -0.3% to -1.6%; requesting the second half one or two k-steps later
+    // Measured (same box): encoder GEMM set -3.9%, weight-gradient group -5%,
+    // 8192^3 -3%; splitting the pairs the other way (even / odd wavefronts) or
+    // each wavefront's own loads in two gave -0.3% to -1.6%; requesting the second half one or two k-steps later
     // was slower than not splitting.
     for (int t = 0; t < ntiles; ++t) {
       static_for<0, KS>([&](auto ksc) {
@@ -459,7 +387,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
           // Unconditional (also for the last k-tile, whose "next" fragments
           // are never used): a branch here would make the compiler wait for
           // these reads before the last k-step's MFMAs.
-          wait_ktile<C::DMA_PER_TILE, NS>(min(ntiles - 1, t + NS - 1) - (t + 1));
+          wait_vm_lgkm0<0>();
           __syncthreads();
           if (t + NS < ntiles && wave < C::WAVES / 2)
             issue_ktile<BM, BN, AK, BKM>(g, T, t + NS, smem, wave, lane);
@@ -532,16 +460,15 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     // Start the next output tile's first NS k-tiles, then run this tile's
     // epilogue (its staging area is separate from the ring).
     __syncthreads();
-    const int m0 = T.m0, n0 = T.n0, zs = T.zs, zb = T.zb;
+    const int m0 = T.m0, n0 = T.n0, zs = T.zs;
     const GemmArgs ge = g;  // this tile's problem (g moves on to the next tile's)
-    const int64_t offC = batch_off(zb, ge.zdiv, ge.sC1, ge.sC2);
     const int mw = m0 + wm * C::WM, nw = n0 + wn * C::WN;
     constexpr int CH = C::WN / 8;  // 8-column chunks per staged row
     constexpr int QN = 16 * CH / 64;  // chunks per lane per staged 16-row half
-    // EPI_MUL / EPI_RESID read one bf16 operand chunk per output chunk; the
+    // EPI_MUL reads one bf16 operand chunk per output chunk; the
     // chunks of the next staged half are loaded while this one is processed
     // (the first ones before the next tile's k-tiles are requested).
-    constexpr bool AUX = EPI == EPI_MUL || EPI == EPI_RESID;
+    constexpr bool AUX = EPI == EPI_MUL;
     u32x4_t axv[2][QN];
     auto aux_load = [&](int it, u32x4_t* dst) {
 #pragma unroll
@@ -550,7 +477,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
         const int row = c / CH, col = (c % CH) * 8;
         const int m = mw + (it >> 1) * 32 + 16 * (it & 1) + row, n = nw + col;
         dst[q] = (m < ge.M && n < ge.N)
-                     ? *(const u32x4_t*)((const bf16_t*)ge.aux + offC + (int64_t)m * ge.ldaux + n)
+                     ? *(const u32x4_t*)((const bf16_t*)ge.aux + (int64_t)m * ge.ldaux + n)
                      : u32x4_t{0, 0, 0, 0};
       }
     };
@@ -572,11 +499,11 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
           if (t < T.ntiles) issue_ktile<BM, BN, AK, BKM>(g, T, t, smem, wave, lane);
       }
     };
-    // EPI_MUL / EPI_RESID read an operand per output chunk.  Loads and
-    // stores share one counter, so a load waited for after stores drains
-    // the stores too: these epilogues compute every chunk first (results
-    // packed into the registers the consumed accumulators free), then
-    // request the next tile's k-tiles and store.  The others request the
+    // EPI_MUL reads an operand per output chunk.  Loads and stores share one
+    // counter, so a load waited for after stores drains the stores too: this
+    // epilogue computes every chunk first (results packed into the registers
+    // the consumed accumulators free), then requests the next tile's k-tiles
+    // and stores.  The others request the
     // k-tiles first and store as they go.
     if constexpr (!AUX) issue_next();
     u32x4_t res[AUX ? 2 * TM : 1][QN];
@@ -587,16 +514,15 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
     // the wavefront's LDS area as fp32; columns are XOR-swizzled by 32 on
     // rows 4-7 / 12-15 so the two lane halves' stores hit different banks.
     float* stg = (float*)(smem + NS * C::STAGE_BYTES) + wave * 16 * C::WN;
-    // Optional column sums (EPI_MUL): every lane keeps one 8-column chunk
-    // (CH divides 64) over the rows it writes.
-    constexpr bool COLSUM = EPI == EPI_MUL && (CH == 16 || CH == 8) && C::WM == 128;
+    // Column sums (EPI_MUL): every lane keeps one 8-column chunk (CH divides
+    // 64) over the rows it writes.
+    static_assert(64 % CH == 0 && C::WM == 128, "column sums per 128 rows");
     float csum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (DIRECT) {
-      // fp32 results (split-K partials, or alpha * acc + bias) straight
-      // from the accumulators, no LDS round trip: for each register, lanes
-      // 0-31 and 32-63 write 32 consecutive columns of two rows, whole
-      // 128-byte lines.
-      float* Cp = (float*)ge.C + (EPI == EPI_PARTIAL ? (int64_t)zs * ge.M * ge.ldc : offC);
+    if constexpr (EPI == EPI_PARTIAL) {
+      // fp32 results straight from the accumulators, no LDS round trip: for
+      // each register, lanes 0-31 and 32-63 write 32 consecutive columns of
+      // two rows, whole 128-byte lines.
+      float* Cp = (float*)ge.C + (int64_t)zs * ge.M * ge.ldc;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -605,12 +531,7 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int m = mw + i * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-            float v = acc[i][j][r];
-            if (EPI == EPI_STORE) {
-              v *= ge.alpha;
-              if (ge.bias) v += bias0[j];
-            }
-            if (m < ge.M && n < ge.N) Cp[(int64_t)m * ge.ldc + n] = v;
+            if (m < ge.M && n < ge.N) Cp[(int64_t)m * ge.ldc + n] = acc[i][j][r];
           }
         }
     } else {
@@ -646,16 +567,16 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
               v[4 + e] = x1[e];
             }
             if constexpr (AUX) {
-              res[it][q] = aux8<EPI>(v, axv[it & 1][q]);
+              res[it][q] = mul8(v, axv[it & 1][q]);
               // keep the packed result here (not recomputed from fp32 values
               // held until the stores)
               asm volatile("" : "+v"(res[it][q]));
-              if (COLSUM && m < ge.M && n < ge.N) {
+              if (m < ge.M && n < ge.N) {
   #pragma unroll
                 for (int e = 0; e < 8; ++e) csum[e] += v[e];
               }
             } else if (m < ge.M && n < ge.N) {
-              epi8<EPI, OUTF32>(ge, offC, zs, m, n, v, u32x4_t{0, 0, 0, 0}, bias0, bias1);
+              epi8<EPI>(ge, zs, m, n, v, bias0, bias1);
             }
           }
           __builtin_amdgcn_wave_barrier();
@@ -672,10 +593,10 @@ __global__ __launch_bounds__((64 * RingShape<BM, BN>::WAVES), 1) void gemm_bf16_
           const int row = c / CH, col = (c % CH) * 8;
           const int m = mw + (it >> 1) * 32 + 16 * (it & 1) + row, n = nw + col;
           if (m < ge.M && n < ge.N)
-            *(u32x4_t*)((bf16_t*)ge.C + offC + (int64_t)m * ge.ldc + n) = res[it][q];
+            *(u32x4_t*)((bf16_t*)ge.C + (int64_t)m * ge.ldc + n) = res[it][q];
         }
     }
-    if (COLSUM && ge.colpart) {
+    if (AUX && ge.colpart) {
       // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same columns: fixed-order sum
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -763,17 +684,15 @@ int device_cus() {
 
 namespace {
 
-template <int BM, int BN, bool AK, bool BKM, int EPI, bool OUTF32>
-hipError_t launch_bf16(const GemmArgs& g0, int batch, hipStream_t st) {
-  GemmArgs g = g0;
-  g.zdiv_total = batch * g.ksplit;
-  const int64_t total = (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.zdiv_total;
+template <bool AK, bool BKM, int EPI>
+hipError_t launch_256(const GemmArgs& g, hipStream_t st) {
+  const int64_t total = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
   // One work-group per CU (LDS and registers allow no more); a multiple of
   // 8 so that each work-group stays on one XCD's share of the tiles.
   int64_t grid = std::min<int64_t>(total, device_cus());
   if (grid >= 8) grid -= grid % 8;
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, AK, BKM, EPI, OUTF32>), dim3((unsigned)grid),
-                     dim3(TileCfg<BM, BN, AK, BKM>::THREADS), 0, st, g);
+  hipLaunchKernelGGL((gemm_bf16_kernel<256, 256, AK, BKM, EPI>), dim3((unsigned)grid),
+                     dim3(TileCfg<256, 256>::THREADS), 0, st, g);
   return hipGetLastError();
 }
 
@@ -803,12 +722,12 @@ hipError_t gemm_bf16(const GemmArgs& g0, bool b_kmajor, GemmEpi epi, hipStream_t
   if (g.tile == 0) g.tile = gemm_bf16_plan(g.M, g.N, g.K, b_kmajor, epi, false).tile;
   if (g.tile == GEMM_TILE_256x256 && g.ksplit == 1) {
     if (b_kmajor) {
-      if (epi == EPI_STORE) return launch_bf16<256, 256, true, true, EPI_STORE, false>(g, 1, st);
-      if (epi == EPI_GELU) return launch_bf16<256, 256, true, true, EPI_GELU, false>(g, 1, st);
-      if (epi == EPI_PARTIAL) return launch_bf16<256, 256, true, true, EPI_PARTIAL, true>(g, 1, st);
+      if (epi == EPI_STORE) return launch_256<true, true, EPI_STORE>(g, st);
+      if (epi == EPI_GELU) return launch_256<true, true, EPI_GELU>(g, st);
+      if (epi == EPI_PARTIAL) return launch_256<true, true, EPI_PARTIAL>(g, st);
     } else {
-      if (epi == EPI_STORE) return launch_bf16<256, 256, true, false, EPI_STORE, false>(g, 1, st);
-      if (epi == EPI_MUL) return launch_bf16<256, 256, true, false, EPI_MUL, false>(g, 1, st);
+      if (epi == EPI_STORE) return launch_256<true, false, EPI_STORE>(g, st);
+      if (epi == EPI_MUL) return launch_256<true, false, EPI_MUL>(g, st);
     }
     return hipErrorInvalidValue;
   }
@@ -933,12 +852,7 @@ bool group_table_of(const GemmArgs* p, int n, GemmGroup& gg) {
   gg.n = n;
   int64_t tiles = 0;
   for (int q = 0; q < n; ++q) {
-    GemmArgs g = p[q];
-    g.zdiv = 1;
-    g.ksplit = 1;
-    g.kchunk = g.K;
-    g.zdiv_total = 1;
-    g.sA1 = g.sA2 = g.sB1 = g.sB2 = g.sC1 = g.sC2 = 0;
+    const GemmArgs& g = p[q];
     gg.g[q] = g;
     gg.tile0[q] = (int)tiles;
     tiles += (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
@@ -1015,8 +929,8 @@ hipError_t gemm_bf16_wgrad_group(const GemmArgs* p, int n, hipStream_t st) {
   GemmGroup gg;
   if (!group_table_of(p, n, gg)) return hipErrorInvalidValue;
   if (gg.work == 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_bf16_kernel<256, 256, false, false, EPI_PARTIAL, true, true>),
-                     dim3((unsigned)group_grid()), dim3(TileCfg<256, 256, false, false>::THREADS),
+  hipLaunchKernelGGL((gemm_bf16_kernel<256, 256, false, false, EPI_PARTIAL, true>),
+                     dim3((unsigned)group_grid()), dim3(TileCfg<256, 256>::THREADS),
                      0, st, gg);
   return hipGetLastError();
 }

@@ -301,7 +301,7 @@ __device__ __forceinline__ void mid_body(const GemmArgs& g, int zs, int tm, int 
     }
     if (m < g.M && n < g.N) {
       if constexpr (AUX) {
-        const u32x4_t o = aux8<EPI>(v, ax[q]);
+        const u32x4_t o = mul8(v, ax[q]);
         *(u32x4_t*)((bf16_t*)g.C + (int64_t)m * g.ldc + n) = o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) cs[e] += v[e];
@@ -324,7 +324,7 @@ __device__ __forceinline__ void mid_body(const GemmArgs& g, int zs, int tm, int 
         for (int x = 1; x < 8; x <<= 1) d += __shfl_xor(d, x, 64);
         if ((tid & 7) == 0) g.dsum[((int64_t)sb * (g.N >> 6) + (n >> 6)) * g.dsum_S + ss] = d;
       } else {
-        epi8<EPI, false>(g, 0, zs, m, n, v, u32x4_t{0, 0, 0, 0}, b0, b1);
+        epi8<EPI>(g, zs, m, n, v, b0, b1);
       }
     }
     if constexpr (DSUM)
@@ -474,7 +474,7 @@ hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
   w.tail = tail;
   if (!tail_prepare(w.tail)) return hipErrorInvalidValue;
   const int bm = tile == GEMM_TILE_64x64 ? 64 : tile == GEMM_TILE_256x128 ? 256 : 128;
-  const int bn = tile == GEMM_TILE_64x64 || tile == GEMM_TILE_128x64 ? 64 : 128;
+  const int bn = tile == GEMM_TILE_64x64 ? 64 : 128;
   int64_t blocks = 0;
   for (int q = 0; q < n; ++q) {
     if (p[q].ldc != p[q].N) return hipErrorInvalidValue;
@@ -497,9 +497,6 @@ hipError_t gemm_mid_wgrad(const GemmArgs* p, float* const* out, int n, int tile,
       break;
     case GEMM_TILE_128x128:
       hipLaunchKernelGGL((gemm_mid_wgrad_kernel<128, 128>), grid, dim3(MidCfg<128, 128>::THREADS), 0, st, w);
-      break;
-    case GEMM_TILE_128x64:
-      hipLaunchKernelGGL((gemm_mid_wgrad_kernel<128, 64>), grid, dim3(MidCfg<128, 64>::THREADS), 0, st, w);
       break;
     case GEMM_TILE_64x64:
       hipLaunchKernelGGL((gemm_mid_wgrad_kernel<64, 64>), grid, dim3(MidCfg<64, 64>::THREADS), 0, st, w);

@@ -29,8 +29,8 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // dma_tile issues the direct-to-LDS loads (buffer_load ... lds, 16 bytes per
 // lane; lane l of a load lands at LDS base + 16 l) that fill one operand tile
 // of k-tile k0 (k relative to the resource, see the kernel), so the tile
-// never passes through VGPRs.  Each 1 KB block is one instruction; the 4
-// wavefronts split the blocks.
+// never passes through VGPRs.  Each 1 KB block is one instruction; the W
+// wavefronts of the work-group split the blocks.
 template <int BK>
 __device__ __forceinline__ int kswz(int r) {
   return BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3);
@@ -143,49 +143,29 @@ struct FragPtrs {
 };
 
 
-// Epilogue for 8 consecutive columns n..n+7 of row m (n % 8 == 0, n < N).
-// b0, b1: bias[n .. n + 7] (EPI_STORE with a bias, EPI_GELU), loaded once
-// per tile by the caller.  For EPI_MUL, v returns the values as stored.
-template <int EPI, bool OUTF32>
-__device__ __forceinline__ void epi8(const GemmArgs& g, int64_t offC, int zs, int m, int n,
-                                     float v[8], u32x4_t x, f32x4_t b0, f32x4_t b1) {
+// Epilogue for 8 consecutive columns n..n+7 of row m (n % 8 == 0, n < N):
+// EPI_STORE, EPI_GELU, EPI_PARTIAL (slot zs).
+// b0, b1: bias[n .. n + 7], loaded once per tile by the caller.
+template <int EPI>
+__device__ __forceinline__ void epi8(const GemmArgs& g, int zs, int m, int n, float v[8], f32x4_t b0,
+                                     f32x4_t b1) {
+  static_assert(EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_PARTIAL, "");
   const int64_t idx = (int64_t)m * g.ldc + n;
-  if (EPI == EPI_PARTIAL) {
+  if constexpr (EPI == EPI_PARTIAL) {
     float* C = (float*)g.C + (int64_t)zs * g.M * g.ldc + idx;
     *(f32x4_t*)C = f32x4_t{v[0], v[1], v[2], v[3]};
     *(f32x4_t*)(C + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
     return;
   }
-  if (EPI == EPI_STORE || EPI == EPI_GELU) {
-    if (EPI == EPI_STORE) {
+  if (EPI == EPI_STORE) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] *= g.alpha;
-    }
-    if (g.bias) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] += b0[i];
-        v[4 + i] += b1[i];
-      }
-    }
+    for (int i = 0; i < 8; ++i) v[i] *= g.alpha;
   }
-  if (EPI == EPI_STORE && OUTF32) {
-    float* C = (float*)g.C + offC + idx;
-    *(f32x4_t*)C = f32x4_t{v[0], v[1], v[2], v[3]};
-    *(f32x4_t*)(C + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
-    return;
-  }
-  if (EPI == EPI_MUL || EPI == EPI_RESID) {
+  if (g.bias) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float a0 = __uint_as_float(x[i] << 16), a1 = __uint_as_float(x[i] & 0xffff0000u);
-      if (EPI == EPI_MUL) {
-        v[2 * i] *= a0;
-        v[2 * i + 1] *= a1;
-      } else {
-        v[2 * i] += a0;
-        v[2 * i + 1] += a1;
-      }
+      v[i] += b0[i];
+      v[4 + i] += b1[i];
     }
   }
   if (EPI == EPI_GELU) {
@@ -204,39 +184,24 @@ __device__ __forceinline__ void epi8(const GemmArgs& g, int64_t offC, int zs, in
       o[i] = pack_bf16x2(gv[0], gv[1]);
       q[i] = pack_bf16x2(dv[0], dv[1]);
     }
-    *(u32x4_t*)((bf16_t*)g.C + offC + idx) = o;
-    *(u32x4_t*)((bf16_t*)g.C2 + offC + idx) = q;
+    *(u32x4_t*)((bf16_t*)g.C + idx) = o;
+    *(u32x4_t*)((bf16_t*)g.C2 + idx) = q;
     return;
   }
   u32x4_t o;
 #pragma unroll
   for (int i = 0; i < 4; ++i) o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-  *(u32x4_t*)((bf16_t*)g.C + offC + idx) = o;
-  if (EPI == EPI_MUL) {  // hand back the stored (rounded) values
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = __uint_as_float(o[i] << 16);
-      v[2 * i + 1] = __uint_as_float(o[i] & 0xffff0000u);
-    }
-  }
-
+  *(u32x4_t*)((bf16_t*)g.C + idx) = o;
 }
 
-// EPI_MUL / EPI_RESID on 8 values: v * aux or v + aux (aux: 8 packed bf16),
-// rounded to bf16 and packed; v returns the rounded values.
-template <int EPI>
-__device__ __forceinline__ u32x4_t aux8(float v[8], u32x4_t x) {
+// EPI_MUL on 8 values: v * aux (aux: 8 packed bf16), rounded to bf16 and packed;
+// v returns the rounded values.
+__device__ __forceinline__ u32x4_t mul8(float v[8], u32x4_t x) {
   u32x4_t o;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float a0 = __uint_as_float(x[i] << 16), a1 = __uint_as_float(x[i] & 0xffff0000u);
-    if (EPI == EPI_MUL) {
-      v[2 * i] *= a0;
-      v[2 * i + 1] *= a1;
-    } else {
-      v[2 * i] += a0;
-      v[2 * i + 1] += a1;
-    }
+    v[2 * i] *= __uint_as_float(x[i] << 16);
+    v[2 * i + 1] *= __uint_as_float(x[i] & 0xffff0000u);
     o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
     v[2 * i] = __uint_as_float(o[i] << 16);
     v[2 * i + 1] = __uint_as_float(o[i] & 0xffff0000u);

@@ -11,7 +11,7 @@
 // GEMM:  C[m, n] = sum_k A(m, k) * B(k, n), then an epilogue.
 //   A(m, k) = A[m * lda + k]  if a_kmajor  else  A[k * lda + m]
 //   B(k, n) = B[n * ldb + k]  if b_kmajor  else  B[k * ldb + n]
-// Batched over grid z: batch index zb splits into (zb / zdiv, zb % zdiv),
+// fp32, batched over grid z: batch index zb splits into (zb / zdiv, zb % zdiv),
 // and each operand is offset by (zb / zdiv) * s*1 + (zb % zdiv) * s*2.
 // With ksplit > 1 the K range is cut into ksplit chunks of kchunk elements
 // and each chunk writes an fp32 partial to C + split * M * ldc (EPI_PARTIAL).
@@ -20,7 +20,7 @@ enum GemmEpi {
   EPI_STORE = 0,    // C = alpha * acc (+ bias[n] when bias != nullptr)
   EPI_GELU = 1,     // u = acc + bias[n]:  GELU(u) -> C;  GELU'(u) -> C2
   EPI_MUL = 2,      // C = acc * aux[m, n]  (the FFN backward: dU = dG * GELU'(u))
-  EPI_RESID = 3,    // C = acc + aux[m, n]
+  EPI_RESID = 3,    // C = acc + aux[m, n]  (fp32)
   EPI_PARTIAL = 4,  // fp32 C[split][m][n] = acc over this split's K range
   EPI_DSUM = 5,     // C = acc (dO), and per row and head (64 columns) of C as stored
                     // the sum over its columns of C * (aux + aux2): rowsum(dO * O)
@@ -53,7 +53,6 @@ struct GemmArgs {
   // sC2 + n].
   float* colpart;
   int64_t cp_batch, cp_ld;
-  int zdiv_total;  // internal: batch * ksplit
 };
 
 inline GemmArgs gemm_args(const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
