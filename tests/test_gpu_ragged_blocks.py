@@ -1,12 +1,15 @@
-"""bf16 stages over an odd number of 128-token blocks.
+"""bf16 stages over an odd number of row blocks of the FFN2 data gradient's
+column sums.
 
-The FFN2 data-gradient GEMM walks 256-row tiles and writes one row of column
-sums per 128 rows; the buffer holds ceil(T / 128) rows, so with an odd number
-of them the last tile's second half has no row of its own.  540 and 825
-tokens put that row beyond the end of a page of the buffer (5 x 768 x 4 =
-15360 and 7 x 1024 x 4 = 28672 bytes held), 96 inside its only page.  Checked
-against the oracle with the bf16 tolerance of the gradients (relative L2
-1e-2)."""
+The 256 x 256 tiles of that GEMM write one row of column sums per 128 rows; the
+buffer holds ceil(T / 128) of them (twice that up to 4096 tokens, for 64-row
+tiles), so with an odd number the last tile's second half has no row of its own:
+1025 and 8200 tokens, the latter in a buffer without room to spare.  The smaller
+sizes take 64 x 64 tiles, one row per 64 rows, with a ragged last one (540, 825)
+and a full one (96: two).  Checked against the oracle with the bf16 tolerance of
+the gradients (relative L2 1e-2)."""
+import ctypes
+
 import pytest
 
 import synth
@@ -15,10 +18,24 @@ from _parity import rel_l2, run_gpu, run_oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("hidden,ffn,batch,seq", [(192, 768, 30, 18), (256, 1024, 5, 165),
-                                                  (128, 512, 3, 32)])
-def test_odd_block_count(hidden, ffn, batch, seq):
+class Plan(ctypes.Structure):
+    _fields_ = [("tile", ctypes.c_int), ("ks", ctypes.c_int)]
+
+
+def tile_of_ffn2_dgrad(tokens, hidden, ffn):
+    """1: 256 x 256, 5: 64 x 64 (the rule's choice on this device)."""
+    from paper_2202_11836_amd import load_library
+    plan = load_library()._Z14gemm_bf16_planiiib7GemmEpib
+    plan.restype = Plan
+    return plan(tokens, ffn, hidden, False, 2, False).tile
+
+
+@pytest.mark.parametrize("hidden,ffn,batch,seq,tile", [
+    (192, 768, 30, 18, 5), (256, 1024, 5, 165, 5), (128, 512, 3, 32, 5), (128, 8192, 5, 205, 1),
+    (320, 1280, 41, 200, 1)])
+def test_odd_block_count(hidden, ffn, batch, seq, tile):
     assert (batch * seq + 127) // 128 % 2 == 1
+    assert tile_of_ffn2_dgrad(batch * seq, hidden, ffn) == tile
     print(f"h {hidden} f {ffn} B {batch} S {seq}", flush=True)
     cfg = synth.StageConfig("odd", 1, hidden, hidden // 64, ffn, batch, seq, max(1, seq // 2), seq,
                             "bf16", 5)
