@@ -355,8 +355,8 @@ __global__ __launch_bounds__((TileCfg<BM, BN>::THREADS), 1) void gemm_bf16_kerne
     // halves have requested the same k-tiles, so that wait is unchanged.
     // Measured (same box): encoder GEMM set -3.9%, weight-gradient group -5%,
     // 8192^3 -3%; splitting the pairs the other way (even / odd wavefronts) or
-    // each wavefront's own loads in two gave -0.3% to -1.6%; requesting the second half one or two k-steps later
-    // was slower than not splitting.
+    // each wavefront's own loads in two gave -0.3% to -1.6%; requesting the
+    // second half one or two k-steps later was slower than not splitting.
     for (int t = 0; t < ntiles; ++t) {
       static_for<0, KS>([&](auto ksc) {
         constexpr int ks = decltype(ksc)::value;

@@ -592,7 +592,9 @@ bool vec_ok(const GemmArgs& g, bool ak, bool bk) {
                       (bk ? g.K : g.N);
   return (any & 3) == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
 }
-// A load's offsets span at most 8 rows and one k extent (32-bit bytes).
+// A load's offsets are 32-bit bytes below OOB.  k-major: 7 rows and the k extent,
+// less than 7 x 2^27 + 2^30; m/n-major: up to 15 k-rows (16 x 16 tiles), less than
+// 15 x 2^27.
 bool fits(const GemmArgs& g) {
   const int64_t k = g.K;
   return std::max(g.lda, g.ldb) < ((int64_t)1 << 25) && k * 4 < ((int64_t)1 << 30);

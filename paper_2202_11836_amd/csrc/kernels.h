@@ -278,7 +278,8 @@ hipError_t softmax_bwd(const float* dP, const T* P, T* dS, int BH, int S, int ld
 //   lse:  [B*H, S] fp32 log2-sum-exp of the scaled scores (forward output)
 //   o, dout: forward context and its gradient [B*S, h] (backward inputs)
 //   out_lo / o_lo: the context's bf16 rounding residual [B*S, h]
-//   dsum: [B*H, S] fp32 rowsum(dO * O) (written by attn_backward_dq)
+//   dsum: [B*H, S] fp32 rowsum(dO * O) (written by attn_backward_dq, or by the
+//   EPI_DSUM product that makes dO)
 // ---------------------------------------------------------------------------
 struct AttnArgs {
   // backward, optional: column sums of dQKV per 32-row block of each

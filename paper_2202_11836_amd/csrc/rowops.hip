@@ -1,6 +1,7 @@
 // HBM-bound row kernels of the encoder layer: residual + bias + LayerNorm
-// (forward and backward), deterministic column reductions for the bias /
-// gamma / beta gradients, and the masked row softmax (forward and backward).
+// (forward and backward), the column partial sums of the gamma / beta / bias
+// gradients (reduced by the units of tail.h), and the masked row softmax of long
+// fp32 sequences (forward and backward).
 // One wavefront owns one row; reductions across the row are wavefront
 // shuffles.  No MFMA here.
 #include <algorithm>
@@ -539,8 +540,15 @@ hipError_t add_ln_fwd(const TA* a, int np, const float* bias, const T* resid, co
 }
 
 // 32 rows per work-group (two row pairs per wavefront and eight loads of them
-// in flight hide HBM latency); fewer when that leaves less than one work-group
-// per CU: 2048 rows of 768 took 15.5 us in 64 work-groups.
+// in flight hide HBM latency) above 4096 rows, then half as many at each power of
+// two, so that 1024, 2048 and 4096 rows are 256 work-groups, one per CU (2048 rows
+// of 768 took 15.5 us in 64 work-groups), and between them there are 129 to 256.
+// Not more: rows wider than 1024 leave room for one work-group per CU, and with
+// the lines at 2040, 4080 and 8160 rows (129 to 510 work-groups) width 2048 went
+// from 17.7 to 22.7 us at 1536 rows, 23.4 to 28.9 at 2064 and 38.8 to 43.7 at
+// 5040.  Widths up to 1024 have room for two and are faster that way (768: 20.9
+// -> 17.9 us at 5040 rows, 12.8 -> 11.4 at 2064, unchanged up to 2040); a line per
+// width is not drawn.
 int ln_bwd_rpb(int rows) { return rows > 4096 ? 32 : rows > 2048 ? 16 : rows > 1024 ? 8 : 4; }
 int ln_bwd_blocks(int rows) { return (rows + ln_bwd_rpb(rows) - 1) / ln_bwd_rpb(rows); }
 int ln_bwd_blocks_max(int rows) {
