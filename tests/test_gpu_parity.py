@@ -326,3 +326,31 @@ def test_bf16_smaller_batches_after_the_full_batch():
             assert batch == 32 or (st.device_bytes() > held) == (batch == 20)
     finally:
         st.close()
+
+
+def test_bf16_attention_backward_in_two_launches():
+    """dQ with its own rowsum(dO * O), then dK and dV (token counts whose
+    out-projection data gradient takes 256 x 256 tiles): B30 x S410, a key mask
+    that is not a prefix and one sequence with no valid key.  dy is zero outside
+    three sequences; the oracle runs only those."""
+    from _parity import make_stage
+    cfg = synth.StageConfig("two", 1, 1024, 16, 256, 30, 410, 1, 410, "bf16", 34)
+    _say(f"case bf16 attention backward in two launches {cfg}")
+    inp = synth.make_inputs(cfg)
+    mask = (np.random.default_rng(2).random((cfg.batch, cfg.seq)) < 0.6).astype(np.uint8)
+    mask[1] = 0
+    mask[29, -1] = 1
+    inp["mask"] = mask
+    params = synth.make_params(cfg, perturb=True)
+    sel = np.zeros(cfg.batch, bool)
+    sel[[0, 1, 29]] = True
+    dy = inp["dy"].copy()
+    dy[~sel] = 0.0
+    st = make_stage(cfg, params)
+    st.trace(["attn_bwd_dq", "attn_bwd_dkdv"])
+    got = run_gpu(cfg, inp, params, dy=dy, stage=st, saved=(0, 3))
+    assert st.trace_read()[0] == 2
+    lw = check_bf16_layerwise(cfg, inp, params, got, seqs=np.flatnonzero(sel))
+    ref = run_oracle(cfg.with_(batch=3), {"x": inp["x"][sel], "mask": mask[sel], "dy": dy[sel]}, params)
+    assert_bf16(lw, check_bf16(cfg, got, ref, rows=sel))
+    st.close()
