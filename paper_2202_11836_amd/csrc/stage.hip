@@ -607,15 +607,19 @@ AttnF32Args attn_f32_args(stage_t* s, const float* qkv, void* P, float* out, int
 // device's memory; an extent the runtime has to judge) goes through a runtime
 // copy, which reads it or refuses it.
 bool reads_in_place(const void* p, size_t n, int device) {
-  hipPointerAttribute_t at{};
-  hipDeviceptr_t base = nullptr;
+  int type = 0, dev = -1, managed = 0;
   size_t size = 0;
-  const bool ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice &&
-                  !at.isManaged && at.device == device &&
-                  hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) == hipSuccess &&
-                  (size_t)((const char*)p - (const char*)base) + n <= size;
-  if (!ok) (void)hipGetLastError();  // (a failed query leaves an error behind)
-  return ok;
+  const char* base = nullptr;
+  hipPointer_attribute what[] = {HIP_POINTER_ATTRIBUTE_MEMORY_TYPE, HIP_POINTER_ATTRIBUTE_DEVICE_ORDINAL,
+                                 HIP_POINTER_ATTRIBUTE_IS_MANAGED, HIP_POINTER_ATTRIBUTE_RANGE_SIZE,
+                                 HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR};
+  void* to[] = {&type, &dev, &managed, &size, &base};
+  if (hipDrvPointerGetAttributes(5, what, to, (hipDeviceptr_t)p) != hipSuccess) {
+    (void)hipGetLastError();  // (a failed query leaves an error behind)
+    return false;
+  }
+  const size_t at = (size_t)((const char*)p - base);
+  return type == hipMemoryTypeDevice && !managed && dev == device && at <= size && n <= size - at;
 }
 
 template <typename T>
